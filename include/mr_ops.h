@@ -116,9 +116,11 @@ int mr_distance_transform(const void *img, void *dist, int64_t H, int64_t W, int
  * index y * W + x of its G-connected component, background pixels 0: the
  * root of each union-find tree is its smallest element, so the labels are
  * unique and independent of the order of the merges. H * W < 2^31 - 1.
- * Three launches: union-find inside 32 x 64 tiles in LDS, merges of the
- * trees across tile borders with device atomics, and flattening. Workspace:
- * the forest, 4 bytes per pixel. Errors: MR_EINVAL, MR_ENOMEM, MR_EHIP. */
+ * Three launches: union-find of horizontal runs inside 64 x 64 tiles in LDS,
+ * merges of the trees across tile borders with device atomics, and the labels
+ * written. Workspace: the forest, 4 bytes per pixel. img is read in aligned
+ * 32-bit words that hold at least one of its pixels. Errors: MR_EINVAL,
+ * MR_ENOMEM, MR_EHIP. */
 size_t mr_ccl_workspace_bytes(int64_t H, int64_t W);
 int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,
            int64_t label_pitch, int conn, void *ws, size_t ws_bytes, void *stream);
@@ -129,7 +131,10 @@ int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,
  * area lies outside [min_area, max_area] is set to 0 (min_area > max_area
  * removes every object). After the call the workspace starts with the
  * H * W + 1 per-label areas as int32 (entry l = area of label l; entry 0
- * unused), for callers that want them. Labels outside [0, H * W] are neither
+ * unused), for callers that want them. A workspace of just these
+ * (H * W + 1) * 4 bytes, rounded up to 256, is accepted; the size the query
+ * gives holds a further bit per four labels, which spares the filter a second
+ * read of the background. Labels outside [0, H * W] are neither
  * counted nor changed. Errors: MR_EINVAL, MR_ENOMEM, MR_EHIP. */
 size_t mr_area_threshold_workspace_bytes(int64_t H, int64_t W);
 int mr_area_threshold(void *labels_inout, int64_t H, int64_t W, int64_t pitch, int64_t min_area,

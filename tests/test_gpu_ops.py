@@ -236,3 +236,48 @@ def test_area_threshold_random_labels(H, W, pad):
         d = to_dev(lab, pad=pad)
         ops.area_threshold(d, lo, hi)
         check(d.cpu().numpy(), oracle.area_threshold(lab, lo, hi)[0], f"[{lo},{hi}]: ")
+
+
+# Tile edges of the labelling's 64 x 64 tiles, with image rows at every
+# alignment and label planes that allow 16-byte stores or not; nearly empty
+# tiles (early outs) and dense ones (32 runs a row).
+@pytest.mark.parametrize("shape,pad,lpad", [((64, 64), 0, 0), ((65, 129), 0, 0), ((128, 192), 3, 4),
+                                            ((127, 66), 1, 0), ((190, 97), 2, 5), ((3, 256), 0, 1)])
+@pytest.mark.parametrize("conn", [4, 8])
+def test_ccl_tile_edges(shape, pad, lpad, conn):
+    H, W = shape
+    rng = np.random.default_rng(H * 7 + W + conn)
+    checker = (np.add.outer(np.arange(H), np.arange(W)) % 2).astype(np.uint8)
+    border = np.zeros(shape, np.uint8)  # pixels that touch only across tile borders
+    border[63::64], border[64::64] = rng.random((2, 1, W)) < 0.4
+    border[:, 63::64] |= (rng.random((H, 1)) < 0.4).astype(np.uint8)
+    border[:, 64::64] |= (rng.random((H, 1)) < 0.4).astype(np.uint8)
+    dot = np.zeros(shape, np.uint8)
+    dot[H - 1, W - 1] = 7
+    stripes = np.zeros(shape, np.uint8)
+    stripes[:, ::2] = 255
+    for img in (checker, border, dot, stripes, (rng.random(shape) < 0.55).astype(np.uint8)):
+        out = torch.full((H, W + lpad), -9, dtype=torch.int32, device=DEV)
+        ops.ccl(to_dev(img, pad), conn, out=out[:, :W])
+        check(out[:, :W].cpu().numpy(), oracle.ccl(img, conn))
+        assert bool((out[:, W:] == -9).all())
+
+
+# The area threshold's word path on gapless planes of any length (words past
+# the last whole one, chunks past the last whole 64 words) and with a workspace
+# that has no room for the marks; sparse and dense planes.
+@pytest.mark.parametrize("H,W", [(1, 3), (1, 5), (7, 37), (64, 65), (129, 131), (40, 1024)])
+@pytest.mark.parametrize("p", [0.02, 0.9])
+def test_area_threshold_words(H, W, p):
+    rng = np.random.default_rng(H * W)
+    lab = np.where(rng.random((H, W)) < p, rng.integers(1, min(9, H * W) + 1, (H, W)), 0).astype(np.int32)
+    lab.reshape(-1)[-1] = 1
+    n = np.bincount(lab.reshape(-1), minlength=H * W + 1)
+    n[0] = 0
+    for lo, hi in [(0, 10**9), (2, int(np.median(n[n > 0])))]:
+        want = np.where((lab > 0) & ((n[lab] < lo) | (n[lab] > hi)), 0, lab)
+        for room in (None, torch.empty((4 * (H * W + 1) + 255) // 256 * 256, dtype=torch.uint8, device=DEV)):
+            d = to_dev(lab)
+            _, ws = ops.area_threshold(d, lo, hi, workspace=room)
+            check(d.cpu().numpy(), want, f"[{lo},{hi}]: ")
+            check(ws[: 4 * (H * W + 1)].view(torch.int32).cpu().numpy(), n.astype(np.int32))
