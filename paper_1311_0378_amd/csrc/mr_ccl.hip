@@ -60,6 +60,7 @@ int chip(hipError_t e, const char *what) {
 size_t up256(size_t n) { return (n + 255) / 256 * 256; }
 
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
 
 constexpr int CT = 64;              // tile side: a row is one 64-bit mask, lane = row
 constexpr int CT_RUNS = CT / 2;     // a row holds at most this many runs
@@ -180,9 +181,12 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
     uint64_t *row_of = rows[wv];
     {
         const int c0 = 16 * (lane & 3);
-        const bool whole = c0 + 16 <= (int)T.w;
         uint32_t bits[4];
-        if (whole) {
+        if (W >= 16) {
+            // a chunk that leaves the image on the right loads the image's last
+            // 16 columns, and its bits are shifted back
+            const int cs = std::min(c0, (int)(W - 16) - (int)T.x0);
+            const int back = std::min(16, c0 - cs);
             // Aligned words that hold the 16 pixels: a fifth word where the
             // pixels are not word-aligned (it holds the last of them, so no
             // word is read that holds none).
@@ -191,7 +195,7 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t r = std::min<uint32_t>(16 * j + (lane >> 2), T.h - 1);
-                const uintptr_t a = (uintptr_t)(img + (int64_t)(T.y0 + r) * pitch + T.x0 + c0);
+                const uintptr_t a = (uintptr_t)(img + (int64_t)(T.y0 + r) * pitch + (int64_t)T.x0 + cs);
                 const uint32_t *q = (const uint32_t *)(a & ~(uintptr_t)3);
                 sh[j] = (uint32_t)(a & 3);
                 __builtin_memcpy(&d[j], q, 16);
@@ -199,17 +203,19 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
             }
 #pragma unroll
             for (int j = 0; j < 4; ++j)
-                bits[j] = nonzero_bits(__builtin_amdgcn_alignbyte(d[j].y, d[j].x, sh[j])) |
-                          nonzero_bits(__builtin_amdgcn_alignbyte(d[j].z, d[j].y, sh[j])) << 4 |
-                          nonzero_bits(__builtin_amdgcn_alignbyte(d[j].w, d[j].z, sh[j])) << 8 |
-                          nonzero_bits(__builtin_amdgcn_alignbyte(d4[j], d[j].w, sh[j])) << 12;
+                bits[j] = (nonzero_bits(__builtin_amdgcn_alignbyte(d[j].y, d[j].x, sh[j])) |
+                           nonzero_bits(__builtin_amdgcn_alignbyte(d[j].z, d[j].y, sh[j])) << 4 |
+                           nonzero_bits(__builtin_amdgcn_alignbyte(d[j].w, d[j].z, sh[j])) << 8 |
+                           nonzero_bits(__builtin_amdgcn_alignbyte(d4[j], d[j].w, sh[j])) << 12) >>
+                          back;
         } else {
 #pragma unroll
             for (int j = 0; j < 4; ++j) {
                 const uint32_t r = std::min<uint32_t>(16 * j + (lane >> 2), T.h - 1);
                 const uint8_t *p = img + (int64_t)(T.y0 + r) * pitch + T.x0;
                 bits[j] = 0;
-                for (int k = 0; c0 + k < (int)T.w; ++k) bits[j] |= (p[c0 + k] ? 1u : 0u) << k;
+                for (int k = 0; k < 16 && c0 + k < (int)T.w; ++k)
+                    bits[j] |= (p[c0 + k] ? 1u : 0u) << k;
             }
         }
 #pragma unroll
@@ -380,12 +386,11 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_
 // listed in LDS in order, and each listed run's root looked up in the forest
 // by one lane; then every pixel takes its run's label from the list (the rank
 // of its run in the row) and the tile's labels are written, 16 bytes a lane
-// where rows allow it (VEC). Bound by the label write: 196 us on that image
+// (on any dword: rows of any width and pitch). Bound by the label write: 196 us on that image
 // (5.5 TB/s; the flatten pass it replaces read the plane the local phase had
 // written and took 242 us). The stores are streaming: the plane is four times
 // the last-level cache, and the call is 3 % faster than with cached ones.
 // Two or eight tiles a workgroup instead of four: 3 to 4 % slower calls.
-template <bool VEC>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_t W,
                                                              uint32_t tiles_x, uint32_t n_tiles,
                                                              uint32_t *labels, int64_t lpitch,
@@ -435,35 +440,28 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
         if (!((rm >> x) & 1)) return 0u;
         return list[base + (uint32_t)__popcll(rs & ((2ull << x) - 1)) - 1u];
     };
-    if (VEC) {
-        const int c = 4 * (lane & 15);
+    const int c = 4 * (lane & 15);
 #pragma unroll 4
-        for (int j = 0; j < CT / 4; ++j) {
-            const uint32_t r = 4 * j + (lane >> 4);
-            uint4 v = {0, 0, 0, 0};
-            if (any) {
-                const uint64_t rm = row_of[r];
-                if ((rm >> c) & 15) {
-                    const uint64_t rs = rm & ~(rm << 1);
-                    const uint32_t b = base_of[r];
-                    v = uint4{label(rm, rs, b, c), label(rm, rs, b, c + 1), label(rm, rs, b, c + 2),
-                              label(rm, rs, b, c + 3)};
-                }
+    for (int j = 0; j < CT / 4; ++j) {
+        const uint32_t r = 4 * j + (lane >> 4);
+        v4u v = {0, 0, 0, 0};
+        if (any) {
+            const uint64_t rm = row_of[r];
+            if ((rm >> c) & 15) {
+                const uint64_t rs = rm & ~(rm << 1);
+                const uint32_t b = base_of[r];
+                v = v4u{label(rm, rs, b, c), label(rm, rs, b, c + 1), label(rm, rs, b, c + 2),
+                        label(rm, rs, b, c + 3)};
             }
-            if (r < T.h && c < (int)T.w)
-                __builtin_nontemporal_store(
-                    v4u{v.x, v.y, v.z, v.w},
-                    (v4u *)(labels + (int64_t)(T.y0 + r) * lpitch + T.x0 + c));
         }
-    } else {
-#pragma unroll 4
-        for (uint32_t r = 0; r < T.h; ++r) {
-            uint32_t v = 0;
-            if (any) {
-                const uint64_t rm = row_of[r];
-                if (rm) v = label(rm, rm & ~(rm << 1), base_of[r], lane);
-            }
-            if ((uint32_t)lane < T.w) labels[(int64_t)(T.y0 + r) * lpitch + T.x0 + lane] = v;
+        if (r >= T.h) continue;
+        uint32_t *o = labels + (int64_t)(T.y0 + r) * lpitch + T.x0 + c;
+        if (c + 4 <= (int)T.w) {
+            __builtin_nontemporal_store(v, (v4u_dw *)o);
+        } else {
+            if (c < (int)T.w) o[0] = v.x;
+            if (c + 1 < (int)T.w) o[1] = v.y;
+            if (c + 2 < (int)T.w) o[2] = v.z;
         }
     }
 }
@@ -633,8 +631,9 @@ __global__ __launch_bounds__(256) void k_area_filter(int32_t *__restrict__ label
 
 // The word path of the filter: a word's 4 counter reads are in flight
 // together, and it is written back only if one of its labels was cleared. With
-// `marks` (see the count) a wave takes 64 chunks, lists the words that hold a
-// label in LDS and gives each lane one of them, so that planes of mostly
+// `marks` (see the count) a wave takes `group` chunks (64 of a large plane, fewer
+// of a small one, so that it still spreads over the chip: 1003 x 1021 labels
+// took 13 us in groups of 64), lists the words that hold a label in LDS and gives each lane one of them, so that planes of mostly
 // background are not read again; a wave whose words are mostly marked, and
 // planes without marks, go chunk by chunk. 16384 x 16384 labels, 1.6 % of
 // them foreground: 22 us with marks, 222 us reading every word.
@@ -642,7 +641,7 @@ template <bool LIN>
 __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labels, uint32_t N,
                                                       uint32_t NQ, uint32_t Wq, int64_t pitch,
                                                       const int32_t *__restrict__ area, int64_t lo,
-                                                      int64_t hi,
+                                                      int64_t hi, uint32_t group,
                                                       const uint64_t *__restrict__ marks) {
     constexpr uint32_t LIST = 2048; // listed words of a wave's 4096
     __shared__ uint16_t lists[4][LIST];
@@ -660,9 +659,9 @@ __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labe
         const int4 o = {keep(l.x), keep(l.y), keep(l.z), keep(l.w)};
         if (o.x != l.x || o.y != l.y || o.z != l.z || o.w != l.w) *p = o;
     };
-    for (uint32_t c0 = wave * 64u; c0 < chunks; c0 += waves * 64u) {
-        uint64_t w = c0 + lane < chunks ? ~0ull : 0ull;
-        uint32_t total = 64 * 64;
+    for (uint32_t c0 = wave * group; c0 < chunks; c0 += waves * group) {
+        uint64_t w = (uint32_t)lane < group && c0 + lane < chunks ? ~0ull : 0ull;
+        uint32_t total = LIST + 1;
         if (marks) {
             if (w) w = marks[c0 + lane];
             const uint32_t n = (uint32_t)__popcll(w);
@@ -686,7 +685,7 @@ __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labe
                 continue;
             }
         }
-        for (int k = 0; k < 64; k += AREA_UNROLL) {
+        for (uint32_t k = 0; k < group; k += AREA_UNROLL) {
             int4 q[AREA_UNROLL];
 #pragma unroll
             for (int j = 0; j < AREA_UNROLL; ++j) {
@@ -763,11 +762,7 @@ int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,
                            tiles, L, label_pitch, F);
         hipLaunchKernelGGL(k_ccl_merge<4>, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
     }
-    // 16-byte label stores where every row's groups of four are whole and aligned
-    if (W % 4 == 0 && label_pitch % 4 == 0 && (uintptr_t)labels % 16 == 0)
-        hipLaunchKernelGGL(k_ccl_write<true>, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
-    else
-        hipLaunchKernelGGL(k_ccl_write<false>, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
+    hipLaunchKernelGGL(k_ccl_write, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? MR_OK : chip(e, "ccl");
 }
@@ -802,17 +797,19 @@ int mr_area_threshold(void *labels_inout, int64_t H, int64_t W, int64_t pitch, i
         const uint32_t wq = (uint32_t)(W / 4), chunks = (NQ + 63) / 64;
         const unsigned gc = std::min<unsigned>((chunks + 4 * AREA_UNROLL - 1) / (4 * AREA_UNROLL),
                                                AREA_BLOCKS);
-        const unsigned gf = std::min<unsigned>((chunks + 255) / 256, AREA_BLOCKS);
+        // chunks a wave of the filter takes: 4 waves a SIMD before it grows
+        const uint32_t group = std::max(4u, std::min(64u, chunks / 4096 / 4 * 4));
+        const unsigned gf = std::min<unsigned>((chunks + 4 * group - 1) / (4 * group), AREA_BLOCKS);
         if (lin) {
             hipLaunchKernelGGL(k_area_count4<true>, dim3(gc), dim3(256), 0, s, l, N, NQ, wq, pitch,
                                area, marks);
             hipLaunchKernelGGL(k_area_filter4<true>, dim3(gf), dim3(256), 0, s, l, N, NQ, wq, pitch,
-                               (const int32_t *)area, min_area, max_area, marks);
+                               (const int32_t *)area, min_area, max_area, group, marks);
         } else {
             hipLaunchKernelGGL(k_area_count4<false>, dim3(gc), dim3(256), 0, s, l, N, NQ, wq, pitch,
                                area, marks);
             hipLaunchKernelGGL(k_area_filter4<false>, dim3(gf), dim3(256), 0, s, l, N, NQ, wq,
-                               pitch, (const int32_t *)area, min_area, max_area, marks);
+                               pitch, (const int32_t *)area, min_area, max_area, group, marks);
         }
     } else {
         hipLaunchKernelGGL(k_area_count, dim3(grid_for(H * W)), dim3(256), 0, s,
