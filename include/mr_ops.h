@@ -99,9 +99,11 @@ int mr_disk13(int op, const void *in, void *out, int64_t H, int64_t W, int64_t p
  * shortest path to a background (zero) pixel: conn 8 gives the chessboard
  * distance max(|dy|, |dx|), conn 4 the city-block distance |dy| + |dx|;
  * background pixels get 0, and every pixel gets -1 when the image has no
- * background pixel. The result is unique. Computed as wavefront propagation
+ * background pixel. The result is unique. A first pass settles distances up
+ * to 16 from the image's bits; what is further goes by wavefront propagation
  * over 64 x 64 tiles, revisiting tiles whose border changed until no tile
- * changes (the host waits on a small counter between batches of rounds).
+ * changes (the host waits on a small counter between batches of rounds). img
+ * is read in aligned 32-bit words that hold at least one of its pixels.
  * Errors: MR_EINVAL, MR_ENOMEM, MR_EHIP. */
 size_t mr_distance_transform_workspace_bytes(int64_t H, int64_t W, int conn);
 int mr_distance_transform(const void *img, void *dist, int64_t H, int64_t W, int64_t pitch,

@@ -281,3 +281,34 @@ def test_area_threshold_words(H, W, p):
             _, ws = ops.area_threshold(d, lo, hi, workspace=room)
             check(d.cpu().numpy(), want, f"[{lo},{hi}]: ")
             check(ws[: 4 * (H * W + 1)].view(torch.int32).cpu().numpy(), n.astype(np.int32))
+
+
+# The distance transform's first pass settles distances up to 16 in windows of
+# 96 x 96 pixels (16 more on each side): distances around that bound, deep
+# objects that later rounds finish, background only in a margin or only far
+# away, image rows and distance rows at every alignment, ragged windows.
+@pytest.mark.parametrize("shape,pad,dpad", [((96, 96), 0, 0), ((97, 193), 0, 0), ((111, 112), 1, 3),
+                                            ((113, 95), 4, 0), ((200, 309), 2, 1), ((2, 400), 0, 0),
+                                            ((400, 3), 5, 2)])
+@pytest.mark.parametrize("conn", [4, 8])
+def test_dt_first_pass_bounds(shape, pad, dpad, conn):
+    H, W = shape
+    rng = np.random.default_rng(H + 3 * W + conn)
+    images = []
+    for step in (15, 16, 17, 18, 33, 34, 40):  # largest distances around the bound
+        img = np.full(shape, 3, np.uint8)
+        img[::2 * step, ::2 * step] = 0
+        images.append(img)
+        img = np.full(shape, 255, np.uint8)
+        img[:, ::2 * step] = 0
+        images.append(img)
+    for y, x in ((0, 0), (H - 1, W - 1), (H // 2, W // 2)):  # one background pixel
+        img = np.ones(shape, np.uint8)
+        img[y, x] = 0
+        images.append(img)
+    images += [(rng.random(shape) < p).astype(np.uint8) for p in (0.03, 0.5, 0.97, 0.9995)]
+    for img in images:
+        out = torch.full((H, W + dpad), -7, dtype=torch.int32, device=DEV)
+        ops.distance_transform(to_dev(img, pad), conn, out=out[:, :W])
+        check(out[:, :W].cpu().numpy(), oracle.distance_transform(img, conn))
+        assert bool((out[:, W:] == -7).all())
