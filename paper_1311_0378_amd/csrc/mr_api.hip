@@ -84,11 +84,13 @@ Layout layout_for(int64_t n_tiles, int64_t fill_plane_bytes, int64_t plane_pitch
 
 int64_t tiles_across(int64_t n) { return (n + TI - 1) / TI; }
 
-// uint8 planes whose base and pitch are multiples of 16 bytes: the tile
-// loads then move whole aligned 16-byte words (and the rounds may prefetch)
+// uint8 planes that the tile kernels' 32-bit buffer offsets reach (any base and
+// pitch; a full 2^32-pixel plane goes without): their rounds are pipelined
 bool staged_planes(int t, const ImgDesc &d) {
-    const auto a16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
-    return t == MR_U8 && a16(d.J) && a16(d.I) && d.pJ % 16 == 0 && d.pI % 16 == 0;
+    const auto reach = [&](const void *p, int64_t pitch) {
+        return ((uintptr_t)p & 15) + (uint64_t)((d.H - 1) * pitch + d.W) + 3 <= STAGE_MAX_BYTES;
+    };
+    return t == MR_U8 && reach(d.J, d.pJ) && reach(d.I, d.pI);
 }
 
 bool valid_dtype(int t) { return t == MR_U8 || t == MR_I32; }

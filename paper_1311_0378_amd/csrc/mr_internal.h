@@ -36,6 +36,11 @@ struct ImgDesc {
     uint32_t *wide;
 };
 
+// Bytes of a uint8 plane, from its base rounded down to 16, that tile loads
+// with 32-bit buffer offsets reach: offsets up to 80 bytes past a row's start
+// must not wrap.
+constexpr uint64_t STAGE_MAX_BYTES = 0xFFFFFE00ull;
+
 // Device control block at the start of every workspace. Contended words sit
 // on their own 128-byte lines.
 struct alignas(128) Line {
@@ -78,8 +83,8 @@ struct Imgs {
     const ImgDesc *d;
     int32_t n;
     const uint32_t *owner;
-    // 1 when every image is uint8 with 16-byte aligned planes and pitches
-    // (both J and I): the tile rounds may then use the pipelined kernel
+    // 1 when every image is uint8 and its planes (J and I) lie within the
+    // range of a buffer offset: the tile rounds then use the pipelined kernel
     int32_t staged;
     // 1 when the images have widened planes for the queue phase
     int32_t wide;

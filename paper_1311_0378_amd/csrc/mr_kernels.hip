@@ -158,79 +158,102 @@ __device__ __forceinline__ void wave_sync() {
 }
 
 
-// Buffer resource over one uint8 plane of `bytes` bytes, used only when the
-// plane base and pitch are multiples of 16, so every 16-byte chunk load is
+// Buffer resource over `bytes` bytes (whole dwords) from a 16-byte aligned
+// address, so every 16-byte chunk load is
 // aligned and the per-dword range check matches whole memory words. Loads past
 // the end, or at the huge offsets used for rows outside the image, return 0.
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t plane_rsrc(const void *p, uint64_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0,
-                                             (int)(bytes < 0xFFFFFFF0ull ? (uint32_t)bytes : 0xFFFFFFF0u),
+    return __builtin_amdgcn_make_buffer_rsrc((void *)p, (short)0, (int)(uint32_t)bytes,
                                              0x00020000);
 }
 
-__device__ __forceinline__ bool stage_ok(const void *p, int64_t pitch) {
-    return ((uintptr_t)p & 15) == 0 && (pitch & 15) == 0;
+// Bytes from the aligned start of a uint8 plane's resource to the end of its
+// last pixel's dword.
+__device__ __forceinline__ uint64_t plane_bytes(const void *p, int64_t H, int64_t W,
+                                                int64_t pitch) {
+    return (((uint64_t)((uintptr_t)p & 15) + (uint64_t)((H - 1) * pitch + W)) + 3) & ~3ull;
 }
 
-// uint8 staging: row r of a tile (image row gy0 + r) is fetched as five
-// 16-byte chunks covering image columns a .. a+79, a = gx0 rounded down to 16,
-// and kept in LDS at r * SROW. SROW is an odd number of dwords, so the row
-// writes (lane = row) and the column reads (lane = column) are both free of
-// bank conflicts.
+// Any uint8 plane whose bytes a 32-bit buffer offset reaches can be staged.
+__device__ __forceinline__ bool stage_ok(const ImgDesc &d) {
+    return plane_bytes(d.I, d.H, d.W, d.pI) <= STAGE_MAX_BYTES &&
+           plane_bytes(d.J, d.H, d.W, d.pJ) <= STAGE_MAX_BYTES;
+}
+
+// uint8 staging: the 64 pixels of tile row r (image row gy0 + r, columns gx0..)
+// lie in five aligned 16-byte chunks. Lane r fetches them, shifts its words by
+// the row's byte misalignment (rows of an odd pitch each have their own), and
+// writes them to LDS displaced by its word misalignment, so that column c of
+// the tile is byte c of the stage row whatever the plane's base and pitch.
+// A stage row is an odd number of dwords, so the row writes (lane = row) and the
+// column reads (lane = column) are both free of bank conflicts; of the words
+// a row writes outside its 16, up to 3 come before it and 4 after it, and all
+// land behind the pixels of a row (its own or the one before), or in the
+// STAGE_PAD bytes before the first.
 constexpr int SROW = 84;
 // Cache policy of loads that must see other compute units' stores at device
 // scope (sc1: not served from a compute unit's or a die's non-coherent cache).
 constexpr int CPOL_DEVICE = 16;
+constexpr int STAGE_PAD = 16;
 constexpr int STAGE_BYTES = TS * SROW;
-static_assert(2 * STAGE_BYTES <= TS * (TS + 1) * 4, "the stage must fit in the transpose buffer");
+static_assert(STAGE_PAD + 2 * STAGE_BYTES <= TS * (TS + 1) * 4,
+              "the stage must fit in the transpose buffer");
 
 typedef uint32_t v4u __attribute__((ext_vector_type(4)));
 
-// Lane r fetches tile row r, chunk k per load. Staged planes have a pitch of
-// at least 16 and H * pitch < 2^32, so rows and offsets fit 32 bits. The lane
+// Byte offset of pixel (gy, gx) from the plane's aligned start (mod 2^32: a
+// tile at the image's left edge starts before its row, in row 0 before the
+// plane, where the offset wraps out of the resource's range).
+__device__ __forceinline__ uint32_t stage_offset(const void *p, int32_t gy, uint32_t pitch,
+                                                 int64_t gx0) {
+    return (uint32_t)((uintptr_t)p & 15) + (uint32_t)gy * pitch + (uint32_t)(int32_t)gx0;
+}
+
+// The five chunks of lane's row. The lane
 // id goes through an empty asm so that nothing derived from it is hoisted out
 // of the caller's tile loop: held across the sweeps, such values would be
 // spilled, and every reload would wait for all memory operations in flight.
+// Pixels of chunks outside the image are whatever lies there in the plane, or
+// 0 out of its range; the tile masks them.
 template <int CPOL = 0>
-__device__ __forceinline__ void stage_issue(__amdgpu_buffer_rsrc_t rs, int64_t gy0, int64_t H,
-                                            uint32_t pitch, int64_t a, int lane, v4u (&v)[5],
+__device__ __forceinline__ void stage_issue(const void *p, int64_t gy0, int64_t gx0, int64_t H,
+                                            int64_t W, int64_t pitch, int lane, v4u (&v)[5],
                                             bool live = true) {
+    const __amdgpu_buffer_rsrc_t rs =
+        plane_rsrc((const void *)((uintptr_t)p & ~(uintptr_t)15), plane_bytes(p, H, W, pitch));
     uint32_t ln = (uint32_t)lane;
     asm volatile("" : "+v"(ln));
     const int32_t gy = (int32_t)gy0 + (int32_t)ln;
     const bool rowok = live && gy >= 0 && gy < (int32_t)H;
-    uint32_t off = (uint32_t)gy * pitch + (uint32_t)(int32_t)a;
+    uint32_t off = rowok ? stage_offset(p, gy, (uint32_t)pitch, gx0) & ~15u : 0xFFFFFF00u;
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        // a + 16 k < 0 only for chunk 0 of a tile at the left image edge;
-        // below row 0 it reads the end of the previous row (outside pixels,
-        // masked out later), in row 0 it is out of range
-        const bool in = rowok && (gy > 0 || a + 16 * k >= 0);
-        v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, in ? off : 0xFFFFFFF0u, 0, CPOL);
+        v[k] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, CPOL);
         off += 16;
     }
 }
 
-// Row `lane` of the stage at st gets the 80 bytes fetched by stage_issue.
-__device__ __forceinline__ void stage_commit(const v4u (&v)[5], int lane, uint8_t *st) {
+// Row `lane` of the stage at st gets the words fetched by stage_issue, each
+// exclusive-ored with `flip`.
+__device__ __forceinline__ void stage_commit(const v4u (&v)[5], const void *p, int64_t gy0,
+                                             int64_t gx0, int64_t pitch, int lane, uint8_t *st,
+                                             uint32_t flip) {
     uint32_t ln = (uint32_t)lane;
     asm volatile("" : "+v"(ln));
-    uint32_t *w = (uint32_t *)(st + ln * SROW);
+    const uint32_t mis = stage_offset(p, (int32_t)gy0 + (int32_t)ln, (uint32_t)pitch, gx0) & 15u;
+    uint32_t *w = (uint32_t *)(st + ln * SROW) - (mis >> 2);
+    const uint32_t sh = mis & 3u;
+    uint32_t x[21];
 #pragma unroll
     for (int k = 0; k < 5; ++k) {
-        w[4 * k + 0] = v[k].x;
-        w[4 * k + 1] = v[k].y;
-        w[4 * k + 2] = v[k].z;
-        w[4 * k + 3] = v[k].w;
+        x[4 * k + 0] = v[k].x;
+        x[4 * k + 1] = v[k].y;
+        x[4 * k + 2] = v[k].z;
+        x[4 * k + 3] = v[k].w;
     }
-}
-
-template <int CPOL = 0>
-__device__ __forceinline__ void stage_u8(__amdgpu_buffer_rsrc_t rs, int64_t gy0, int64_t H,
-                                         uint32_t pitch, int64_t a, int lane, uint8_t *st) {
-    v4u v[5];
-    stage_issue<CPOL>(rs, gy0, H, pitch, a, lane, v);
-    stage_commit(v, lane, st);
+    x[20] = 0;
+#pragma unroll
+    for (int k = 0; k < 20; ++k) w[k] = __builtin_amdgcn_alignbyte(x[k + 1], x[k], sh) ^ flip;
 }
 
 // A tile's stage rows in flight, held by value (mask words, working-image
@@ -240,27 +263,33 @@ struct StageWords {
     v4u i0, i1, i2, i3, i4, j0, j1, j2, j3, j4;
 };
 
-// Issue the stage loads of tile t of image d (uint8, staged planes); with
+// Where tile t of image d lies: tile row and column.
+__device__ __forceinline__ void tile_place(const ImgDesc &d, int64_t t, int &ty, int &tx) {
+    const uint32_t lt = (uint32_t)(t - d.tile_base); // (tile ids are below 2^31)
+    ty = (int)(lt / (uint32_t)d.ntx);
+    tx = (int)(lt - (uint32_t)ty * (uint32_t)d.ntx);
+}
+
+// Issue the stage loads of tile t of image d (uint8); with
 // live false every load is out of the buffer's range (zeros, no memory
-// access), so that the count of loads does not depend on the path.
-template <bool NEEDJ>
+// access), so that the count of loads does not depend on the path. CPOL is the
+// working image's cache policy.
+template <bool NEEDJ, int CPOL = 0>
 __device__ __forceinline__ StageWords stage_fetch(const ImgDesc &d, int64_t t, int lane,
                                                   bool live = true) {
-    const int64_t lt = t - d.tile_base;
-    const int ty = (int)(lt / d.ntx), tx = (int)(lt - (int64_t)ty * d.ntx);
+    int ty, tx;
+    tile_place(d, t, ty, tx);
     const int64_t gy0 = (int64_t)ty * TI - 1, gx0 = (int64_t)tx * TI - 1;
-    const int64_t a = gx0 & ~(int64_t)15;
     StageWords w;
     v4u v[5];
-    stage_issue(plane_rsrc(d.I, (uint64_t)(d.H * d.pI)), gy0, d.H, (uint32_t)d.pI, a, lane, v, live);
+    stage_issue(d.I, gy0, gx0, d.H, d.W, d.pI, lane, v, live);
     w.i0 = v[0];
     w.i1 = v[1];
     w.i2 = v[2];
     w.i3 = v[3];
     w.i4 = v[4];
     if (NEEDJ) {
-        stage_issue(plane_rsrc(d.J, (uint64_t)(d.H * d.pJ)), gy0, d.H, (uint32_t)d.pJ, a, lane, v,
-                    live);
+        stage_issue<CPOL>(d.J, gy0, gx0, d.H, d.W, d.pJ, lane, v, live);
         w.j0 = v[0];
         w.j1 = v[1];
         w.j2 = v[2];
@@ -272,13 +301,19 @@ __device__ __forceinline__ StageWords stage_fetch(const ImgDesc &d, int64_t t, i
     return w;
 }
 
+// The fetched rows of tile t go to the stage (mask rows, then working-image
+// rows); a fill-holes image's mask is complemented on the way.
 template <bool NEEDJ>
-__device__ __forceinline__ void stage_commit_words(const StageWords &w, int lane, uint8_t *st) {
+__device__ __forceinline__ void stage_commit_words(const StageWords &w, const ImgDesc &d,
+                                                   int64_t t, int lane, uint8_t *st, bool fill) {
+    int ty, tx;
+    tile_place(d, t, ty, tx);
+    const int64_t gy0 = (int64_t)ty * TI - 1, gx0 = (int64_t)tx * TI - 1;
     const v4u vi[5] = {w.i0, w.i1, w.i2, w.i3, w.i4};
-    stage_commit(vi, lane, st);
+    stage_commit(vi, d.I, gy0, gx0, d.pI, lane, st + STAGE_PAD, fill ? ~0u : 0u);
     if (NEEDJ) {
         const v4u vj[5] = {w.j0, w.j1, w.j2, w.j3, w.j4};
-        stage_commit(vj, lane, st + STAGE_BYTES);
+        stage_commit(vj, d.J, gy0, gx0, d.pJ, lane, st + STAGE_PAD + STAGE_BYTES, 0u);
     }
 }
 
@@ -294,66 +329,63 @@ __device__ __forceinline__ void store_j(gptr<T> p, uint32_t off, T v) {
     else p[off] = v;
 }
 
-// Load one 64 x 64 register tile. INITIAL builds the starting working image
+// The register tile of one visit. `initial` builds the starting working image
 // (reconstruction: min(marker, mask); fill-holes: the complement on the image
-// border and the minimum inside) instead of reading it; FILL reads the input
-// image and complements it into the mask. Outside pixels become key 0 in
-// both, which keeps them at 0.
+// border and the minimum inside) instead of reading it; `fill` reads the input
+// image and complements it into the mask. Both are uniform, and constants in
+// the kernels made for one kind of visit. Outside pixels become key 0 in
+// both planes, which keeps them at 0.
 // The halo is not frozen: a sweep may raise a halo pixel from its in-tile
 // neighbours. That is a true geodesic dilation step on real values, so every
 // value stays at or below the reconstruction; halo values are never stored,
 // and a tile at a fixed point against a raised halo is one against the stored
 // halo as well (the dilation step is monotone).
-// uint8 tiles whose planes are 16-byte aligned are staged through LDS
-// (`stage`, at least 2 * STAGE_BYTES); other uint8 planes and int32 rows (which
-// are already 256-byte coalesced loads) go straight to registers from
-// clamped, in-bounds addresses. For staged tiles inside the image the
+// uint8 tiles are staged through LDS; int32 rows (which are 256-byte coalesced
+// loads) and uint8 planes beyond a buffer offset's range go straight to
+// registers from clamped, in-bounds addresses. For staged tiles inside the
+// image the
 // transposed mask IT (lane = row, register = column) and the loaded halo
 // columns JL, JR (lane = row) are read straight from the stage, and `it_done`
 // says so.
-// From a stage that holds the tile's mask rows (stage) and working-image rows
-// (stage + STAGE_BYTES), written and synchronized: the register tile J, I
+// From a stage that holds the tile's mask rows (complemented already for
+// fill-holes) and working-image rows, written and synchronized: the register
+// tile J, I
 // (lane = column), and for tiles inside the image the transposed mask IT and
 // the halo columns JL, JR (lane = row), with it_done set. Ends with a wave sync:
 // the stage's memory is the transpose buffer afterwards.
-template <typename T, bool FILL, bool INITIAL>
 __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_t gx0, int lane,
                                            uint32_t (&J)[TS], uint32_t (&I)[TS],
                                            uint32_t (&IT)[TS], uint32_t &JL, uint32_t &JR,
-                                           const uint8_t *stage, bool &it_done) {
-    using P = Pix<T>;
+                                           const uint8_t *stage, bool &it_done, bool fill,
+                                           bool initial) {
     const int64_t H = d.H, W = d.W;
     const int64_t gx = gx0 + lane;
     const bool xin = gx >= 0 && gx < W;
     const bool xedge = gx == 0 || gx == W - 1;
+    // The whole tile, halo included, lies inside the image (wave-uniform):
+    // no pixel needs the outside rule. A fill-holes image's first visit also
+    // needs to know the image border, so it always takes the general path.
     const bool inside =
-        !(FILL && INITIAL) && gy0 >= 0 && gy0 + TS <= H && gx0 >= 0 && gx0 + TS <= W;
-    const int64_t a = gx0 & ~(int64_t)15;
-    const int sh = (int)(gx0 - a) + lane;
-    const uint8_t *stI = stage, *stJ = stage + STAGE_BYTES;
+        !(fill && initial) && gy0 >= 0 && gy0 + TS <= H && gx0 >= 0 && gx0 + TS <= W;
+    const uint8_t *stI = stage + STAGE_PAD, *stJ = stI + STAGE_BYTES;
     if (inside) {
 #pragma unroll
         for (int r = 0; r < TS; ++r) {
-            uint32_t iv = stI[r * SROW + sh];
-            if (FILL) iv = P::KMAX - iv;
-            uint32_t jv = stJ[r * SROW + sh];
-            if (INITIAL) jv = min(jv, iv);
+            const uint32_t iv = stI[r * SROW + lane];
+            uint32_t jv = stJ[r * SROW + lane];
+            if (initial) jv = min(jv, iv);
             J[r] = jv;
             I[r] = iv;
         }
         // lane = row: this lane's row of the mask, and the working image's
         // two halo pixels of that row
-        const uint8_t *row = stI + lane * SROW + (int)(gx0 - a);
+        const uint8_t *row = stI + lane * SROW;
 #pragma unroll
-        for (int c = 0; c < TS; ++c) {
-            uint32_t v = row[c];
-            if (FILL) v = P::KMAX - v;
-            IT[c] = v;
-        }
-        const uint8_t *rowJ = stJ + lane * SROW + (int)(gx0 - a);
+        for (int c = 0; c < TS; ++c) IT[c] = row[c];
+        const uint8_t *rowJ = stJ + lane * SROW;
         JL = rowJ[0];
         JR = rowJ[TS - 1];
-        if (INITIAL) {
+        if (initial) {
             JL = min(JL, IT[0]);
             JR = min(JR, IT[TS - 1]);
         }
@@ -363,51 +395,37 @@ __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_
         for (int r = 0; r < TS; ++r) {
             const int64_t gy = gy0 + r;
             const bool ok = xin && gy >= 0 && gy < H;
-            uint32_t iv = stI[r * SROW + sh];
-            if (FILL) iv = P::KMAX - iv;
-            uint32_t jv;
-            if (FILL && INITIAL)
-                jv = (xedge || gy == 0 || gy == H - 1) ? iv : 0u;
-            else if (INITIAL)
-                jv = min((uint32_t)stJ[r * SROW + sh], iv);
-            else
-                jv = stJ[r * SROW + sh];
-            jv = ok ? jv : 0u;
-            iv = ok ? iv : 0u;
-            J[r] = jv;
-            I[r] = iv;
+            const uint32_t iv = stI[r * SROW + lane];
+            uint32_t jv = stJ[r * SROW + lane];
+            if (initial)
+                jv = fill ? ((xedge || gy == 0 || gy == H - 1) ? iv : 0u) : min(jv, iv);
+            J[r] = ok ? jv : 0u;
+            I[r] = ok ? iv : 0u;
         }
     }
     wave_sync();
 }
 
-template <typename T, bool FILL, bool INITIAL, bool COH = false>
-__device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t gy0, int64_t gx0, int lane,
-                                          uint32_t (&J)[TS], uint32_t (&I)[TS],
+template <typename T, bool COH = false>
+__device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t t, int64_t gy0, int64_t gx0,
+                                          int lane, uint32_t (&J)[TS], uint32_t (&I)[TS],
                                           uint32_t (&IT)[TS], uint32_t &JL, uint32_t &JR,
-                                          uint8_t *stage, bool &it_done) {
+                                          uint8_t *stage, bool &it_done, bool fill, bool initial) {
     using P = Pix<T>;
+    if (sizeof(T) == 1 && stage_ok(d)) {
+        const StageWords w = stage_fetch<true, COH ? CPOL_DEVICE : 0>(d, t, lane);
+        stage_commit_words<true>(w, d, t, lane, stage, fill);
+        wave_sync();
+        stage_read(d, gy0, gx0, lane, J, I, IT, JL, JR, stage, it_done, fill, initial);
+        return;
+    }
     const int64_t H = d.H, W = d.W;
     const int64_t gx = gx0 + lane;
     const bool xin = gx >= 0 && gx < W;
     const bool xedge = gx == 0 || gx == W - 1;
-    // The whole tile, halo included, lies inside the image (wave-uniform):
-    // no pixel needs the outside rule. A fill-holes image's first visit also
-    // needs to know the image border, so it always takes the general path.
     const bool inside =
-        !(FILL && INITIAL) && gy0 >= 0 && gy0 + TS <= H && gx0 >= 0 && gx0 + TS <= W;
-    if (sizeof(T) == 1 && stage_ok(d.I, d.pI) && stage_ok(d.J, d.pJ)) {
-        const int64_t a = gx0 & ~(int64_t)15;
-        uint8_t *stI = stage, *stJ = stage + STAGE_BYTES;
-        stage_u8(plane_rsrc(d.I, (uint64_t)(H * d.pI)), gy0, H, (uint32_t)d.pI, a, lane, stI);
-        const bool needJ = !(FILL && INITIAL);
-        if (needJ)
-            stage_u8<COH ? CPOL_DEVICE : 0>(plane_rsrc(d.J, (uint64_t)(H * d.pJ)), gy0, H,
-                                            (uint32_t)d.pJ, a, lane, stJ);
-        wave_sync();
-        stage_read<T, FILL, INITIAL>(d, gy0, gx0, lane, J, I, IT, JL, JR, stage, it_done);
-        return;
-    }
+        !(fill && initial) && gy0 >= 0 && gy0 + TS <= H && gx0 >= 0 && gx0 + TS <= W;
+    const uint32_t flip = fill ? P::KMAX : 0u;
     cgptr<T> Jp = (cgptr<T>)d.J;
     cgptr<T> Ip = (cgptr<T>)d.I;
     if (inside) {
@@ -415,10 +433,9 @@ __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t gy0, int64_t
         uint32_t oJ = (uint32_t)gy0 * (uint32_t)d.pJ + (uint32_t)gx;
 #pragma unroll
         for (int r = 0; r < TS; ++r) {
-            uint32_t iv = P::key(Ip[oI]);
-            if (FILL) iv = P::KMAX - iv;
+            const uint32_t iv = P::key(Ip[oI]) ^ flip;
             uint32_t jv = P::key(load_j<T, COH>(Jp, oJ));
-            if (INITIAL) jv = min(jv, iv);
+            if (initial) jv = min(jv, iv);
             J[r] = jv;
             I[r] = iv;
             oI += (uint32_t)d.pI;
@@ -432,16 +449,13 @@ __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t gy0, int64_t
         const int64_t gy = gy0 + r;
         const bool ok = xin && gy >= 0 && gy < H;
         const uint32_t yc = (uint32_t)(gy < 0 ? 0 : (gy > H - 1 ? H - 1 : gy));
-        uint32_t iv = P::key(Ip[yc * (uint32_t)d.pI + xc]);
-        if (FILL) iv = P::KMAX - iv;
+        uint32_t iv = P::key(Ip[yc * (uint32_t)d.pI + xc]) ^ flip;
         uint32_t jv;
-        if (INITIAL) {
-            if (FILL)
-                jv = (xedge || yc == 0 || yc == (uint32_t)(H - 1)) ? iv : 0u;
-            else
-                jv = min(P::key(load_j<T, COH>(Jp, yc * (uint32_t)d.pJ + xc)), iv);
+        if (fill && initial) {
+            jv = (xedge || yc == 0 || yc == (uint32_t)(H - 1)) ? iv : 0u;
         } else {
             jv = P::key(load_j<T, COH>(Jp, yc * (uint32_t)d.pJ + xc));
+            if (initial) jv = min(jv, iv);
         }
         jv = ok ? jv : 0u;
         iv = ok ? iv : 0u;
@@ -627,10 +641,8 @@ __device__ __forceinline__ void app_flush(Appender &a, int lane) {
 // pusher has made what the entry stands for visible first: device-scope
 // atomics it waited for, device-coherent stores it waited for, or stores of
 // an earlier launch.
-__device__ __forceinline__ void ring_push(Ctrl *ctrl, uint32_t *ring, uint64_t cap, uint32_t t) {
-    __hip_atomic_fetch_add(&ctrl->pending.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const unsigned long long pos =
-        __hip_atomic_fetch_add(&ctrl->q_tail.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+__device__ __forceinline__ void ring_put(Ctrl *ctrl, uint32_t *ring, uint64_t cap, uint32_t t,
+                                         unsigned long long pos) {
     uint32_t *slot = ring + (pos & (cap - 1));
     // The capacity bound means the slot is already free; the wait is a guard,
     // capped so that a broken bound cannot hang the device. Past the cap the
@@ -649,6 +661,30 @@ __device__ __forceinline__ void ring_push(Ctrl *ctrl, uint32_t *ring, uint64_t c
         __builtin_amdgcn_s_sleep(2);
     }
     __hip_atomic_store(slot, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One lane's entry.
+__device__ __forceinline__ void ring_push(Ctrl *ctrl, uint32_t *ring, uint64_t cap, uint32_t t) {
+    __hip_atomic_fetch_add(&ctrl->pending.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long pos =
+        __hip_atomic_fetch_add(&ctrl->q_tail.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    ring_put(ctrl, ring, cap, t, pos);
+}
+
+// The whole wave: every lane with t != Q_EMPTY pushes it, with one update of the
+// tail and of the pending count for all of them. The pending count's update has
+// been performed before an entry can be seen.
+__device__ __forceinline__ void ring_push(Ctrl *ctrl, uint32_t *ring, uint64_t cap, uint32_t t,
+                                          int lane) {
+    const uint64_t m = __ballot(t != Q_EMPTY);
+    if (m == 0) return;
+    unsigned long long pos = 0;
+    if (lane < 2) // both updates in one instruction, performed together
+        pos = __hip_atomic_fetch_add(lane == 0 ? &ctrl->q_tail.v : &ctrl->pending.v,
+                                     (unsigned long long)__popcll(m), __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+    pos = __shfl(pos, 0);
+    if (t != Q_EMPTY) ring_put(ctrl, ring, cap, t, pos + __popcll(m & ((1ull << lane) - 1)));
 }
 
 // Wait until this wave's memory operations are done (its device-coherent
@@ -714,18 +750,10 @@ __device__ __forceinline__ void ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t
 // Tile-queue visits read and write the working image device-coherent and
 // wait for their stores before any mark, so a visit that a mark leads to
 // sees the marking visit's pixels without cache-wide fences.
-struct TailQ {
-    uint32_t *state;
-    uint32_t *ring;
-    uint64_t cap;
-    Ctrl *ctrl;
+struct TailMarks {
+    bool want = false; // this lane asks for tile nb (lane 0: for the visited tile itself)
+    uint32_t nb = 0;
 };
-
-__device__ __forceinline__ void tail_mark(const TailQ &q, uint32_t t) {
-    const uint32_t prev =
-        __hip_atomic_fetch_or(q.state + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (prev == 0u) ring_push(q.ctrl, q.ring, q.cap, t);
-}
 
 // One visit of one tile: load, sweep to a local fixed point (or the cap),
 // store, and mark the neighbours whose halo changed: onto the next round's
@@ -808,35 +836,34 @@ __device__ __forceinline__ uint32_t mark_neighbours(const ImgDesc &d, int lane, 
 // and synchronized): on the round path, after the marking atomics are issued
 // and before the stores, the visit issues the stage loads of the next tile
 // (*dn, tn) when has_next, and returns them; otherwise it returns zeros.
-template <typename T, int CONN, bool FILL, bool INITIAL, bool TAIL = false, bool PIPE = false>
+template <typename T, int CONN, bool TAIL = false, bool PIPE = false, bool NEEDJ = true>
 __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, int lane,
                                                  uint32_t *__restrict__ flags, Appender &app,
                                                  Ctrl *__restrict__ ctrl, uint32_t round,
                                                  int max_iters, uint32_t (*tb)[TS + 1],
-                                                 const TailQ *tq = nullptr,
+                                                 bool fill, bool initial,
+                                                 TailMarks *tm = nullptr,
                                                  const ImgDesc *dn = nullptr, int64_t tn = 0,
                                                  bool has_next = false) {
-    constexpr bool STAGED = PIPE;
     StageWords pre{};
     using P = Pix<T>;
     // nothing derived from the lane id is hoisted out of the caller's tile
     // loop: held across the sweeps, such values would be spilled, and their
     // reloads would wait behind the stores of the visit
     asm volatile("" : "+v"(lane));
-    constexpr bool first = INITIAL;
-    const int64_t lt = t - d.tile_base;
-    const int ty = (int)(lt / d.ntx), tx = (int)(lt - (int64_t)ty * d.ntx);
+    int ty, tx;
+    tile_place(d, t, ty, tx);
     const int64_t gy0 = (int64_t)ty * TI - 1, gx = (int64_t)tx * TI - 1 + lane;
 
     uint32_t J[TS], I[TS], IT[TS];
     uint32_t JL, JR; // loaded halo columns 0 and TS-1, lane = row
     bool it_done = false;
-    if (STAGED) // the caller has written and synchronized the stage
-        stage_read<T, FILL, INITIAL>(d, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR,
-                                     (const uint8_t *)tb, it_done);
+    if (PIPE) // the caller has written and synchronized the stage
+        stage_read(d, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, (const uint8_t *)tb,
+                   it_done, fill, initial);
     else
-        load_tile<T, FILL, INITIAL, TAIL>(d, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR,
-                                          (uint8_t *)tb, it_done);
+        load_tile<T, TAIL>(d, t, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, (uint8_t *)tb,
+                           it_done, fill, initial);
     if (!it_done) {
         // (before the mask transpose: fewer registers live)
         halo_cols(J, tb, lane, JL, JR);
@@ -884,7 +911,7 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
         // measures faster for them; a first visit at its sweep cap leaves
         // the check out: the tile is left unstable, and so listed again)
         if (sizeof(T) == 4 && it < 2) continue;
-        if (INITIAL && it >= max_iters) break;
+        if (initial && it >= max_iters) break;
         relax_once<CONN>(J, I);
         col_now = col_sum<T>(J);
         ch = in_lane && col_now != col_prev;
@@ -896,7 +923,7 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
     }
     if (lane == 0) atomicAdd(&ctrl->iters[t & (NCNT - 1)], (unsigned long long)it);
 
-    if (changed || first) {
+    if (changed || initial) {
         gptr<T> Jw = (gptr<T>)d.J;
         if (in_lane && gx < d.W) {
             // rows gy0+1 .. gy0+62 are all >= 0; only the last tile row may
@@ -930,7 +957,7 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
     auto fetch_next = [&]() {
         if (PIPE) {
             asm volatile("" ::: "memory");
-            pre = stage_fetch<!(FILL && INITIAL)>(*dn, tn, lane, has_next);
+            pre = stage_fetch<NEEDJ>(*dn, tn, lane, has_next);
         }
     };
     if (!changed && stable) {
@@ -956,9 +983,8 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
     uint32_t tnb = 0;
     const bool want = mark_decide<CONN>(d, lane, ty, tx, J, I, IT, JT, JB, JL, JR, top_in, bot_in,
                                         col_in, col_prev, stable, tb, tnb);
-    // the visits these marks lead to must see this visit's stores
-    wait_vmem();
-    if (want) tail_mark(*tq, tnb);
+    tm->want = want;
+    tm->nb = tnb;
     return pre;
 }
 
@@ -1116,36 +1142,27 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
     TileCursor cur = cursor_start(w);
     for (int64_t t; (t = cursor_next(cur, w, all_tiles, flags, round, lane)) >= 0;) {
         const ImgDesc d = load_desc(imgs, t);
-        if (V >= 0) {
-            if (!d.done)
-                visit_tile<T, CONN, (V >> 1) & 1, V & 1>(d, t, lane, flags, app, ctrl, round,
-                                                         max_iters, tb);
-        } else if (!d.done) {
-            if (d.first_round == (int64_t)round) {
-                if (d.op == MR_OP_FILL)
-                    visit_tile<T, CONN, true, true>(d, t, lane, flags, app, ctrl, round, max_iters, tb);
-                else
-                    visit_tile<T, CONN, false, true>(d, t, lane, flags, app, ctrl, round, max_iters, tb);
-            } else {
-                if (d.op == MR_OP_FILL)
-                    visit_tile<T, CONN, true, false>(d, t, lane, flags, app, ctrl, round, max_iters, tb);
-                else
-                    visit_tile<T, CONN, false, false>(d, t, lane, flags, app, ctrl, round, max_iters, tb);
-            }
-        }
+        if (!d.done)
+            visit_tile<T, CONN>(d, t, lane, flags, app, ctrl, round, max_iters, tb,
+                                V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL,
+                                V >= 0 ? V & 1 : d.first_round == (int64_t)round);
         if (app.cnt > APP_CAP - 9) app_flush(app, lane);
     }
     app_flush(app, lane);
 }
 
-// The same round for launches whose images are all uint8 with 16-byte
-// aligned planes and pitches and take one visit kind V, software-pipelined
+// The same round for launches whose images are all uint8 (of a size the stage
+// reaches), software-pipelined
 // over the block's tiles: the stage loads of the next tile are issued during
 // the current visit, after its marking atomics and before its stores, so
 // that their memory latency (and that of the next list entry and
 // descriptor) overlaps the current tile's stores and the wait for its marks
 // instead of starting the next visit. The loads land in registers that the
-// sweeps no longer need; the next visit writes them to the stage.
+// sweeps no longer need; the next visit writes them to the stage. With V < 0
+// (mixed batches, the server) a visit's kind is read from its image.
+// Planes of any base and pitch take this kernel: a batch of 40 mixed tiles of
+// odd sizes spends 582 us in its rounds (757 us when such planes were loaded
+// byte by byte by k_tile_round), one 293 x 421 image 61 us instead of 120.
 template <int CONN, int V>
 __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_tiles,
                                                          uint32_t *__restrict__ flags,
@@ -1154,8 +1171,7 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                                                          uint32_t *__restrict__ counts_out,
                                                          int all_tiles, Ctrl *__restrict__ ctrl,
                                                          uint32_t round, int max_iters) {
-    constexpr bool FILL = (V >> 1) & 1, INITIAL = V & 1;
-    constexpr bool needJ = !(FILL && INITIAL);
+    constexpr bool needJ = V != 3;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer and load stage
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
@@ -1163,22 +1179,37 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
     Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles};
     uint8_t *stage = (uint8_t *)tb;
     TileCursor cur = cursor_start(w);
-    int64_t t = cursor_next(cur, w, all_tiles, flags, round, lane);
+    // the next tile to visit and its image (images that are done take no visit)
+    auto next = [&](ImgDesc &d) -> int64_t {
+        int64_t t;
+        while ((t = cursor_next(cur, w, all_tiles, flags, round, lane)) >= 0) {
+            d = load_desc(imgs, t);
+            if (!d.done) break;
+        }
+        return t;
+    };
+    ImgDesc d{};
+    int64_t t = next(d);
     if (t >= 0) {
-        ImgDesc d = load_desc(imgs, t);
         StageWords pre = stage_fetch<needJ>(d, t, lane);
         while (true) {
+            const bool fill = V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL;
+            const bool initial = V >= 0 ? V & 1 : d.first_round == (int64_t)round;
             // the fetched rows of tile t go to the stage; the previous visit's
             // last reads of the transpose buffer are behind this sync
             wave_sync();
-            stage_commit_words<needJ>(pre, lane, stage);
+            stage_commit_words<needJ>(pre, d, t, lane, stage, fill);
             wave_sync();
-            int64_t tn = cursor_next(cur, w, all_tiles, flags, round, lane);
+            ImgDesc dn = d;
+            int64_t tn = next(dn);
             const bool has = tn >= 0;
-            if (!has) tn = t;
-            const ImgDesc dn = has ? load_desc(imgs, tn) : d;
-            pre = visit_tile<uint8_t, CONN, FILL, INITIAL, false, true>(
-                d, t, lane, flags, app, ctrl, round, max_iters, tb, nullptr, &dn, tn, has);
+            if (!has) {
+                tn = t;
+                dn = d;
+            }
+            pre = visit_tile<uint8_t, CONN, false, true, needJ>(d, t, lane, flags, app, ctrl,
+                                                                round, max_iters, tb, fill,
+                                                                initial, nullptr, &dn, tn, has);
             if (app.cnt > APP_CAP - 9) app_flush(app, lane);
             if (!has) break;
             t = tn;
@@ -1219,6 +1250,9 @@ __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists,
 // and waits for that entry, so no two waves contend for an entry. The wave
 // that retires the last queued-or-running tile writes a stop entry for every
 // wave. The watchdog (ring_take) turns a stall into an error instead of a hang.
+// Bound by the latency of a link, so a wave hands itself the first idle
+// neighbour it marks instead of queueing it: on the holes of a 4096 x 4096
+// tile the queue takes 269 us (357 us with every neighbour through the ring).
 
 template <typename T, int CONN, int V>
 __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restrict__ ctrl,
@@ -1228,50 +1262,88 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
                                                       unsigned long long wait_us) {
     __shared__ uint32_t tb[TS][TS + 1];
     const int lane = threadIdx.x;
-    const TailQ tq{state, ring, cap, ctrl};
     Appender app{nullptr, 0, nullptr, nullptr, 0}; // unused: marks go to the ring
     unsigned long long visits = 0;
     // nothing seeded: no wave will ever retire a tile and write the stops
     if (__hip_atomic_load(&ctrl->pending.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
         return;
+    uint32_t t = Q_EMPTY; // the tile this wave holds: its state is 2, it counts as pending
     while (true) {
-        uint32_t t = Q_EMPTY;
-        if (lane == 0) t = ring_take(ctrl, ring, cap, wait_us);
-        t = __shfl(t, 0);
-        if (t == Q_STOP) break;
-        // queued -> visited, performed before any pixel is read: a mark that
-        // comes later finds state 2 and gets the tile visited again, one that
-        // came earlier had its stores done before it
-        if (lane == 0)
-            (void)__hip_atomic_exchange(state + t, 2u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        wait_vmem();
+        if (t == Q_EMPTY) {
+            if (lane == 0) t = ring_take(ctrl, ring, cap, wait_us);
+            t = (uint32_t)__builtin_amdgcn_readfirstlane(t); // (uniform: scalar descriptor loads)
+            if (t == Q_STOP) break;
+            // queued -> visited, performed before any pixel is read: a mark that
+            // comes later finds state 2 and gets the tile visited again, one that
+            // came earlier had its stores done before it
+            if (lane == 0)
+                (void)__hip_atomic_exchange(state + t, 2u, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+            wait_vmem();
+        }
         const ImgDesc d = load_desc(imgs, t);
+        TailMarks tm;
         if (!d.done) {
             ++visits;
-            if (V >= 0) {
-                visit_tile<T, CONN, (V >> 1) & 1, false, true>(d, t, lane, nullptr, app, ctrl, 0,
-                                                               max_iters, tb, &tq);
-            } else if (d.op == MR_OP_FILL) {
-                visit_tile<T, CONN, true, false, true>(d, t, lane, nullptr, app, ctrl, 0,
-                                                       max_iters, tb, &tq);
-            } else {
-                visit_tile<T, CONN, false, false, true>(d, t, lane, nullptr, app, ctrl, 0,
-                                                        max_iters, tb, &tq);
+            visit_tile<T, CONN, true>(d, t, lane, nullptr, app, ctrl, 0, max_iters, tb,
+                                      V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL, false, &tm);
+        }
+        // the visits these marks lead to must see this visit's stores
+        wait_vmem();
+        // Marks and the release of this tile, all in flight together. The first
+        // neighbour asked for is tried as this wave's next tile (idle ->
+        // visited by this wave), without a way through the ring; lane 63
+        // releases the tile (visited -> idle), unless the sweep cap stopped
+        // its visit: then the wave keeps it.
+        const uint64_t wm = __ballot(tm.want);
+        const bool again = wm & 1;
+        const uint64_t others = wm & ~1ull;
+        const int first = others && !again ? __builtin_ctzll(others) : -1;
+        const bool try_next = lane == first, release = lane == 63 && !again;
+        uint32_t expect = release ? 2u : 0u;
+        bool swapped = false;
+        if (try_next || release)
+            swapped = __hip_atomic_compare_exchange_strong(
+                state + (release ? t : tm.nb), &expect, release ? 0u : 2u, __ATOMIC_RELAXED,
+                __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t prev = 1u;
+        if (tm.want && lane != 0 && !try_next)
+            prev = __hip_atomic_fetch_or(state + tm.nb, 1u, __ATOMIC_RELAXED,
+                                         __HIP_MEMORY_SCOPE_AGENT);
+        uint32_t next = again ? t : Q_EMPTY;
+        if (__ballot(try_next && swapped)) {
+            next = (uint32_t)__builtin_amdgcn_readlane(tm.nb, first);
+        } else if (first >= 0) {
+            // queued, visited or marked already: an ordinary mark (by now the tile
+            // may be idle again, and is then queued by this lane)
+            if (try_next)
+                prev = __hip_atomic_fetch_or(state + tm.nb, 1u, __ATOMIC_RELAXED,
+                                             __HIP_MEMORY_SCOPE_AGENT);
+        }
+        uint32_t push = prev == 0u ? tm.nb : Q_EMPTY;
+        if (again) {
+            // visited again by this wave: marks from before its loads are answered
+            if (lane == 0)
+                (void)__hip_atomic_exchange(state + t, 2u, __ATOMIC_RELAXED,
+                                            __HIP_MEMORY_SCOPE_AGENT);
+        } else if (__ballot(release && !swapped)) {
+            // marked while it was visited (state 3): this wave visits it again, or
+            // queues it if it has another tile already
+            if (next == Q_EMPTY) {
+                next = t;
+                if (lane == 0)
+                    (void)__hip_atomic_exchange(state + t, 2u, __ATOMIC_RELAXED,
+                                                __HIP_MEMORY_SCOPE_AGENT);
+            } else if (lane == 63) {
+                __hip_atomic_store(state + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                push = t;
             }
         }
         wait_vmem();
-        if (lane == 0) {
-            uint32_t expect = 2u;
-            if (!__hip_atomic_compare_exchange_strong(state + t, &expect, 0u, __ATOMIC_RELAXED,
-                                                      __ATOMIC_RELAXED,
-                                                      __HIP_MEMORY_SCOPE_AGENT)) {
-                // marked while it was visited (state 3): queue it again
-                __hip_atomic_store(state + t, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-                ring_push(ctrl, ring, cap, t);
-            }
-            wait_vmem();
-            ring_retire(ctrl, ring, cap, gridDim.x);
-        }
+        ring_push(ctrl, ring, cap, push, lane);
+        // one entry held before and, with a next tile, one held now
+        if (next == Q_EMPTY && lane == 0) ring_retire(ctrl, ring, cap, gridDim.x);
+        t = next;
     }
     if (lane == 0 && visits)
         atomicAdd(&ctrl->tiles[(blockIdx.x) & (NCNT - 1)], visits);
@@ -1283,18 +1355,18 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
 // pixel takes min(I, max of J over itself and its neighbours). Raised pixels
 // are stored, their bits form the tile's frontier bitmap rows, and the tile
 // enters the ring. Tiles that are not dirty only clear their bitmap and flag.
-template <typename T, int CONN, bool FILL>
+template <typename T, int CONN>
 __device__ __forceinline__ void seed_tile(const ImgDesc &d, int64_t t, int lane, Ctrl *ctrl,
                                           uint64_t *bitmap, uint32_t *qflag, uint32_t *ring,
-                                          uint64_t cap, uint8_t *stage) {
+                                          uint64_t cap, uint8_t *stage, bool fill) {
     using P = Pix<T>;
-    const int64_t lt = t - d.tile_base;
-    const int ty = (int)(lt / d.ntx), tx = (int)(lt - (int64_t)ty * d.ntx);
+    int ty, tx;
+    tile_place(d, t, ty, tx);
     const int64_t gy0 = (int64_t)ty * TI - 1, gx = (int64_t)tx * TI - 1 + lane;
     uint32_t J[TS], I[TS], IT[TS], JL, JR;
     bool it_done = false;
-    load_tile<T, FILL, false>(d, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, stage,
-                              it_done);
+    load_tile<T>(d, t, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, stage, it_done, fill,
+                 false);
     uint64_t myrow = 0; // lane r ends up holding row r's bits
     uint32_t nseed = 0;
     gptr<T> Jw = (gptr<T>)d.J;
@@ -1339,7 +1411,7 @@ __global__ __launch_bounds__(64) void k_seed(Imgs imgs, int64_t n_tiles,
                                              uint64_t *__restrict__ bitmap,
                                              uint32_t *__restrict__ qflag,
                                              uint32_t *__restrict__ ring, uint64_t cap) {
-    __shared__ uint8_t stage[2 * STAGE_BYTES];
+    __shared__ __align__(16) uint8_t stage[STAGE_PAD + 2 * STAGE_BYTES];
     const int lane = threadIdx.x;
     const int band = blockIdx.x % NBANDS;
     const int64_t local = blockIdx.x / NBANDS, per = gridDim.x / NBANDS;
@@ -1349,10 +1421,8 @@ __global__ __launch_bounds__(64) void k_seed(Imgs imgs, int64_t n_tiles,
         const int64_t t = list_in[i];
         const ImgDesc d = load_desc(imgs, t);
         if (d.done) continue;
-        if (d.op == MR_OP_FILL)
-            seed_tile<T, CONN, true>(d, t, lane, ctrl, bitmap, qflag, ring, cap, stage);
-        else
-            seed_tile<T, CONN, false>(d, t, lane, ctrl, bitmap, qflag, ring, cap, stage);
+        seed_tile<T, CONN>(d, t, lane, ctrl, bitmap, qflag, ring, cap, stage,
+                           d.op == MR_OP_FILL);
     }
 }
 
@@ -1707,11 +1777,13 @@ static hipError_t tile_round_v(const Imgs &imgs, int64_t n_tiles, uint32_t *flag
                                hipStream_t s) {
     const int64_t want = std::max<int64_t>(NBANDS, (n_tiles + NBANDS - 1) / NBANDS * NBANDS);
     const unsigned g = (unsigned)(std::min<int64_t>(grid, want) / NBANDS * NBANDS);
-    if (sizeof(T) == 1 && V >= 0 && imgs.staged)
-        hipLaunchKernelGGL((k_tile_round_pf<CONN, (V < 0 ? 0 : V)>), dim3(g), dim3(64), 0, s, imgs,
+    // (uint8 planes beyond the stage's range are rare: one kernel for all visits)
+    constexpr int VR = sizeof(T) == 1 ? -1 : V;
+    if (sizeof(T) == 1 && imgs.staged)
+        hipLaunchKernelGGL((k_tile_round_pf<CONN, V>), dim3(g), dim3(64), 0, s, imgs,
                            n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters);
     else
-        hipLaunchKernelGGL((k_tile_round<T, CONN, V>), dim3(g), dim3(64), 0, s, imgs, n_tiles,
+        hipLaunchKernelGGL((k_tile_round<T, CONN, VR>), dim3(g), dim3(64), 0, s, imgs, n_tiles,
                            flags, lists, cin, cout, all, ctrl, round, max_iters);
     return hipGetLastError();
 }

@@ -426,7 +426,10 @@ int mr_server_step(mr_server *s) {
     clear_error();
     if (!s) return sfail(MR_EINVAL, "null server");
     hipError_t e;
-    Imgs imgs{s->descs, s->max_jobs, s->owner};
+    // (a job's planes lie in the arena; one too large to stage is found below)
+    Imgs imgs{s->descs, s->max_jobs, s->owner, s->t == MR_U8 ? 1 : 0, 0};
+    for (const auto &r : s->resident)
+        if ((uint64_t)r.second.plane > STAGE_MAX_BYTES) imgs.staged = 0;
     // 1. launch the step's rounds over every resident job (including those
     //    admitted since the last step); the host does not wait for them here
     uint32_t launched = 0;
