@@ -308,9 +308,23 @@ uint64_t round_total(const Ctrl &h, size_t r) {
     return n;
 }
 
-// The whole propagation over the images of one launch.
+// Tiles that a round before the tile queue leaves to it: a round that lists no
+// more than this visits nothing, nor do the rounds after it. A link of the queue
+// takes 6 us where a round takes 13 at least, and its visits see their
+// neighbours' newest pixels; its loads of the working image bypass the caches,
+// though, which costs uint8 visits (issue bound, rows shared through L2) more
+// than int32 ones (bound by memory traffic, 256-byte rows). Measured, 8 rounds
+// asked for, left at 0 / half these / these / more (8192 and 262144) tiles:
+// 16384 x 16384 int32 5390 / 5246 / 5084 / 5495 us, uint8 1492 / 1490 / 1490 /
+// 1515 us; 4096 x 4096 int32 h-dome 980 / 779 / 780 / 778 us, uint8 fill-holes
+// 436 / 416 / 416 / 416 us, erosion 719 / 722 / 730 / 715 us.
+uint32_t tail_leave(int tbytes) { return tbytes == 1 ? 4096u : 65536u; }
+
+// The whole propagation over the images of one launch. With `desc`, the one
+// image's descriptor goes there.
 int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *ws,
-                 const mr_tune &tn, hipStream_t s, bool any_fill, int op_all) {
+                 const mr_tune &tn, hipStream_t s, bool any_fill, int op_all,
+                 const ImgDesc *desc = nullptr) {
     char *base = (char *)ws;
     Ctrl *ctrl = (Ctrl *)base;
     uint32_t *flags = (uint32_t *)(base + L.off_flags);
@@ -323,7 +337,8 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
 
     // control block, dirty flags, and the queue flags and ring (untouched by
     // the rounds, so the tile queue can start from them as they are)
-    if ((e = launch_clear_start(ctrl, L.n_tiles, flags, qflag, ring, (int64_t)L.ring_cap, s)) !=
+    if ((e = launch_clear_start(ctrl, L.n_tiles, flags, qflag, ring, (int64_t)L.ring_cap,
+                                desc ? (ImgDesc *)imgs.d : nullptr, desc ? *desc : ImgDesc{}, s)) !=
         hipSuccess)
         return hip_fail(e, "clear");
 
@@ -336,7 +351,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
         // nearly every tile is visited again in the second tile round.
         LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
         e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                              tn.first_sweeps, grid, s, op_all);
+                              tn.first_sweeps, grid, s, op_all, 0);
     }
     if (e != hipSuccess) return hip_fail(e, "tile round");
     span.add();
@@ -377,7 +392,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
             {
                 LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                 e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                                      tn.max_sweeps, grid, s, op_all);
+                                      tn.max_sweeps, grid, s, op_all, 0);
             }
             if (e != hipSuccess) return hip_fail(e, "tile round");
             span.add();
@@ -391,25 +406,24 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
     } else if (tn.tail_rounds > 0) {
         // converge mode with the tile queue: a fixed number of rounds, then
         // the queue takes every tile still listed and runs to the fixed point
+        // (it also writes ctrl->rounds)
+        const uint32_t leave = tail_leave(tbytes);
         for (round = 2; round <= (uint32_t)tn.tail_rounds; ++round) {
             span.begin(round);
             {
                 LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                 e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                                      tn.max_sweeps, grid, s, op_all);
+                                      tn.max_sweeps, grid, s, op_all, leave);
             }
             if (e != hipSuccess) return hip_fail(e, "tile round");
             span.add();
         }
         span.close();
-        if ((e = launch_store_u64(&ctrl->rounds, (unsigned long long)tn.tail_rounds, s)) !=
-            hipSuccess)
-            return hip_fail(e, "store");
         {
             LaunchTimer lt(s, MR_K_TILE_QUEUE, 0);
             e = launch_tile_queue(tbytes, conn, imgs, L.n_tiles, lists, (uint32_t)tn.tail_rounds + 1,
                                   ctrl, qflag, ring, L.ring_cap, tn.max_sweeps, grid,
-                                  QUEUE_WAIT_US, s, op_all);
+                                  QUEUE_WAIT_US, s, op_all, leave);
         }
         if (e != hipSuccess) return hip_fail(e, "tile queue");
     } else {
@@ -433,7 +447,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
                 {
                     LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                     e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl,
-                                          round, tn.max_sweeps, grid, s, op_all);
+                                          round, tn.max_sweeps, grid, s, op_all, 0);
                 }
                 if (e != hipSuccess) return e;
                 span.add();
@@ -524,9 +538,7 @@ int run_single(int op, void *J_io, const void *I, int64_t H, int64_t W, int64_t 
     imgs.d = (const ImgDesc *)((char *)ws + L.off_desc);
     imgs.staged = staged_planes(t, d) ? 1 : 0;
     imgs.wide = wide ? 1 : 0;
-    hipError_t e = launch_put_desc((ImgDesc *)imgs.d, d, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "descriptor");
-    return run_sequence(t, conn, imgs, L, ws, tn, (hipStream_t)stream, op == MR_OP_FILL, op);
+    return run_sequence(t, conn, imgs, L, ws, tn, (hipStream_t)stream, op == MR_OP_FILL, op, &d);
 }
 
 // ---------------------------------------------------------------- batches

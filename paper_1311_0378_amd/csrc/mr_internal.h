@@ -105,18 +105,22 @@ int set_error(int code, const char *msg);
 hipError_t launch_clear_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_clear_ctrl(Ctrl *c, int64_t n_tiles, hipStream_t s);
 // Clears what a launch sequence starts from in one kernel: the control block,
-// flags[n_tiles], qflag[n_tiles] (0) and ring[ring_cap] (Q_EMPTY).
+// flags[n_tiles], qflag[n_tiles] (0) and ring[ring_cap] (Q_EMPTY). Writes the
+// descriptor d to *desc as well, unless desc is null.
 hipError_t launch_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_t *qflag,
-                              uint32_t *ring, int64_t ring_cap, hipStream_t s);
+                              uint32_t *ring, int64_t ring_cap, ImgDesc *desc, const ImgDesc &d,
+                              hipStream_t s);
 // Round r visits every tile (r == 1) or the dirty lists of round r -- band
 // b's at lists[(r & 1) * n_tiles + band start], ctrl->round_tiles[r][b] long
 // -- and lists each tile it dirties for round r + 1 in the other half
 // (flags[t] = the latest round t is listed for). Every image's first round
 // is 1; op_all is the op of all images (MR_OP_RECON / MR_OP_FILL), or -1 if
-// they differ.
+// they differ. A round after the first that lists at most `leave` tiles visits
+// none of them: they are for a tile queue launched with the same `leave`.
 hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              uint32_t *flags, uint32_t *lists, Ctrl *ctrl, uint32_t round,
-                             int max_iters, int grid, hipStream_t s, int op_all);
+                             int max_iters, int grid, hipStream_t s, int op_all,
+                             uint32_t leave);
 // The same round with explicit list-length counters (NBANDS each) for this
 // round and the next; all_tiles visits every tile instead of a list.
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
@@ -130,20 +134,21 @@ hipError_t launch_clear_u64(uint64_t *p, int64_t n, hipStream_t s);
 hipError_t launch_queue(int tbytes, int conn, const Imgs &imgs, Ctrl *ctrl, uint64_t *bitmap,
                         uint32_t *qflag, uint32_t *ring, uint64_t cap, int blocks,
                         unsigned long long wait_us, hipStream_t s);
-// Tile queue: seed it with every tile listed for `round` (state[t] = 1, ring
+// Tile queue: seed it with every tile listed for `round`, or for the earlier
+// round that `leave` left to it (state[t] = 1, ring
 // entries, pending), then visit tiles from it on a persistent grid until none
 // is queued or running. state[] and ring[] start cleared (0, Q_EMPTY).
 hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              const uint32_t *lists, uint32_t round, Ctrl *ctrl, uint32_t *state,
                              uint32_t *ring, uint64_t cap, int max_iters, int grid,
-                             unsigned long long wait_us, hipStream_t s, int op_all);
+                             unsigned long long wait_us, hipStream_t s, int op_all,
+                             uint32_t leave);
 // The queue phase's widened planes: copy every tile interior of J into
 // `wide` (to_wide), or back (from wide to J).
 hipError_t launch_widen(const Imgs &imgs, int64_t n_tiles, bool to_wide, hipStream_t s);
 hipError_t launch_fill_output(int tbytes, const Imgs &imgs, int64_t n_tiles, hipStream_t s,
                               int64_t t0 = 0);
 hipError_t launch_store_u64(unsigned long long *p, unsigned long long v, hipStream_t s);
-hipError_t launch_put_desc(ImgDesc *dst, const ImgDesc &v, hipStream_t s);
 // Writes n descriptors (n <= DESC_CHUNK per launch) through kernel arguments,
 // which keeps uploads stream-ordered and capturable.
 constexpr int DESC_CHUNK = 16;

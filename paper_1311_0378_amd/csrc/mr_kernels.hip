@@ -1021,7 +1021,7 @@ struct RoundWork {
 // loses nothing.
 __device__ __forceinline__ RoundWork round_work(int64_t n_tiles, const uint32_t *lists,
                                                 const uint32_t *counts_in, int all_tiles,
-                                                uint32_t round) {
+                                                uint32_t round, uint32_t leave) {
     RoundWork w;
     w.band = blockIdx.x % NBANDS;
     w.local = blockIdx.x / NBANDS;
@@ -1037,7 +1037,9 @@ __device__ __forceinline__ RoundWork round_work(int64_t n_tiles, const uint32_t 
             total += c[q];
             cmax = c[q] > cmax ? c[q] : cmax;
         }
-        if (total <= gridDim.x && cmax > (uint32_t)w.per) {
+        if (total <= leave) { // left to the tile queue (see tail_leave)
+            w.n = 0;
+        } else if (total <= gridDim.x && cmax > (uint32_t)w.per) {
             uint32_t i = blockIdx.x, cb = c[0];
             int b = 0;
 #pragma unroll
@@ -1133,11 +1135,12 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
                                                       const uint32_t *__restrict__ counts_in,
                                                       uint32_t *__restrict__ counts_out,
                                                       int all_tiles, Ctrl *__restrict__ ctrl,
-                                                      uint32_t round, int max_iters) {
+                                                      uint32_t round, int max_iters,
+                                                      uint32_t leave) {
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer (and load stage)
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
-    const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round);
+    const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round, leave);
     Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles};
     TileCursor cur = cursor_start(w);
     for (int64_t t; (t = cursor_next(cur, w, all_tiles, flags, round, lane)) >= 0;) {
@@ -1170,12 +1173,13 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                                                          const uint32_t *__restrict__ counts_in,
                                                          uint32_t *__restrict__ counts_out,
                                                          int all_tiles, Ctrl *__restrict__ ctrl,
-                                                         uint32_t round, int max_iters) {
+                                                         uint32_t round, int max_iters,
+                                                         uint32_t leave) {
     constexpr bool needJ = V != 3;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer and load stage
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
-    const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round);
+    const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round, leave);
     Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles};
     uint8_t *stage = (uint8_t *)tb;
     TileCursor cur = cursor_start(w);
@@ -1221,16 +1225,29 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
 
 // ------------------------------------------------------------- tile queue
 
-// Seeds the tile queue with band b's dirty list of `round` (block b).
-__global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists,
-                                  const uint32_t *__restrict__ counts, int64_t n_tiles,
-                                  uint32_t round, uint32_t *__restrict__ state,
-                                  uint32_t *__restrict__ ring, uint64_t cap, Ctrl *ctrl) {
+// Seeds the tile queue with band b's dirty list (block b): of `round`, or of an
+// earlier round whose tiles were left to the queue (more than none and at most
+// `leave` of them; the rounds after it had nothing to visit).
+__global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl, int64_t n_tiles,
+                                  uint32_t round, uint32_t leave, uint32_t *__restrict__ state,
+                                  uint32_t *__restrict__ ring, uint64_t cap) {
     __shared__ unsigned long long base;
+    __shared__ uint32_t from;
     const int b = blockIdx.x;
-    const uint32_t n = counts[b];
+    if (threadIdx.x == 0) {
+        uint32_t r = 2;
+        for (; r < round; ++r) {
+            uint32_t total = 0;
+#pragma unroll
+            for (int q = 0; q < NBANDS; ++q) total += ctrl->round_tiles[r][q];
+            if (total <= leave) break;
+        }
+        from = r;
+    }
+    __syncthreads();
+    const uint32_t n = ctrl->round_tiles[from][b];
     if (n == 0) return;
-    const uint32_t *list = lists + (round & 1) * n_tiles + band_lo(n_tiles, b);
+    const uint32_t *list = lists + (from & 1) * n_tiles + band_lo(n_tiles, b);
     if (threadIdx.x == 0) {
         base = atomicAdd(&ctrl->q_tail.v, (unsigned long long)n);
         atomicAdd(&ctrl->pending.v, (unsigned long long)n);
@@ -1259,9 +1276,26 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
                                                       uint32_t *__restrict__ state,
                                                       uint32_t *__restrict__ ring, uint64_t cap,
                                                       int max_iters,
-                                                      unsigned long long wait_us) {
+                                                      unsigned long long wait_us,
+                                                      uint32_t round, uint32_t leave) {
     __shared__ uint32_t tb[TS][TS + 1];
     const int lane = threadIdx.x;
+    // The counts for the work counters: rounds launched, and the tiles of a
+    // round left to the queue moved to where handed-over tiles stand.
+    if (blockIdx.x == 0 && lane < NBANDS) {
+        if (lane == 0) ctrl->rounds = round - 1;
+        for (uint32_t r = 2; r < round; ++r) {
+            const uint32_t n = ctrl->round_tiles[r][lane];
+            uint32_t total = n;
+#pragma unroll
+            for (int k = 1; k < NBANDS; k <<= 1) total += __shfl_xor(total, k);
+            if (total <= leave) {
+                ctrl->round_tiles[r][lane] = 0;
+                ctrl->round_tiles[round][lane] = n;
+                break;
+            }
+        }
+    }
     Appender app{nullptr, 0, nullptr, nullptr, 0}; // unused: marks go to the ring
     unsigned long long visits = 0;
     // nothing seeded: no wave will ever retire a tile and write the stops
@@ -1607,10 +1641,12 @@ __global__ void k_clear_ctrl(Ctrl *c, int64_t n_tiles) {
 }
 
 // The start of a launch sequence in one kernel: the control block (block 0;
-// round 1 lists every tile of each band), the dirty flags, and the queue
-// flags and ring of the tile queue and the queue phase.
+// round 1 lists every tile of each band), the dirty flags, the queue
+// flags and ring of the tile queue and the queue phase, and a single image's
+// descriptor.
 __global__ void k_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_t *qflag,
-                              uint32_t *ring, int64_t ring_cap) {
+                              uint32_t *ring, int64_t ring_cap, ImgDesc *desc, ImgDesc d) {
+    if (desc && blockIdx.x == 0 && threadIdx.x == 0) *desc = d;
     if (blockIdx.x == 0) {
         unsigned long long *p = (unsigned long long *)c;
         const int n = (int)(sizeof(Ctrl) / sizeof(unsigned long long));
@@ -1673,8 +1709,6 @@ __global__ __launch_bounds__(64) void k_fill_output(Imgs imgs, int64_t t0) {
 }
 
 __global__ void k_store_u64(unsigned long long *p, unsigned long long v) { *p = v; }
-
-__global__ void k_put_desc(ImgDesc *dst, ImgDesc v) { *dst = v; }
 
 struct DescChunk {
     ImgDesc d[DESC_CHUNK];
@@ -1762,11 +1796,12 @@ hipError_t launch_clear_ctrl(Ctrl *c, int64_t n_tiles, hipStream_t s) {
     return hipGetLastError();
 }
 hipError_t launch_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_t *qflag,
-                              uint32_t *ring, int64_t ring_cap, hipStream_t s) {
+                              uint32_t *ring, int64_t ring_cap, ImgDesc *desc, const ImgDesc &d,
+                              hipStream_t s) {
     const int64_t n = std::max<int64_t>(n_tiles, ring_cap);
     const int64_t blocks = std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 4096));
     hipLaunchKernelGGL(k_clear_start, dim3((unsigned)blocks), dim3(256), 0, s, c, n_tiles, flags,
-                       qflag, ring, ring_cap);
+                       qflag, ring, ring_cap, desc, d);
     return hipGetLastError();
 }
 
@@ -1774,17 +1809,17 @@ template <typename T, int CONN, int V>
 static hipError_t tile_round_v(const Imgs &imgs, int64_t n_tiles, uint32_t *flags,
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
-                               hipStream_t s) {
+                               hipStream_t s, uint32_t leave) {
     const int64_t want = std::max<int64_t>(NBANDS, (n_tiles + NBANDS - 1) / NBANDS * NBANDS);
     const unsigned g = (unsigned)(std::min<int64_t>(grid, want) / NBANDS * NBANDS);
     // (uint8 planes beyond the stage's range are rare: one kernel for all visits)
     constexpr int VR = sizeof(T) == 1 ? -1 : V;
     if (sizeof(T) == 1 && imgs.staged)
         hipLaunchKernelGGL((k_tile_round_pf<CONN, V>), dim3(g), dim3(64), 0, s, imgs,
-                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters);
+                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, leave);
     else
         hipLaunchKernelGGL((k_tile_round<T, CONN, VR>), dim3(g), dim3(64), 0, s, imgs, n_tiles,
-                           flags, lists, cin, cout, all, ctrl, round, max_iters);
+                           flags, lists, cin, cout, all, ctrl, round, max_iters, leave);
     return hipGetLastError();
 }
 
@@ -1792,26 +1827,27 @@ template <typename T, int CONN>
 static hipError_t tile_round_t(const Imgs &imgs, int64_t n_tiles, uint32_t *flags,
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
-                               hipStream_t s, int variant) {
+                               hipStream_t s, int variant, uint32_t leave) {
     switch (variant) {
-    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s);
-    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s);
-    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s);
-    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s);
-    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s);
+    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
+    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
+    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
+    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
+    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
     }
 }
 
 static hipError_t tile_round_any(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                                  uint32_t *flags, uint32_t *lists, const uint32_t *cin,
                                  uint32_t *cout, int all, Ctrl *ctrl, uint32_t round,
-                                 int max_iters, int grid, hipStream_t s, int variant) {
+                                 int max_iters, int grid, hipStream_t s, int variant,
+                                 uint32_t leave) {
     if (!ctrl) return hipErrorInvalidValue;
     if (tbytes == 1)
-        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant)
-                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant);
-    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant)
-                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant);
+        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave)
+                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave);
+    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave)
+                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave);
 }
 
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
@@ -1819,12 +1855,12 @@ hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t 
                                 uint32_t *cout, int all, Ctrl *ctrl, uint32_t round,
                                 int max_iters, int grid, hipStream_t s) {
     return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round,
-                          max_iters, grid, s, -1);
+                          max_iters, grid, s, -1, 0);
 }
 
 hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              uint32_t *flags, uint32_t *lists, Ctrl *ctrl, uint32_t round,
-                             int max_iters, int grid, hipStream_t s, int op_all) {
+                             int max_iters, int grid, hipStream_t s, int op_all, uint32_t leave) {
     // every image starts in round 1 here, so with one op for all of them the
     // visit is known for the whole launch
     const int variant = op_all < 0 ? -1 : ((op_all == MR_OP_FILL ? 2 : 0) | (round == 1 ? 1 : 0));
@@ -1836,44 +1872,45 @@ hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_t
     // stale more often), so uint8 rounds keep the lists.
     return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, ctrl->round_tiles[round],
                           ctrl->round_tiles[round + 1], round == 1 ? 1 : (tbytes == 4 ? 2 : 0), ctrl, round,
-                          max_iters, grid, s, variant);
+                          max_iters, grid, s, variant, leave);
 }
 
 template <typename T, int CONN, int V>
 static hipError_t tile_queue_v(const Imgs &imgs, Ctrl *ctrl, uint32_t *state, uint32_t *ring,
                                uint64_t cap, int max_iters, int grid, unsigned long long wait_us,
-                               hipStream_t s) {
+                               hipStream_t s, uint32_t round, uint32_t leave) {
     hipLaunchKernelGGL((k_tile_queue<T, CONN, V>), dim3((unsigned)grid), dim3(64), 0, s, imgs,
-                       ctrl, state, ring, cap, max_iters, wait_us);
+                       ctrl, state, ring, cap, max_iters, wait_us, round, leave);
     return hipGetLastError();
 }
 template <typename T, int CONN>
 static hipError_t tile_queue_t(const Imgs &imgs, Ctrl *ctrl, uint32_t *state, uint32_t *ring,
                                uint64_t cap, int max_iters, int grid, unsigned long long wait_us,
-                               hipStream_t s, int op_all) {
+                               hipStream_t s, int op_all, uint32_t round, uint32_t leave) {
     if (op_all == MR_OP_RECON)
-        return tile_queue_v<T, CONN, 0>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s);
+        return tile_queue_v<T, CONN, 0>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
     if (op_all == MR_OP_FILL)
-        return tile_queue_v<T, CONN, 2>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s);
-    return tile_queue_v<T, CONN, -1>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s);
+        return tile_queue_v<T, CONN, 2>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
+    return tile_queue_v<T, CONN, -1>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
 }
 hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              const uint32_t *lists, uint32_t round, Ctrl *ctrl, uint32_t *state,
                              uint32_t *ring, uint64_t cap, int max_iters, int grid,
-                             unsigned long long wait_us, hipStream_t s, int op_all) {
+                             unsigned long long wait_us, hipStream_t s, int op_all,
+                             uint32_t leave) {
     if (!ctrl || round > (uint32_t)MAX_ROUNDS + 1 || grid < 1 || n_tiles < 1)
         return hipErrorInvalidValue;
     // no more waves than tiles: a wave visits one tile at a time
     grid = (int)std::min<int64_t>(std::min<int64_t>(grid, RING_SLACK), n_tiles);
-    hipLaunchKernelGGL(k_tile_queue_seed, dim3(NBANDS), dim3(256), 0, s, lists,
-                       ctrl->round_tiles[round], n_tiles, round, state, ring, cap, ctrl);
+    hipLaunchKernelGGL(k_tile_queue_seed, dim3(NBANDS), dim3(256), 0, s, lists, ctrl, n_tiles,
+                       round, leave, state, ring, cap);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (tbytes == 1)
-        return conn == 8 ? tile_queue_t<uint8_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all)
-                         : tile_queue_t<uint8_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all);
-    return conn == 8 ? tile_queue_t<int32_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all)
-                     : tile_queue_t<int32_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all);
+        return conn == 8 ? tile_queue_t<uint8_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave)
+                         : tile_queue_t<uint8_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave);
+    return conn == 8 ? tile_queue_t<int32_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave)
+                     : tile_queue_t<int32_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave);
 }
 
 template <typename T, int CONN>
@@ -1970,11 +2007,6 @@ hipError_t launch_fill_output(int tbytes, const Imgs &imgs, int64_t n_tiles, hip
         hipLaunchKernelGGL(k_fill_output<uint8_t>, dim3((unsigned)n_tiles), dim3(64), 0, s, imgs, t0);
     else
         hipLaunchKernelGGL(k_fill_output<int32_t>, dim3((unsigned)n_tiles), dim3(64), 0, s, imgs, t0);
-    return hipGetLastError();
-}
-
-hipError_t launch_put_desc(ImgDesc *dst, const ImgDesc &v, hipStream_t s) {
-    hipLaunchKernelGGL(k_put_desc, dim3(1), dim3(1), 0, s, dst, v);
     return hipGetLastError();
 }
 
