@@ -10,7 +10,9 @@
  *     Sec. III-B) and area threshold (Table II: a map and a reduction).
  *
  * Conventions (as in mr.h): every image pointer is a DEVICE pointer owned by
- * the caller; rows are `pitch` elements apart (0 means W); H, W >= 1; the
+ * the caller; rows are `pitch` elements apart (0 means W); H, W >= 1; uint8
+ * images are read in aligned 32-bit words, each holding at least one of the
+ * image's pixels; the
  * library allocates no device memory, scratch space is the caller's
  * workspace (256-byte aligned, contents on entry irrelevant) whose size the
  * *_workspace_bytes call gives; `stream` is a hipStream_t as void* (NULL =
@@ -102,8 +104,7 @@ int mr_disk13(int op, const void *in, void *out, int64_t H, int64_t W, int64_t p
  * background pixel. The result is unique. A first pass settles distances up
  * to 16 from the image's bits; what is further goes by wavefront propagation
  * over 64 x 64 tiles, revisiting tiles whose border changed until no tile
- * changes (the host waits on a small counter between batches of rounds). img
- * is read in aligned 32-bit words that hold at least one of its pixels.
+ * changes (the host waits on a small counter between batches of rounds).
  * Errors: MR_EINVAL, MR_ENOMEM, MR_EHIP. */
 size_t mr_distance_transform_workspace_bytes(int64_t H, int64_t W, int conn);
 int mr_distance_transform(const void *img, void *dist, int64_t H, int64_t W, int64_t pitch,
@@ -120,8 +121,7 @@ int mr_distance_transform(const void *img, void *dist, int64_t H, int64_t W, int
  * unique and independent of the order of the merges. H * W < 2^31 - 1.
  * Three launches: union-find of horizontal runs inside 64 x 64 tiles in LDS,
  * merges of the trees across tile borders with device atomics, and the labels
- * written. Workspace: the forest, 4 bytes per pixel. img is read in aligned
- * 32-bit words that hold at least one of its pixels. Errors: MR_EINVAL,
+ * written. Workspace: the forest, 4 bytes per pixel. Errors: MR_EINVAL,
  * MR_ENOMEM, MR_EHIP. */
 size_t mr_ccl_workspace_bytes(int64_t H, int64_t W);
 int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,

@@ -8,6 +8,7 @@
 #include <algorithm>
 #include <cstdarg>
 #include <cstdio>
+#include <type_traits>
 
 #include "../../include/mr_ops.h"
 #include "mr_internal.h"
@@ -293,30 +294,34 @@ __global__ __launch_bounds__(256) void k_rgb2gray1(const uint8_t *__restrict__ r
 
 // -------------------------------------------------------- 13 x 13 disk
 
-// The disk of radius 6 as rows: offset dy has half-width HW[|dy|]
-// (dy^2 + dx^2 <= 36: 6, 5, 5, 5, 4, 3, 0).
+// The disk of radius 6 as rows: offset dy has half-width 6, 5, 5, 5, 4, 3, 0 at
+// |dy| = 0..6 (dy^2 + dx^2 <= 36).
 // One wave per workgroup. A wave's 64 lanes cover a window of 256 adjacent
-// columns, 4 per lane, and it produces the 240 columns of lanes 2..61 for
-// DK_TH rows: an extremum over 13 columns needs 6 columns on each side, and
-// lanes 0, 1, 62 and 63 supply them. Per input row each lane loads the one
-// dword of its 4 columns, forms the horizontal extrema of half-widths 1, 3,
-// 4, 5 and 6 of its own columns, taking the few values it needs of the
-// neighbouring lanes' columns by lane shifts (DPP), and folds them into 13
-// running accumulators, one per output row that this input row still
-// contributes to (the accumulator of the output row dy above gets the
-// extremum of half-width HW[|dy|]). Each output row is complete once its
-// last input row is folded in, and is stored. Pixels outside the image read
-// as the operation's identity (255 for the erosion, 0 for the dilation),
-// which leaves the extrema over the inside offsets.
-constexpr int DK_OUT = 240;          // output columns per wave (lanes 2..61)
-constexpr int DK_TH = 64;           // output rows per wave
-constexpr int DK_ROWS = DK_TH + 12;  // input rows per wave
-
-typedef uint16_t u16x2 __attribute__((ext_vector_type(2)));
+// columns, 4 per lane, and it produces the 240 columns of lanes 2..61 for `th`
+// rows: an extremum over 13 columns needs 6 columns on each side, and lanes 0,
+// 1, 62 and 63 supply them. Per input row each lane loads the dword of its 4
+// columns, forms the horizontal extrema of half-widths 1, 3, 4, 5 and 6 of its
+// own columns, taking the few values it needs of the neighbouring lanes' columns
+// by lane shifts (DPP, which the two-operand extrema take along), and combines
+// them down the rows with three-operand extrema: the seven rows of half-width 5
+// (row 0's half-width 6 covers its own) by a running extremum over 3 and 7
+// rows, the others in 13 accumulators, one per output row still open, which
+// take their values in pairs. That is 24 + 24 extrema for 4 pixels.
+// Pixels outside the image read as the operation's identity (255 for the
+// erosion, 0 for the dilation), which leaves the extrema over the inside offsets.
+// Bound by instruction issue: 60 vector instructions a step and wave, which take 94 %
+// of the issue slots while the chip is full; 16384 x 16384 takes 160 us a
+// pass (3.4 TB/s), 238 us when 13 rows folded into 13 packed 16-bit accumulators
+// (packed 16-bit extrema issue at half rate: two strips sharing 16-bit halves
+// took 228 us). Without the die-wise order of the strips: 182 us.
+constexpr int DK_OUT = 240;         // output columns per wave (lanes 2..61)
+constexpr int DK_WAVES_PER_SIMD = 4; // by its registers
 
 template <bool MIN> __device__ __forceinline__ uint32_t ext(uint32_t a, uint32_t b) {
     return MIN ? min(a, b) : max(a, b);
 }
+// (opaque: an accumulator's extrema are associative, and the compiler would
+// gather them at the row that completes it, keeping all their operands alive)
 template <bool MIN> __device__ __forceinline__ uint32_t ext3(uint32_t a, uint32_t b, uint32_t c) {
     uint32_t r;
     if (MIN)
@@ -338,177 +343,241 @@ __device__ __forceinline__ uint32_t from_right(uint32_t v) {
 }
 
 template <bool MIN>
-__global__ __launch_bounds__(64) void k_disk13(const uint8_t *__restrict__ in,
-                                               uint8_t *__restrict__ out, int64_t H, int64_t W,
-                                               int64_t pitch, int64_t tiles_x) {
-    const uint32_t ident = MIN ? 0xFFu : 0u;
+__global__ __launch_bounds__(64, DK_WAVES_PER_SIMD) void k_disk13(const uint8_t *__restrict__ in,
+                                                                  uint8_t *__restrict__ out,
+                                                                  int64_t H, int64_t W,
+                                                                  int64_t pitch, uint32_t tiles_x,
+                                                                  uint32_t tiles, int th) {
     const uint32_t ident4 = MIN ? 0xFFFFFFFFu : 0u;
     const int lane = threadIdx.x;
-    const int64_t tile = blockIdx.x;
-    const int64_t ty = tile / tiles_x, tx = tile - ty * tiles_x;
-    const int64_t y0 = ty * DK_TH;
-    const int64_t gx = tx * DK_OUT - 8 + 4 * lane; // this lane's first column
-    const bool whole = gx >= 0 && gx + 3 < W;
-    // A strip whose 256 columns all lie inside the image, with dword-aligned
-    // rows, takes the fast path: a row is one plain dword load per lane from
-    // the row's uniform base plus a 32-bit lane offset, with no per-lane
-    // branch, so the 13 loads of a step are in flight together. Strips at the
-    // image's left and right edges (and unaligned planes) take the general
-    // path below.
-    const bool fast =
-        ((((uintptr_t)in) | ((uintptr_t)out) | (uintptr_t)pitch) & 3) == 0 &&
-        W < (1ll << 31) && __ballot(whole) == ~0ull;
-    const uint32_t lx4 = (uint32_t)(fast ? gx : 0);
-    // input row r of this wave is image row y0 - 6 + r
-    auto load = [&](int r) -> uint32_t {
-        const int64_t gy = y0 - 6 + r;
-        if (gy < 0 || gy >= H) return ident4;
-        const uint8_t *p = in + gy * pitch + gx;
-        if (whole && (((uintptr_t)p) & 3) == 0) return *(const uint32_t *)p;
-        uint32_t v = 0u;
+    // (read back to scalars: the division runs on the vector unit)
+    // Workgroups go to the eight dies in turn: each die takes a contiguous range of
+    // strips, so that neighbouring strips, which share cache lines at both ends of
+    // every row (240 columns are no whole lines), share them in one L2.
+    const uint32_t per = gridDim.x / 8, tile = (blockIdx.x & 7) * per + blockIdx.x / 8;
+    if (tile >= tiles) return;
+    const uint32_t ty = (uint32_t)__builtin_amdgcn_readfirstlane(tile / tiles_x);
+    const uint32_t tx = tile - ty * tiles_x;
+    const int64_t y0 = (int64_t)ty * th;           // the strip's first output row
+    const int64_t gx0 = (int64_t)tx * DK_OUT - 8;  // the window's first column
+    const int x = 4 * lane;                        // this lane's first column in the window
+    // rows of the image from y0 (as far as the strip reaches; 32-bit compares),
+    // and the window's columns inside the image
+    const int y_lo = (int)-std::min<int64_t>(y0, 1 << 30), y_hi = (int)std::min<int64_t>(H - y0, 1 << 30);
+    const int x_lo = gx0 < 0 ? (int)-gx0 : 0, x_hi = (int)std::min<int64_t>(256, W - gx0);
+    // Three forms of a strip. Dword-aligned rows: a row is one dword load per lane
+    // from the row's uniform base, with nothing else to do where the window and
+    // the input rows all lie inside the image (FAST); else rows outside the image
+    // and columns outside it take the identity (their loads are moved to the
+    // nearest row and dword inside). Other rows (SHIFTED): the
+    // aligned dword below the lane's pixels, and the row's misalignment
+    // shifted out with the next lane's dword.
+    const int steps = th + 12; // (a multiple of 13: see disk_rows)
+    const bool aligned = ((((uintptr_t)in) | (uintptr_t)pitch) & 3) == 0;
+    const bool whole = x_lo == 0 && x_hi == 256 && y_lo <= -6 && y_hi >= th + 6;
+    uint32_t inside = 0; // 0xFF in every byte whose column lies in the image
 #pragma unroll
-        for (int b = 0; b < 4; ++b) {
-            const uint32_t byte = (gx + b >= 0 && gx + b < W) ? p[b] : ident;
-            v |= byte << (8 * b);
-        }
-        return v;
+    for (int c = 0; c < 4; ++c)
+        if (x + c >= x_lo && x + c < x_hi) inside |= 0xFFu << (8 * c);
+    // The nearest row of the image (uniform; opaque, so that a row's address is
+    // this base and a 32-bit lane offset, not a 64-bit address per lane and row).
+    typedef const __attribute__((address_space(1))) uint8_t *row_t;
+    const row_t in0 = (row_t)in + y0 * pitch + gx0;
+    auto row_of = [&](int y) -> row_t { // y: from the strip's first output row
+        row_t p = in0 + (int64_t)(y < y_lo ? y_lo : (y >= y_hi ? y_hi - 1 : y)) * pitch;
+        asm volatile("" : "+s"(p));
+        return p;
     };
+    typedef const __attribute__((address_space(1))) uint32_t *word_t;
 
-    // 13 accumulators per column in a ring: output row o (wave-relative)
-    // lives in slot o mod 13. Input row r reaches output rows r - 12 .. r
-    // (offsets dy = 6 .. -6), which sit in slots (r + 1 + k) mod 13,
-    // k = 0..12; the rows are walked 13 at a time so that every slot index is
-    // a constant. Two columns per accumulator, one in each 16-bit half (the
-    // pixels are 8-bit), folded with packed 16-bit extrema.
-    const u16x2 identp = {(uint16_t)ident, (uint16_t)ident};
-    u16x2 acc[13][2];
+    // 13 accumulators per column in a ring: output row o (strip-relative) lives
+    // in slot o mod 13. Step r's input row r - 6 opens output row r and
+    // completes output row r - 12; the rows are walked 13 at a time so that
+    // every slot index is a constant.
+    const uint32_t ident = ident4 & 0xFFu;
+    uint32_t acc[13][4];
+    uint32_t e5p[2][4], t3[4][4]; // half-width 5: the rows before; threes of rows before
+    uint32_t e3p[4], p7p[4];      // the row before: half-width 3; seven rows of half-width 5
 #pragma unroll
-    for (int k = 0; k < 13; ++k) acc[k][0] = acc[k][1] = identp;
-    constexpr int HWID[7] = {6, 5, 5, 5, 4, 3, 0}; // half-width of the disk row |dy|
-    const bool stores = lane >= 2 && lane < 62;
+    for (int c = 0; c < 4; ++c) {
+#pragma unroll
+        for (int k = 0; k < 13; ++k) acc[k][c] = ident;
+        e5p[0][c] = e5p[1][c] = e3p[c] = p7p[c] = ident;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) t3[k][c] = ident;
+    }
+    const bool stores = lane >= 2 && lane < 62 && x < x_hi;
+    typedef __attribute__((address_space(1))) uint8_t *orow_t;
+    auto strip = [&](auto kind) {
+    constexpr bool FAST = decltype(kind)::value == 0, SHIFTED = decltype(kind)::value == 2;
+    row_t next_in = in0 - 6 * pitch;                              // FAST: the next row to load
+    orow_t next_out = (orow_t)out + (y0 - 12) * pitch + gx0;      // the next step's output row
 #pragma unroll 1
-    for (int r0 = 0; r0 < DK_ROWS; r0 += 13) {
-        uint32_t wd[13];
-        if (fast) {
+    for (int r0 = 0; r0 < steps; r0 += 13) {
+        uint32_t w[13]; // this lane's dwords of 13 rows
+        const int ra = r0 - 6;
+        if (FAST) {
 #pragma unroll
             for (int rr = 0; rr < 13; ++rr) {
-                // rows outside the image (and past the strip's last input
-                // row) load a clamped row and take the identity instead
-                const int64_t gy = y0 - 6 + r0 + rr;
-                const int64_t cy = gy < 0 ? 0 : (gy >= H ? H - 1 : gy);
-                const uint32_t v = *(const uint32_t *)(in + cy * pitch + lx4);
-                wd[rr] = (gy >= 0 && gy < H && r0 + rr < DK_ROWS) ? v : ident4;
+                // (one row at a time: the scheduler would hold all the addresses)
+                w[rr] = *(word_t)(next_in + (uint32_t)x);
+                next_in += pitch;
+                asm volatile("" : "+s"(next_in));
             }
         } else {
+            uint32_t after[13]; // (lane 63 has no next lane: the dword after its own)
 #pragma unroll
-            for (int rr = 0; rr < 13; ++rr) wd[rr] = r0 + rr < DK_ROWS ? load(r0 + rr) : ident4;
+            for (int rr = 0; rr < 13; ++rr) {
+                row_t row = row_of(ra + rr);
+                const int mis = SHIFTED ? (int)((uintptr_t)row & 3) : 0;
+                // dwords of the row start at multiples of 4 from row - mis (gx0 is one)
+                const int last = (x_hi - 1 + mis) & ~3;
+                const int o = x < (x_lo & ~3) ? x_lo & ~3 : (x > last ? last : x);
+                if (SHIFTED) {
+                    row -= mis;
+                    asm volatile("" : "+s"(row));
+                }
+                w[rr] = *(word_t)(row + (uint32_t)o);
+                if (SHIFTED) after[rr] = *(word_t)(row + (uint32_t)std::min(256, last));
+                __builtin_amdgcn_sched_barrier(0);
+            }
+#pragma unroll
+            for (int rr = 0; rr < 13; ++rr) {
+                if (SHIFTED) {
+                    const uint32_t mis = (uint32_t)((uintptr_t)row_of(ra + rr) & 3);
+                    const uint32_t next = (uint32_t)__builtin_amdgcn_update_dpp(
+                        (int)after[rr], (int)w[rr], 0x130 /* wave_shl:1 */, 0xF, 0xF, false);
+                    w[rr] = __builtin_amdgcn_alignbyte(next, w[rr], mis);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+                w[rr] = (w[rr] & inside) | (ident4 & ~inside);
+            }
         }
 #pragma unroll
         for (int rr = 0; rr < 13; ++rr) {
             const int r = r0 + rr;
-            if (r >= DK_ROWS) break;
-            // e_w[c]: the extremum over columns c - w .. c + w of this lane's
-            // column c (0..3); index c + 1 of the arrays below, so that the
-            // left neighbour's last column is index 0 and the right
-            // neighbour's first is index 5 where a step needs them
-            uint32_t b[4];
-            b[0] = wd[rr] & 0xFFu;
+            const uint32_t v = FAST || (ra + rr >= y_lo && ra + rr < y_hi) ? w[rr] : ident4;
+            uint32_t b[4], e1[4], e3[4], e4[4], e5[4], e6[4];
+            b[0] = v & 0xFFu;
+            b[1] = __builtin_amdgcn_ubfe(v, 8, 8);
+            b[2] = __builtin_amdgcn_ubfe(v, 16, 8);
+            b[3] = v >> 24;
+            // e_w[c]: the extremum over columns c - w .. c + w
+            {
+                const uint32_t m01 = ext<MIN>(b[0], b[1]), m23 = ext<MIN>(b[2], b[3]);
+                e1[0] = ext<MIN>(from_left(b[3]), m01);
+                e1[1] = ext<MIN>(m01, b[2]);
+                e1[2] = ext<MIN>(b[1], m23);
+                e1[3] = ext<MIN>(from_right(b[0]), m23);
+            }
+            {
+                const uint32_t m02 = ext<MIN>(e1[0], e1[2]), m13 = ext<MIN>(e1[1], e1[3]);
+                e3[0] = ext<MIN>(from_left(e1[2]), m02);
+                e3[1] = ext<MIN>(from_left(e1[3]), m13);
+                e3[2] = ext<MIN>(from_right(e1[0]), m02);
+                e3[3] = ext<MIN>(from_right(e1[1]), m13);
+            }
+            auto wider = [&](const uint32_t (&e)[4], uint32_t (&o)[4]) { // a column more each side
+                o[0] = ext<MIN>(from_left(e[3]), e[1]);
+                o[1] = ext<MIN>(e[0], e[2]);
+                o[2] = ext<MIN>(e[1], e[3]);
+                o[3] = ext<MIN>(from_right(e[0]), e[2]);
+            };
+            wider(e3, e4);
+            wider(e4, e5);
+            wider(e5, e6);
+            auto slot = [&](int back) { return (rr - back + 26) % 13; }; // of output row r - back
 #pragma unroll
-            for (int c = 1; c < 4; ++c) b[c] = __builtin_amdgcn_ubfe(wd[rr], 8 * c, 8);
-            uint32_t e1[4], e3[4], e4[4], e5[4], e6[4];
-            {
-                const uint32_t l = from_left(b[3]), rt = from_right(b[0]);
-                e1[0] = ext3<MIN>(l, b[0], b[1]);
-                e1[1] = ext3<MIN>(b[0], b[1], b[2]);
-                e1[2] = ext3<MIN>(b[1], b[2], b[3]);
-                e1[3] = ext3<MIN>(b[2], b[3], rt);
+            for (int c = 0; c < 4; ++c) {
+                // half-width 5 over rows r - 2 .. r, and r - 6 .. r
+                const uint32_t p3 = ext3<MIN>(e5p[1][c], e5p[0][c], e5[c]);
+                const uint32_t p7 = ext3<MIN>(t3[3][c], t3[1][c], p3);
+                e5p[1][c] = e5p[0][c];
+                e5p[0][c] = e5[c];
+                t3[3][c] = t3[2][c];
+                t3[2][c] = t3[1][c];
+                t3[1][c] = t3[0][c];
+                t3[0][c] = p3;
+                uint32_t &a12 = acc[slot(12)][c], &a10 = acc[slot(10)][c], &a6 = acc[slot(6)][c];
+                uint32_t &a2 = acc[slot(2)][c];
+                // (the value of the row before goes with this row's: output row
+                // r - 12 took half-width 3 one row above, and so on)
+                a12 = ext3<MIN>(a12, e3p[c], b[c]);
+                a10 = ext3<MIN>(a10, p7p[c], e4[c]);
+                a6 = ext3<MIN>(a6, e6[c], e6[c]);
+                a2 = ext3<MIN>(a2, e3p[c], e4[c]);
+                e3p[c] = e3[c];
+                p7p[c] = p7;
             }
-            {
-                const uint32_t l2 = from_left(e1[2]), l3 = from_left(e1[3]);
-                const uint32_t r0v = from_right(e1[0]), r1v = from_right(e1[1]);
-                e3[0] = ext3<MIN>(l2, e1[0], e1[2]);
-                e3[1] = ext3<MIN>(l3, e1[1], e1[3]);
-                e3[2] = ext3<MIN>(e1[0], e1[2], r0v);
-                e3[3] = ext3<MIN>(e1[1], e1[3], r1v);
-            }
-            {
-                const uint32_t l = from_left(e3[3]), rt = from_right(e3[0]);
-                e4[0] = ext<MIN>(l, e3[1]);
-                e4[1] = ext<MIN>(e3[0], e3[2]);
-                e4[2] = ext<MIN>(e3[1], e3[3]);
-                e4[3] = ext<MIN>(e3[2], rt);
-            }
-            {
-                const uint32_t l = from_left(e4[3]), rt = from_right(e4[0]);
-                e5[0] = ext<MIN>(l, e4[1]);
-                e5[1] = ext<MIN>(e4[0], e4[2]);
-                e5[2] = ext<MIN>(e4[1], e4[3]);
-                e5[3] = ext<MIN>(e4[2], rt);
-            }
-            {
-                const uint32_t l = from_left(e5[3]), rt = from_right(e5[0]);
-                e6[0] = ext<MIN>(l, e5[1]);
-                e6[1] = ext<MIN>(e5[0], e5[2]);
-                e6[2] = ext<MIN>(e5[1], e5[3]);
-                e6[3] = ext<MIN>(e5[2], rt);
-            }
-            // fold into output row r - 12 + k, which lies dy = 6 - k rows above
-            // this input row, with the disk row's half-width at |dy|
-#pragma unroll
-            for (int k = 0; k < 13; ++k) {
-                const int ady = k <= 6 ? 6 - k : k - 6;
-                const int hw = HWID[ady];
-                const int slot = (rr + 1 + k) % 13;
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    auto pick = [&](int c) -> uint32_t {
-                        return hw == 6 ? e6[c] : hw == 5 ? e5[c] : hw == 4 ? e4[c]
-                             : hw == 3 ? e3[c] : b[c];
-                    };
-                    const u16x2 v = {(uint16_t)pick(2 * h), (uint16_t)pick(2 * h + 1)};
-                    acc[slot][h] = MIN ? __builtin_elementwise_min(acc[slot][h], v)
-                                       : __builtin_elementwise_max(acc[slot][h], v);
-                }
-            }
-            // output row r - 12 has all 13 of its input rows: store it, and
-            // start the slot over for output row r + 1
-            const int done = (rr + 1) % 13;
-            const int64_t oy = y0 + r - 12;
-            if (fast && r >= 12 && oy < H) {
-                if (stores)
-                    *(uint32_t *)(out + oy * pitch + lx4) = __builtin_amdgcn_perm(
-                        __builtin_bit_cast(uint32_t, acc[done][1]),
-                        __builtin_bit_cast(uint32_t, acc[done][0]), 0x06040200u);
-            } else if (r >= 12 && oy < H && stores && gx < W) {
-                uint8_t *orow = out + oy * pitch;
-                // the low bytes of the four 16-bit halves, in column order
-                const uint32_t o4 = __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, acc[done][1]),
-                                                          __builtin_bit_cast(uint32_t, acc[done][0]),
-                                                          0x06040200u);
-                if (gx + 3 < W && (((uintptr_t)(orow + gx)) & 3) == 0) {
-                    *(uint32_t *)(orow + gx) = o4;
+            // output row r - 12 is complete: store it, then open row r
+            if (r >= 12 && (FAST || r - 12 < y_hi) && stores) {
+                const uint32_t *o = acc[slot(12)];
+                const uint32_t q = __builtin_amdgcn_perm(o[2] | o[3] << 8, o[0] | o[1] << 8,
+                                                         0x05040100u);
+                typedef uint32_t u32_any __attribute__((aligned(1)));
+                orow_t op = next_out + (uint32_t)x;
+                if (FAST || x_hi == 256 || x + 4 <= x_hi) { // (a dword store on any byte)
+                    *(__attribute__((address_space(1))) u32_any *)op = q;
                 } else {
-#pragma unroll
-                    for (int c = 0; c < 4; ++c)
-                        if (gx + c < W) orow[gx + c] = (uint8_t)(o4 >> (8 * c));
+                    op[0] = (uint8_t)q;
+                    if (x + 1 < x_hi) op[1] = (uint8_t)(q >> 8);
+                    if (x + 2 < x_hi) op[2] = (uint8_t)(q >> 16);
                 }
             }
-            acc[done][0] = acc[done][1] = identp;
+            next_out += pitch;
+            asm volatile("" : "+s"(next_out));
+#pragma unroll
+            for (int c = 0; c < 4; ++c) acc[rr][c] = b[c];
+            // (steps overlapped further by the scheduler would spill)
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
+    };
+    if (aligned && whole)
+        strip(std::integral_constant<int, 0>{});
+    else if (aligned)
+        strip(std::integral_constant<int, 1>{});
+    else
+        strip(std::integral_constant<int, 2>{});
+}
+
+// Rows per strip: 13 m - 12, so that its th + 12 steps are whole turns of the
+// accumulator ring. The chip holds a fixed number of waves: the strips are cut so
+// that they fill it a whole number of times, twice at least, and the number of
+// times is the one with the fewest steps in all. (Filled once, the chip waits
+// for the strips at the image's edges, which take longer: 16384 x 16384 takes
+// 175 us filled once, 160 us twice or three times, 166 us five times. Strips
+// of 64 rows, 4.3 fillings, took 218 us.)
+int disk_rows(int64_t H, int64_t tx) {
+    const int64_t cap = (int64_t)persistent_grid() / 2 * DK_WAVES_PER_SIMD; // (grid: 2 waves a SIMD)
+    int64_t best = 1ll << 62;
+    int th = 13 * 6 - 12;
+    for (int64_t k = 2; k <= 8; ++k) {
+        const int64_t strips = k * cap / tx;
+        if (strips == 0) continue;
+        const int64_t m = std::max<int64_t>(2, ((H + strips - 1) / strips + 12 + 12) / 13);
+        if (m > 1 << 16) continue;
+        if (k * m < best) {
+            best = k * m;
+            th = (int)(13 * m - 12);
+        }
+    }
+    return th;
 }
 
 hipError_t launch_disk13(bool erode, const uint8_t *in, uint8_t *out, int64_t H, int64_t W,
                          int64_t pitch, hipStream_t s) {
-    const int64_t tx = (W + DK_OUT - 1) / DK_OUT, ty = (H + DK_TH - 1) / DK_TH;
-    const int64_t n = tx * ty;
-    if (n >= (1ll << 31)) return hipErrorInvalidValue;
+    const int64_t tx = (W + DK_OUT - 1) / DK_OUT;
+    const int th = disk_rows(H, tx);
+    const int64_t n = tx * ((H + th - 1) / th);
+    if (n >= (1ll << 31) - 8) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(n + 7) / 8 * 8);
     if (erode)
-        hipLaunchKernelGGL(k_disk13<true>, dim3((unsigned)n), dim3(64), 0, s, in, out, H, W, pitch,
-                           tx);
+        hipLaunchKernelGGL(k_disk13<true>, grid, dim3(64), 0, s, in, out, H, W, pitch,
+                           (uint32_t)tx, (uint32_t)n, th);
     else
-        hipLaunchKernelGGL(k_disk13<false>, dim3((unsigned)n), dim3(64), 0, s, in, out, H, W,
-                           pitch, tx);
+        hipLaunchKernelGGL(k_disk13<false>, grid, dim3(64), 0, s, in, out, H, W,
+                           pitch, (uint32_t)tx, (uint32_t)n, th);
     return hipGetLastError();
 }
 

@@ -312,3 +312,20 @@ def test_dt_first_pass_bounds(shape, pad, dpad, conn):
         ops.distance_transform(to_dev(img, pad), conn, out=out[:, :W])
         check(out[:, :W].cpu().numpy(), oracle.distance_transform(img, conn))
         assert bool((out[:, W:] == -7).all())
+
+
+# The disk's three row forms (whole strips, aligned edges, shifted rows), windows
+# of 240 columns, strips of 14 rows on images this small and longer ones on
+# larger ones: widths around a window, every row alignment, a dword past the
+# window at its right end, wide and tall images.
+@pytest.mark.parametrize("shape,pad", [((14, 240), 0), ((15, 241), 0), ((13, 239), 1), ((29, 488), 0),
+                                       ((40, 487), 1), ((43, 486), 1), ((44, 485), 1), ((70, 736), 0),
+                                       ((71, 1000), 2), ((5, 9), 4), ((900, 13), 0), ((2100, 1500), 0)])
+def test_disk_row_forms(shape, pad):
+    rng = np.random.default_rng(shape[0] + 5 * shape[1])
+    img = rng.integers(0, 256, shape).astype(np.uint8)
+    img[rng.random(shape) < 0.9] |= 0xF0  # erosions with more than zeros in them
+    d = to_dev(img, pad)
+    check(ops.disk13(0, d).cpu().numpy(), oracle.erode_disk13(img), "erode: ")
+    check(ops.disk13(1, d).cpu().numpy(), oracle.dilate_disk13(img), "dilate: ")
+    check(ops.open_disk13(d).cpu().numpy(), oracle.open_disk13(img), "open: ")
