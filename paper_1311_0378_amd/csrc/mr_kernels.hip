@@ -698,10 +698,13 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" 
 // wave gives up with Q_STOP. One lane per wave calls it.
 constexpr uint32_t Q_STOP = 0xFFFFFFFEu;
 
+__device__ __forceinline__ unsigned long long ring_ticket(Ctrl *ctrl) {
+    return __hip_atomic_fetch_add(&ctrl->q_head.v, 1ull, __ATOMIC_RELAXED,
+                                  __HIP_MEMORY_SCOPE_AGENT);
+}
+
 __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
-                                              unsigned long long wait_us) {
-    const unsigned long long h =
-        __hip_atomic_fetch_add(&ctrl->q_head.v, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                                              unsigned long long h, unsigned long long wait_us) {
     uint32_t *slot = ring + (h & (cap - 1));
     unsigned long long t0 = wall_clock64(), seen = h;
     uint32_t t;
@@ -729,17 +732,23 @@ __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64
     return t;
 }
 
-// Retire one processed entry; the wave that retires the last one writes a
+// Retire one processed entry (the whole wave); the wave that retires the last one
+// writes a
 // stop entry for each of the launch's `waves` waves (each holds at most one
 // ticket past the last entry).
 __device__ __forceinline__ void ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
-                                            unsigned waves) {
-    const unsigned long long left = __hip_atomic_fetch_add(
-        &ctrl->pending.v, (unsigned long long)-1ll, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (left != 1) return;
-    const unsigned long long base = __hip_atomic_fetch_add(
-        &ctrl->q_tail.v, (unsigned long long)waves, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (unsigned k = 0; k < waves; ++k)
+                                            unsigned waves, int lane) {
+    unsigned long long left = 0, base = 0;
+    if (lane == 0)
+        left = __hip_atomic_fetch_add(&ctrl->pending.v, (unsigned long long)-1ll, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+    if (__ballot(left == 1) == 0) return;
+    if (lane == 0)
+        base = __hip_atomic_fetch_add(&ctrl->q_tail.v, (unsigned long long)waves, __ATOMIC_RELAXED,
+                                      __HIP_MEMORY_SCOPE_AGENT);
+    base = __shfl(base, 0);
+    // (all lanes: 2048 stops written by one lane held the launch's end up by 50 us)
+    for (unsigned k = lane; k < waves; k += 64)
         __hip_atomic_store(ring + ((base + k) & (cap - 1)), Q_STOP, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
 }
@@ -1230,10 +1239,11 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
 // `leave` of them; the rounds after it had nothing to visit).
 __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl, int64_t n_tiles,
                                   uint32_t round, uint32_t leave, uint32_t *__restrict__ state,
-                                  uint32_t *__restrict__ ring, uint64_t cap) {
+                                  uint32_t *__restrict__ ring, uint64_t cap, uint32_t waves) {
     __shared__ unsigned long long base;
     __shared__ uint32_t from;
     const int b = blockIdx.x;
+    if (b == 0 && threadIdx.x == 0) ctrl->q_head.v = waves; // (see the queue's first tickets)
     if (threadIdx.x == 0) {
         uint32_t r = 2;
         for (; r < round; ++r) {
@@ -1269,7 +1279,11 @@ __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl
 // wave. The watchdog (ring_take) turns a stall into an error instead of a hang.
 // Bound by the latency of a link, so a wave hands itself the first idle
 // neighbour it marks instead of queueing it: on the holes of a 4096 x 4096
-// tile the queue takes 269 us (357 us with every neighbour through the ring).
+// tile, after 8 rounds, the queue takes 269 us (357 us with every neighbour
+// through the ring). What 2048 waves do one after the other is kept out of the
+// launch's start and end: tickets taken from the head one by one at the start
+// and stops written by one lane cost 70 us of each launch (that image's whole
+// call 419 -> 348 us).
 
 template <typename T, int CONN, int V>
 __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restrict__ ctrl,
@@ -1302,9 +1316,16 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
     if (__hip_atomic_load(&ctrl->pending.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
         return;
     uint32_t t = Q_EMPTY; // the tile this wave holds: its state is 2, it counts as pending
+    // the first tickets are the waves' numbers (the head starts past them)
+    unsigned long long ticket = blockIdx.x;
+    bool first_take = true;
     while (true) {
         if (t == Q_EMPTY) {
-            if (lane == 0) t = ring_take(ctrl, ring, cap, wait_us);
+            if (lane == 0) {
+                if (!first_take) ticket = ring_ticket(ctrl);
+                t = ring_take(ctrl, ring, cap, ticket, wait_us);
+            }
+            first_take = false;
             t = (uint32_t)__builtin_amdgcn_readfirstlane(t); // (uniform: scalar descriptor loads)
             if (t == Q_STOP) break;
             // queued -> visited, performed before any pixel is read: a mark that
@@ -1376,7 +1397,7 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
         wait_vmem();
         ring_push(ctrl, ring, cap, push, lane);
         // one entry held before and, with a next tile, one held now
-        if (next == Q_EMPTY && lane == 0) ring_retire(ctrl, ring, cap, gridDim.x);
+        if (next == Q_EMPTY) ring_retire(ctrl, ring, cap, gridDim.x, lane);
         t = next;
     }
     if (lane == 0 && visits)
@@ -1542,7 +1563,7 @@ __global__ __launch_bounds__(64 * QWAVES) void k_queue(Imgs imgs, Ctrl *__restri
 
     while (true) {
         uint32_t t = Q_EMPTY;
-        if (lane == 0) t = ring_take(ctrl, ring, cap, wait_us);
+        if (lane == 0) t = ring_take(ctrl, ring, cap, ring_ticket(ctrl), wait_us);
         t = __shfl(t, 0);
         if (t == Q_STOP) break;
         const ImgDesc d = load_desc(imgs, t);
@@ -1606,7 +1627,7 @@ __global__ __launch_bounds__(64 * QWAVES) void k_queue(Imgs imgs, Ctrl *__restri
         }
         // everything this tile produced is pushed; retire the ring entry
         wait_vmem();
-        if (lane == 0) ring_retire(ctrl, ring, cap, gridDim.x * QWAVES);
+        ring_retire(ctrl, ring, cap, gridDim.x * QWAVES, lane);
     }
     // fold the per-lane counters
     unsigned long long p = npush, r = retries;
@@ -1903,7 +1924,7 @@ hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_t
     // no more waves than tiles: a wave visits one tile at a time
     grid = (int)std::min<int64_t>(std::min<int64_t>(grid, RING_SLACK), n_tiles);
     hipLaunchKernelGGL(k_tile_queue_seed, dim3(NBANDS), dim3(256), 0, s, lists, ctrl, n_tiles,
-                       round, leave, state, ring, cap);
+                       round, leave, state, ring, cap, (uint32_t)grid);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (tbytes == 1)
