@@ -84,7 +84,8 @@ typedef struct {
                                   pass and the queue phase, which finish any
                                   input (1..1000; 0 = 1000) */
     int32_t tail_rounds;       /* with a negative sweep_rounds: tile rounds
-                                  after which the tiles still listed go to
+                                  after which the tiles still listed (earlier,
+                                  when a round would list only few) go to
                                   the tile queue, one persistent launch that
                                   revisits a tile as soon as a neighbour marks
                                   it, until none is left; the call then never
@@ -101,7 +102,9 @@ typedef struct {
 
 /* Work counters of the last call that used a workspace. */
 typedef struct {
-    uint64_t rounds;      /* tile rounds launched */
+    uint64_t rounds;      /* tile rounds of the call (with a tile queue, rounds
+                             that would list few tiles leave them to it and
+                             visit none; they count here) */
     uint64_t tiles;       /* tile visits (64 x 64 register tiles), in tile
                              rounds and in the tile queue */
     uint64_t seeds;       /* frontier entries made by the seed pass */
@@ -254,14 +257,16 @@ int mr_autotune(const mr_tile *tiles, int32_t n, mr_dtype t, int conn, void *ws,
 /* A request: one image, answered in a buffer of the same kind. Rows of the
  * inputs are `ld` elements apart and rows of the result `ld_result` apart
  * (0 means W), so a job can be a window of a larger image. The buffers must
- * stay valid until the job is reported done.
+ * stay valid, and the inputs unchanged, until the job is reported done.
  * Host jobs (flags 0): data, mask and result are host memory; pinned
  * (page-locked) memory lets the copies run asynchronously, pageable memory
  * works but copies synchronously.
  * Device jobs (flags MR_JOB_DEVICE): data, mask and result are device
  * memory of the server's GPU, for callers whose tiles are already in HBM
  * (an upstream kernel produced them): the copies into and out of the arena
- * are device-to-device, and no PCIe transfer is involved. */
+ * are device-to-device, and no PCIe transfer is involved. What a job only
+ * reads (the mask, or the image to fill) may be read in place until the job is
+ * done, and a filled image may be written to its result directly. */
 enum { MR_JOB_DEVICE = 1 };
 typedef struct {
     const void *data; /* H x W: the marker (MR_OP_RECON) or the image (MR_OP_FILL) */

@@ -24,7 +24,7 @@ struct ImgDesc {
     const void *I;     // reconstruction: the mask; fill-holes: the input image
     void *out;         // fill-holes: where NOT J goes at the end; else null
     int64_t H, W;
-    int64_t pJ, pI;    // pitches in elements (out uses pI)
+    int64_t pJ, pI, pO; // pitches in elements (pO: of out)
     int64_t tile_base;   // first tile id of this image (its tiles are consecutive)
     int64_t first_round; // the tile round that builds its initial working image
     int32_t ntx, nty;    // tiles across and down
@@ -122,10 +122,10 @@ hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_t
                              int max_iters, int grid, hipStream_t s, int op_all,
                              uint32_t leave);
 // The same round with explicit list-length counters (NBANDS each) for this
-// round and the next; all_tiles visits every tile instead of a list.
+// round and the next, and the counters of a round still to come, which it clears.
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                                 uint32_t *flags, uint32_t *lists, const uint32_t *counts_in,
-                                uint32_t *counts_out, int all_tiles, Ctrl *ctrl,
+                                uint32_t *counts_out, uint32_t *counts_clear, Ctrl *ctrl,
                                 uint32_t round, int max_iters, int grid, hipStream_t s);
 hipError_t launch_seed(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                        const uint32_t *lists, uint32_t round, Ctrl *ctrl, uint64_t *bitmap,
@@ -156,12 +156,13 @@ hipError_t launch_put_descs(ImgDesc *dst, const ImgDesc *v, int n, hipStream_t s
 int queue_max_blocks(int tbytes, int conn);
 int persistent_grid();
 
-// Server support: admit one image (descriptor, owner ids, every tile on the
-// dirty list of round `round`), and mark the images that still have tiles on
+// Server support: admit n <= DESC_CHUNK images (descriptors, owner ids, every tile
+// on the dirty list of round `round`), and mark the images that still have tiles on
 // a round's lists (busy[owner] = stamp).
-hipError_t launch_server_admit(ImgDesc *descs, int32_t slot, const ImgDesc &d, uint32_t *owner,
-                               uint32_t *flags, uint32_t *lists_round, uint32_t *counts_round,
-                               int64_t n_tiles, uint32_t round, hipStream_t s);
+hipError_t launch_server_admit(ImgDesc *descs, const int32_t *slots, const ImgDesc *d, int n,
+                               uint32_t *owner, uint32_t *flags, uint32_t *lists_round,
+                               uint32_t *counts_round, int64_t n_tiles, uint32_t round,
+                               hipStream_t s);
 hipError_t launch_server_status(const uint32_t *lists_round, const uint32_t *counts_round,
                                 const uint32_t *owner, uint32_t *busy, int64_t n_tiles,
                                 uint32_t stamp, hipStream_t s);

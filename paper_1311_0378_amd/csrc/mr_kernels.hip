@@ -75,6 +75,7 @@ __device__ __forceinline__ ImgDesc desc_at(kptr<ImgDesc> d, int64_t k) {
     r.W = d[k].W;
     r.pJ = d[k].pJ;
     r.pI = d[k].pI;
+    r.pO = d[k].pO;
     r.tile_base = d[k].tile_base;
     r.first_round = d[k].first_round;
     r.ntx = d[k].ntx;
@@ -84,7 +85,7 @@ __device__ __forceinline__ ImgDesc desc_at(kptr<ImgDesc> d, int64_t k) {
     r.wide = d[k].wide;
     return r;
 }
-static_assert(sizeof(ImgDesc) == 96, "desc_at copies every field of ImgDesc");
+static_assert(sizeof(ImgDesc) == 104, "desc_at copies every field of ImgDesc");
 
 // Descriptor of the image that owns `tile` (owner table, else binary search
 // on tile_base).
@@ -1145,7 +1146,9 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
                                                       uint32_t *__restrict__ counts_out,
                                                       int all_tiles, Ctrl *__restrict__ ctrl,
                                                       uint32_t round, int max_iters,
-                                                      uint32_t leave) {
+                                                      uint32_t leave,
+                                                      uint32_t *__restrict__ counts_clear) {
+    if (counts_clear && blockIdx.x == 0 && threadIdx.x < NBANDS) counts_clear[threadIdx.x] = 0;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer (and load stage)
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
@@ -1183,7 +1186,9 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                                                          uint32_t *__restrict__ counts_out,
                                                          int all_tiles, Ctrl *__restrict__ ctrl,
                                                          uint32_t round, int max_iters,
-                                                         uint32_t leave) {
+                                                         uint32_t leave,
+                                                         uint32_t *__restrict__ counts_clear) {
+    if (counts_clear && blockIdx.x == 0 && threadIdx.x < NBANDS) counts_clear[threadIdx.x] = 0;
     constexpr bool needJ = V != 3;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer and load stage
     __shared__ uint32_t abuf[APP_CAP];
@@ -1707,25 +1712,39 @@ __global__ __launch_bounds__(64) void k_widen(Imgs imgs, int64_t t0) {
     }
 }
 
-// Fill-holes epilogue: out = NOT J over the interior of every tile of the
-// launch whose image is a fill-holes image.
+// Fill-holes epilogue: out = NOT J for every fill-holes image of the launch. Block t
+// takes the 64 x 64 block number t - tile_base of its image (there are no more of
+// those than tiles), 16 bytes a lane: J's rows are 16-byte aligned in the
+// workspace, out's may start on any pixel. Bound by its launch on one tile's
+// 2 x 16 MiB; a pixel a lane, 62 dependent rows a block, took 24 us there.
 template <typename T>
 __global__ __launch_bounds__(64) void k_fill_output(Imgs imgs, int64_t t0) {
-    using P = Pix<T>;
+    constexpr int E = 16 / (int)sizeof(T); // pixels a lane and step
+    constexpr int LPR = TS / E;            // lanes a row
     const int64_t t = t0 + blockIdx.x;
     const int lane = threadIdx.x;
     const ImgDesc d = load_desc(imgs, t);
     if (d.op != MR_OP_FILL || d.done) return;
-    const int64_t lt = t - d.tile_base;
-    const int ty = (int)(lt / d.ntx), tx = (int)(lt - (int64_t)ty * d.ntx);
-    const int64_t gx = (int64_t)tx * TI - 1 + lane;
-    if (lane < 1 || lane > TS - 2 || gx >= d.W) return;
-    cgptr<T> Jp = (cgptr<T>)d.J;
-    gptr<T> O = (gptr<T>)d.out;
-    for (int r = 1; r < TS - 1; ++r) {
-        const int64_t gy = (int64_t)ty * TI - 1 + r;
-        if (gy >= d.H) break;
-        O[gy * d.pI + gx] = P::val(P::KMAX - P::key(Jp[gy * d.pJ + gx]));
+    const int64_t lt = t - d.tile_base, nbx = (d.W + TS - 1) / TS, by = lt / nbx;
+    const int64_t x = (lt - by * nbx) * TS + E * (lane % LPR);
+    if (x >= d.W) return;
+#pragma unroll 4
+    for (int r = lane / LPR; r < TS; r += 64 / LPR) {
+        const int64_t y = by * TS + r;
+        if (y >= d.H) break;
+        // (~key is the key of the complement in both types: bitwise NOT of the bits)
+        v4u v = *(const v4u *)((const T *)d.J + y * d.pJ + x);
+        v = ~v;
+        T *o = (T *)d.out + y * d.pO + x;
+        if (x + E <= d.W) {
+            __builtin_memcpy(o, &v, 16);
+        } else {
+            T e[E];
+            __builtin_memcpy(e, &v, 16);
+#pragma unroll
+            for (int k = 0; k < E; ++k)
+                if (x + k < d.W) o[k] = e[k];
+        }
     }
 }
 
@@ -1742,22 +1761,37 @@ __global__ void k_put_descs(ImgDesc *dst, DescChunk c) {
 
 // ------------------------------------------------------------------ server
 
-// Admit one image: its descriptor, owner[t] for its tiles, and every one of
-// its tiles on the dirty list of `round` (where it builds its initial
-// values). One thread per tile.
-__global__ void k_server_admit(ImgDesc *descs, int32_t slot, ImgDesc d, uint32_t *owner,
-                               uint32_t *flags, uint32_t *lists_round, uint32_t *counts_round,
-                               int64_t n_tiles, uint32_t round) {
+// Admit images: image blockIdx.y's descriptor, owner[t] for its tiles, and every one
+// of its tiles on the dirty list of `round` (where it builds its initial
+// values). One thread per tile; a wave reserves its places in a band's list with
+// one counter update.
+struct AdmitChunk {
+    ImgDesc d[DESC_CHUNK];
+    int32_t slot[DESC_CHUNK];
+};
+__global__ __launch_bounds__(256) void k_server_admit(ImgDesc *descs, AdmitChunk c, uint32_t *owner,
+                                                      uint32_t *flags, uint32_t *lists_round,
+                                                      uint32_t *counts_round, int64_t n_tiles,
+                                                      uint32_t round) {
+    const ImgDesc &d = c.d[blockIdx.y];
     const int64_t nt = (int64_t)d.ntx * d.nty;
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i == 0) descs[slot] = d;
-    if (i >= nt) return;
+    const int lane = threadIdx.x & 63;
+    if (i == 0) descs[c.slot[blockIdx.y]] = d;
+    const bool in = i < nt;
     const int64_t t = d.tile_base + i;
-    owner[t] = (uint32_t)slot;
+    const int b = in ? band_of(n_tiles, t) : -1;
+    for (int q = 0; q < NBANDS; ++q) {
+        const uint64_t m = __ballot(b == q);
+        if (m == 0) continue;
+        uint32_t pos = 0;
+        if (lane == 0) pos = atomicAdd(counts_round + q, (uint32_t)__popcll(m));
+        pos = __shfl(pos, 0) + (uint32_t)__popcll(m & ((1ull << lane) - 1));
+        if (b == q) lists_round[band_lo(n_tiles, q) + pos] = (uint32_t)t;
+    }
+    if (!in) return;
+    owner[t] = (uint32_t)c.slot[blockIdx.y];
     flags[t] = round;
-    const int b = band_of(n_tiles, t);
-    const uint32_t pos = atomicAdd(counts_round + b, 1u);
-    lists_round[band_lo(n_tiles, b) + pos] = (uint32_t)t;
 }
 
 // busy[image] = stamp for every image with a tile on the round's lists.
@@ -1788,12 +1822,20 @@ int persistent_grid() {
     return g;
 }
 
-hipError_t launch_server_admit(ImgDesc *descs, int32_t slot, const ImgDesc &d, uint32_t *owner,
-                               uint32_t *flags, uint32_t *lists_round, uint32_t *counts_round,
-                               int64_t n_tiles, uint32_t round, hipStream_t s) {
-    const int64_t nt = std::max<int64_t>(1, (int64_t)d.ntx * d.nty);
-    hipLaunchKernelGGL(k_server_admit, dim3((unsigned)((nt + 255) / 256)), dim3(256), 0, s, descs,
-                       slot, d, owner, flags, lists_round, counts_round, n_tiles, round);
+hipError_t launch_server_admit(ImgDesc *descs, const int32_t *slots, const ImgDesc *d, int n,
+                               uint32_t *owner, uint32_t *flags, uint32_t *lists_round,
+                               uint32_t *counts_round, int64_t n_tiles, uint32_t round,
+                               hipStream_t s) {
+    if (n < 1 || n > DESC_CHUNK) return hipErrorInvalidValue;
+    AdmitChunk c{};
+    int64_t most = 1;
+    for (int i = 0; i < n; ++i) {
+        c.d[i] = d[i];
+        c.slot[i] = slots[i];
+        most = std::max<int64_t>(most, (int64_t)d[i].ntx * d[i].nty);
+    }
+    hipLaunchKernelGGL(k_server_admit, dim3((unsigned)((most + 255) / 256), (unsigned)n), dim3(256), 0,
+                       s, descs, c, owner, flags, lists_round, counts_round, n_tiles, round);
     return hipGetLastError();
 }
 
@@ -1830,17 +1872,17 @@ template <typename T, int CONN, int V>
 static hipError_t tile_round_v(const Imgs &imgs, int64_t n_tiles, uint32_t *flags,
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
-                               hipStream_t s, uint32_t leave) {
+                               hipStream_t s, uint32_t leave, uint32_t *clear) {
     const int64_t want = std::max<int64_t>(NBANDS, (n_tiles + NBANDS - 1) / NBANDS * NBANDS);
     const unsigned g = (unsigned)(std::min<int64_t>(grid, want) / NBANDS * NBANDS);
     // (uint8 planes beyond the stage's range are rare: one kernel for all visits)
     constexpr int VR = sizeof(T) == 1 ? -1 : V;
     if (sizeof(T) == 1 && imgs.staged)
         hipLaunchKernelGGL((k_tile_round_pf<CONN, V>), dim3(g), dim3(64), 0, s, imgs,
-                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, leave);
+                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear);
     else
         hipLaunchKernelGGL((k_tile_round<T, CONN, VR>), dim3(g), dim3(64), 0, s, imgs, n_tiles,
-                           flags, lists, cin, cout, all, ctrl, round, max_iters, leave);
+                           flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear);
     return hipGetLastError();
 }
 
@@ -1848,13 +1890,14 @@ template <typename T, int CONN>
 static hipError_t tile_round_t(const Imgs &imgs, int64_t n_tiles, uint32_t *flags,
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
-                               hipStream_t s, int variant, uint32_t leave) {
+                               hipStream_t s, int variant, uint32_t leave,
+                               uint32_t *clear) {
     switch (variant) {
-    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
-    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
-    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
-    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
-    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave);
+    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
     }
 }
 
@@ -1862,21 +1905,21 @@ static hipError_t tile_round_any(int tbytes, int conn, const Imgs &imgs, int64_t
                                  uint32_t *flags, uint32_t *lists, const uint32_t *cin,
                                  uint32_t *cout, int all, Ctrl *ctrl, uint32_t round,
                                  int max_iters, int grid, hipStream_t s, int variant,
-                                 uint32_t leave) {
+                                 uint32_t leave, uint32_t *clear) {
     if (!ctrl) return hipErrorInvalidValue;
     if (tbytes == 1)
-        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave)
-                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave);
-    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave)
-                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave);
+        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear)
+                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear);
+    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear)
+                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear);
 }
 
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                                 uint32_t *flags, uint32_t *lists, const uint32_t *cin,
-                                uint32_t *cout, int all, Ctrl *ctrl, uint32_t round,
+                                uint32_t *cout, uint32_t *clear, Ctrl *ctrl, uint32_t round,
                                 int max_iters, int grid, hipStream_t s) {
-    return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round,
-                          max_iters, grid, s, -1, 0);
+    return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, cin, cout, 0, ctrl, round,
+                          max_iters, grid, s, -1, 0, clear);
 }
 
 hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
@@ -1893,7 +1936,7 @@ hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_t
     // stale more often), so uint8 rounds keep the lists.
     return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, ctrl->round_tiles[round],
                           ctrl->round_tiles[round + 1], round == 1 ? 1 : (tbytes == 4 ? 2 : 0), ctrl, round,
-                          max_iters, grid, s, variant, leave);
+                          max_iters, grid, s, variant, leave, nullptr);
 }
 
 template <typename T, int CONN, int V>

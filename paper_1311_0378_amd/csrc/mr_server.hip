@@ -121,6 +121,7 @@ struct Job {
     int band;
     uint32_t first_round;
     ImgDesc d;
+    bool fill_direct = false; // the epilogue writes the result itself
 };
 
 struct Returning {
@@ -139,7 +140,7 @@ struct mr_server {
     int32_t max_jobs = 0;
     int t = 1, conn = 8, max_sweeps = 16;
     hipStream_t stream = nullptr; // rounds and admissions
-    hipStream_t up = nullptr;     // input copies
+    hipStream_t up = nullptr;     // input copies (a step's rounds wait for all of them)
     hipStream_t down = nullptr;   // fill-holes epilogue, result copies
     int64_t n_tiles = 0;          // tile-id space
     // arena head
@@ -156,7 +157,10 @@ struct mr_server {
     std::map<int32_t, Job> resident;  // slot -> job still working
     std::deque<Returning> returning;  // finished, result copy in flight
     std::deque<uint64_t> done;        // result copy complete, not yet polled
-    std::vector<hipEvent_t> ev_in, ev_out; // per slot
+    std::vector<int32_t> admitted;    // slots whose jobs the next step puts on the lists
+    bool copies = false;              // input copies enqueued since the last step
+    hipEvent_t ev_in = nullptr;       // the input copies before a step
+    std::vector<hipEvent_t> ev_out;   // per slot
     hipEvent_t ev_round[2] = {nullptr, nullptr};
     uint32_t *h_busy = nullptr; // pinned, [2][max_jobs]: busy after the last step of each parity
     uint32_t round = 1;         // the round the next step launches first
@@ -254,8 +258,7 @@ int collect(mr_server *s, bool wait) {
 // already waited for the streams (or never used them), where a failed destroy
 // can only leak a handle and has nobody to report to.
 void destroy_handles(mr_server *s) {
-    for (hipEvent_t e : s->ev_in)
-        if (e) (void)hipEventDestroy(e);
+    if (s->ev_in) (void)hipEventDestroy(s->ev_in);
     for (hipEvent_t e : s->ev_out)
         if (e) (void)hipEventDestroy(e);
     for (hipEvent_t e : s->ev_round)
@@ -318,7 +321,6 @@ int mr_server_create(void *arena, size_t arena_bytes, int32_t max_jobs, mr_dtype
     s->mem.init(arena_bytes - o, 256);
     s->tiles.init((size_t)nt, 1);
     for (int32_t i = max_jobs - 1; i >= 0; --i) s->free_slots.push_back(i);
-    s->ev_in.assign(max_jobs, nullptr);
     s->ev_out.assign(max_jobs, nullptr);
     hipError_t e = hipHostMalloc((void **)&s->h_busy, sizeof(uint32_t) * 2 * max_jobs,
                                  hipHostMallocDefault);
@@ -326,9 +328,9 @@ int mr_server_create(void *arena, size_t arena_bytes, int32_t max_jobs, mr_dtype
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&s->down, hipStreamNonBlocking);
     for (int i = 0; i < 2 && e == hipSuccess; ++i)
         e = hipEventCreateWithFlags(&s->ev_round[i], hipEventDisableTiming);
+    if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_in, hipEventDisableTiming);
     for (int32_t i = 0; i < max_jobs && e == hipSuccess; ++i) {
-        e = hipEventCreateWithFlags(&s->ev_in[i], hipEventDisableTiming);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&s->ev_out[i], hipEventDisableTiming);
+        e = hipEventCreateWithFlags(&s->ev_out[i], hipEventDisableTiming);
     }
     if (e == hipSuccess) e = launch_clear_ctrl(s->ctrl, 0, s->stream);
     if (e == hipSuccess) e = launch_clear_u32(s->counts, RING * NBANDS, 0u, s->stream);
@@ -374,14 +376,25 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
 
     char *p0 = s->arena + s->data_off + mo, *p1 = p0 + j.plane;
     const size_t row = (size_t)job->W * s->t, dp = (size_t)j.pitch * s->t;
-    const size_t hp = (size_t)(job->ld ? job->ld : job->W) * s->t;
-    const hipMemcpyKind in_kind =
-        (job->flags & MR_JOB_DEVICE) ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-    hipError_t e = hipMemcpy2DAsync(p0, dp, job->data, hp, row, (size_t)job->H, in_kind, s->up);
-    if (e == hipSuccess && job->op == MR_OP_RECON)
-        e = hipMemcpy2DAsync(p1, dp, job->mask, hp, row, (size_t)job->H, in_kind, s->up);
-    if (e == hipSuccess) e = hipEventRecord(s->ev_in[j.slot], s->up);
-    if (e == hipSuccess) e = hipStreamWaitEvent(s->stream, s->ev_in[j.slot], 0);
+    const int64_t ld = job->ld ? job->ld : job->W;
+    const size_t hp = (size_t)ld * s->t;
+    const bool device = (job->flags & MR_JOB_DEVICE) != 0;
+    // A device job's image that is only read (the mask, or the image to fill) is
+    // read where it is, and a filled image goes straight to its result; planes
+    // beyond the tile loads' 32-bit offsets are copied into the arena like a host
+    // job's.
+    const bool direct =
+        device && (uint64_t)((job->H - 1) * ld + job->W) + 64 <= STAGE_MAX_BYTES &&
+        (uintptr_t)(job->op == MR_OP_RECON ? job->mask : job->data) % s->t == 0;
+    const hipMemcpyKind in_kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+    hipError_t e = hipSuccess;
+    auto copy_in = [&](char *dst, const void *src) {
+        if (e != hipSuccess) return;
+        e = hipMemcpy2DAsync(dst, dp, src, hp, row, (size_t)job->H, in_kind, s->up);
+        s->copies = true;
+    };
+    if (job->op == MR_OP_RECON || !direct) copy_in(p0, job->data);
+    if (job->op == MR_OP_RECON && !direct) copy_in(p1, job->mask);
     ImgDesc &d = j.d;
     d = ImgDesc{};
     d.H = job->H;
@@ -395,18 +408,17 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
     d.pJ = d.pI = j.pitch;
     if (job->op == MR_OP_RECON) {
         d.J = p0;
-        d.I = p1;
+        d.I = direct ? job->mask : p1;
         d.out = nullptr;
     } else {
-        d.I = p0;
-        d.out = p0;
+        d.I = direct ? job->data : p0;
         d.J = p1;
+        // (a result pointer that is not aligned to its pixels takes the copy)
+        j.fill_direct = device && (uintptr_t)job->result % s->t == 0;
+        d.out = j.fill_direct ? job->result : p0;
+        d.pO = j.fill_direct ? (job->ld_result ? job->ld_result : job->W) : j.pitch;
     }
-    const uint32_t r = s->round;
-    if (e == hipSuccess)
-        e = launch_server_admit(s->descs, j.slot, d, s->owner, s->flags,
-                                s->lists + (size_t)(r & 1) * s->n_tiles,
-                                s->counts + (r % RING) * NBANDS, s->n_tiles, r, s->stream);
+    if (direct) d.pI = ld;
     if (e != hipSuccess) {
         // the slot is not handed out: a failed enqueue leaves the streams in
         // an unknown state, and the error is reported
@@ -415,6 +427,7 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
         s->band_tiles[j.band] -= j.n_tiles;
         return hip_err(e, "admit");
     }
+    s->admitted.push_back(j.slot);
     s->free_slots.pop_back();
     ++s->next_id;
     s->resident[j.slot] = j;
@@ -426,10 +439,29 @@ int mr_server_step(mr_server *s) {
     clear_error();
     if (!s) return sfail(MR_EINVAL, "null server");
     hipError_t e;
-    // (a job's planes lie in the arena; one too large to stage is found below)
     Imgs imgs{s->descs, s->max_jobs, s->owner, s->t == MR_U8 ? 1 : 0, 0};
-    for (const auto &r : s->resident)
+    for (const auto &r : s->resident) // (planes the staged loads do not reach)
         if ((uint64_t)r.second.plane > STAGE_MAX_BYTES) imgs.staged = 0;
+    // 0. put the jobs submitted since the last step on the next round's lists, and
+    //    let the rounds wait for their input copies
+    if (s->copies) {
+        if ((e = hipEventRecord(s->ev_in, s->up)) != hipSuccess ||
+            (e = hipStreamWaitEvent(s->stream, s->ev_in, 0)) != hipSuccess)
+            return hip_err(e, "input event");
+        s->copies = false;
+    }
+    for (size_t i = 0; i < s->admitted.size(); i += DESC_CHUNK) {
+        const int n = (int)std::min<size_t>(DESC_CHUNK, s->admitted.size() - i);
+        ImgDesc d[DESC_CHUNK];
+        for (int k = 0; k < n; ++k) d[k] = s->resident[s->admitted[i + k]].d;
+        const uint32_t r = s->round;
+        if ((e = launch_server_admit(s->descs, &s->admitted[i], d, n, s->owner, s->flags,
+                                     s->lists + (size_t)(r & 1) * s->n_tiles,
+                                     s->counts + (r % RING) * NBANDS, s->n_tiles, r, s->stream)) !=
+            hipSuccess)
+            return hip_err(e, "admit");
+    }
+    s->admitted.clear();
     // 1. launch the step's rounds over every resident job (including those
     //    admitted since the last step); the host does not wait for them here
     uint32_t launched = 0;
@@ -441,11 +473,12 @@ int mr_server_step(mr_server *s) {
             const uint32_t r = s->round;
             uint32_t *cin = s->counts + (r % RING) * NBANDS;
             cout = s->counts + ((r + 1) % RING) * NBANDS;
-            if ((e = launch_clear_u32(cout, NBANDS, 0u, s->stream)) != hipSuccess)
-                return hip_err(e, "clear");
+            // (the counters of round r + 2 were last read by round r - 1's status or by
+            // round r - 2: this round clears them)
             if ((e = launch_tile_round_ex(s->t, s->conn, imgs, s->n_tiles, s->flags, s->lists,
-                                          cin, cout, 0, s->ctrl, r, s->max_sweeps,
-                                          persistent_grid(), s->stream)) != hipSuccess)
+                                          cin, cout, s->counts + ((r + 2) % RING) * NBANDS, s->ctrl,
+                                          r, s->max_sweeps, persistent_grid(), s->stream)) !=
+                hipSuccess)
                 return hip_err(e, "tile round");
             s->round = r + 1;
             ++s->rounds_run;
@@ -489,13 +522,14 @@ int mr_server_step(mr_server *s) {
                     hipSuccess)
                 return hip_err(e, "fill output");
             const char *src = (const char *)(j.spec.op == MR_OP_RECON ? j.d.J : j.d.out);
+            const bool copy = !(j.spec.op == MR_OP_FILL && j.fill_direct);
             const size_t row = (size_t)j.spec.W * s->t, dp = (size_t)j.pitch * s->t;
             const size_t hp = (size_t)(j.spec.ld_result ? j.spec.ld_result : j.spec.W) * s->t;
             const hipMemcpyKind out_kind = (j.spec.flags & MR_JOB_DEVICE)
                                                ? hipMemcpyDeviceToDevice
                                                : hipMemcpyDeviceToHost;
-            if ((e = hipMemcpy2DAsync(j.spec.result, hp, src, dp, row, (size_t)j.spec.H,
-                                      out_kind, s->down)) != hipSuccess ||
+            if ((copy && (e = hipMemcpy2DAsync(j.spec.result, hp, src, dp, row, (size_t)j.spec.H,
+                                               out_kind, s->down)) != hipSuccess) ||
                 (e = hipEventRecord(s->ev_out[slot], s->down)) != hipSuccess)
                 return hip_err(e, "result copy");
             s->returning.push_back(
