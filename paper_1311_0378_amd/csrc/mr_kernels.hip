@@ -645,6 +645,11 @@ __device__ __forceinline__ void app_flush(Appender &a, int lane) {
 __device__ __forceinline__ void ring_put(Ctrl *ctrl, uint32_t *ring, uint64_t cap, uint32_t t,
                                          unsigned long long pos) {
     uint32_t *slot = ring + (pos & (cap - 1));
+    // (the first turn around the ring finds every slot as it was cleared)
+    if (pos < cap) {
+        __hip_atomic_store(slot, t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        return;
+    }
     // The capacity bound means the slot is already free; the wait is a guard,
     // capped so that a broken bound cannot hang the device. Past the cap the
     // entry is refused rather than written over another: its work is lost,
@@ -699,9 +704,18 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" 
 // wave gives up with Q_STOP. One lane per wave calls it.
 constexpr uint32_t Q_STOP = 0xFFFFFFFEu;
 
-__device__ __forceinline__ unsigned long long ring_ticket(Ctrl *ctrl) {
-    return __hip_atomic_fetch_add(&ctrl->q_head.v, 1ull, __ATOMIC_RELAXED,
-                                  __HIP_MEMORY_SCOPE_AGENT);
+// A wave's first ticket (later ones come with ring_retire); a workgroup draws those
+// of its waves together, as one counter takes 20 us for 2048 draws. Tickets are
+// drawn by workgroups that run, not dealt by number: an entry dealt to a wave that
+// finds no room on the chip (another stream's waves may hold it, waiting on
+// their own ring) would wait for good. Every thread of the workgroup calls it.
+__device__ __forceinline__ unsigned long long ring_tickets(Ctrl *ctrl, unsigned waves) {
+    __shared__ unsigned long long first;
+    if (threadIdx.x == 0)
+        first = __hip_atomic_fetch_add(&ctrl->q_head.v, (unsigned long long)waves,
+                                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    __syncthreads();
+    return first + (threadIdx.x >> 6);
 }
 
 __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
@@ -733,17 +747,19 @@ __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64
     return t;
 }
 
-// Retire one processed entry (the whole wave); the wave that retires the last one
-// writes a
-// stop entry for each of the launch's `waves` waves (each holds at most one
-// ticket past the last entry).
-__device__ __forceinline__ void ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
-                                            unsigned waves, int lane) {
-    unsigned long long left = 0, base = 0;
-    if (lane == 0)
-        left = __hip_atomic_fetch_add(&ctrl->pending.v, (unsigned long long)-1ll, __ATOMIC_RELAXED,
-                                      __HIP_MEMORY_SCOPE_AGENT);
-    if (__ballot(left == 1) == 0) return;
+// Retire one processed entry and draw the next ticket, in one instruction (the
+// whole wave; the ticket is lane 1's). The wave that retires the last entry
+// writes a stop entry for each of the launch's `waves` waves (each holds at most
+// one ticket past the last entry, this one's new ticket among them).
+__device__ __forceinline__ unsigned long long ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
+                                                          unsigned waves, int lane) {
+    unsigned long long got = 0, base = 0;
+    if (lane < 2)
+        got = __hip_atomic_fetch_add(lane == 0 ? &ctrl->pending.v : &ctrl->q_head.v,
+                                     lane == 0 ? (unsigned long long)-1ll : 1ull, __ATOMIC_RELAXED,
+                                     __HIP_MEMORY_SCOPE_AGENT);
+    const unsigned long long ticket = __shfl(got, 1);
+    if (__ballot(lane == 0 && got == 1) == 0) return ticket;
     if (lane == 0)
         base = __hip_atomic_fetch_add(&ctrl->q_tail.v, (unsigned long long)waves, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
@@ -752,6 +768,7 @@ __device__ __forceinline__ void ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t
     for (unsigned k = lane; k < waves; k += 64)
         __hip_atomic_store(ring + ((base + k) & (cap - 1)), Q_STOP, __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
+    return ticket;
 }
 
 // Tile queue: a tile's state is 0 (idle), 1 (queued), 2 (a wave visits it)
@@ -1244,11 +1261,10 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
 // `leave` of them; the rounds after it had nothing to visit).
 __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl, int64_t n_tiles,
                                   uint32_t round, uint32_t leave, uint32_t *__restrict__ state,
-                                  uint32_t *__restrict__ ring, uint64_t cap, uint32_t waves) {
+                                  uint32_t *__restrict__ ring, uint64_t cap) {
     __shared__ unsigned long long base;
     __shared__ uint32_t from;
     const int b = blockIdx.x;
-    if (b == 0 && threadIdx.x == 0) ctrl->q_head.v = waves; // (see the queue's first tickets)
     if (threadIdx.x == 0) {
         uint32_t r = 2;
         for (; r < round; ++r) {
@@ -1285,23 +1301,28 @@ __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl
 // Bound by the latency of a link, so a wave hands itself the first idle
 // neighbour it marks instead of queueing it: on the holes of a 4096 x 4096
 // tile, after 8 rounds, the queue takes 269 us (357 us with every neighbour
-// through the ring). What 2048 waves do one after the other is kept out of the
-// launch's start and end: tickets taken from the head one by one at the start
-// and stops written by one lane cost 70 us of each launch (that image's whole
-// call 419 -> 348 us).
+// through the ring). The whole launch ends when every wave has its stop: written
+// by one lane, 2048 stops took 50 us. A wave that retires a tile draws its next
+// ticket in the same instruction.
+
+// Waves per workgroup of the tile queue. int32 visits have no register to spare
+// for telling the waves of a workgroup apart (27 spills become 50, h-dome of a
+// 4096 x 4096 int32 tile 714 -> 767 us).
+template <typename T> constexpr int TQ_WAVES = sizeof(T) == 1 ? 4 : 1;
 
 template <typename T, int CONN, int V>
-__global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restrict__ ctrl,
+__global__ __launch_bounds__(64 * TQ_WAVES<T>, 2) void k_tile_queue(Imgs imgs, Ctrl *__restrict__ ctrl,
                                                       uint32_t *__restrict__ state,
                                                       uint32_t *__restrict__ ring, uint64_t cap,
                                                       int max_iters,
                                                       unsigned long long wait_us,
                                                       uint32_t round, uint32_t leave) {
-    __shared__ uint32_t tb[TS][TS + 1];
-    const int lane = threadIdx.x;
+    __shared__ uint32_t tbs[TQ_WAVES<T>][TS][TS + 1];
+    const int lane = threadIdx.x & 63;
+    uint32_t (*tb)[TS + 1] = tbs[TQ_WAVES<T> == 1 ? 0 : threadIdx.x >> 6];
     // The counts for the work counters: rounds launched, and the tiles of a
     // round left to the queue moved to where handed-over tiles stand.
-    if (blockIdx.x == 0 && lane < NBANDS) {
+    if (blockIdx.x == 0 && threadIdx.x < NBANDS) {
         if (lane == 0) ctrl->rounds = round - 1;
         for (uint32_t r = 2; r < round; ++r) {
             const uint32_t n = ctrl->round_tiles[r][lane];
@@ -1321,16 +1342,10 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
     if (__hip_atomic_load(&ctrl->pending.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
         return;
     uint32_t t = Q_EMPTY; // the tile this wave holds: its state is 2, it counts as pending
-    // the first tickets are the waves' numbers (the head starts past them)
-    unsigned long long ticket = blockIdx.x;
-    bool first_take = true;
+    unsigned long long ticket = ring_tickets(ctrl, TQ_WAVES<T>);
     while (true) {
         if (t == Q_EMPTY) {
-            if (lane == 0) {
-                if (!first_take) ticket = ring_ticket(ctrl);
-                t = ring_take(ctrl, ring, cap, ticket, wait_us);
-            }
-            first_take = false;
+            if (lane == 0) t = ring_take(ctrl, ring, cap, ticket, wait_us);
             t = (uint32_t)__builtin_amdgcn_readfirstlane(t); // (uniform: scalar descriptor loads)
             if (t == Q_STOP) break;
             // queued -> visited, performed before any pixel is read: a mark that
@@ -1402,11 +1417,11 @@ __global__ __launch_bounds__(64, 2) void k_tile_queue(Imgs imgs, Ctrl *__restric
         wait_vmem();
         ring_push(ctrl, ring, cap, push, lane);
         // one entry held before and, with a next tile, one held now
-        if (next == Q_EMPTY) ring_retire(ctrl, ring, cap, gridDim.x, lane);
+        if (next == Q_EMPTY) ticket = ring_retire(ctrl, ring, cap, gridDim.x * TQ_WAVES<T>, lane);
         t = next;
     }
     if (lane == 0 && visits)
-        atomicAdd(&ctrl->tiles[(blockIdx.x) & (NCNT - 1)], visits);
+        atomicAdd(&ctrl->tiles[(blockIdx.x * TQ_WAVES<T> + (threadIdx.x >> 6)) & (NCNT - 1)], visits);
 }
 
 // ------------------------------------------------------------------- seeds
@@ -1566,9 +1581,10 @@ __global__ __launch_bounds__(64 * QWAVES) void k_queue(Imgs imgs, Ctrl *__restri
     if (__hip_atomic_load(&ctrl->pending.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
         return;
 
+    unsigned long long ticket = ring_tickets(ctrl, QWAVES);
     while (true) {
         uint32_t t = Q_EMPTY;
-        if (lane == 0) t = ring_take(ctrl, ring, cap, ring_ticket(ctrl), wait_us);
+        if (lane == 0) t = ring_take(ctrl, ring, cap, ticket, wait_us);
         t = __shfl(t, 0);
         if (t == Q_STOP) break;
         const ImgDesc d = load_desc(imgs, t);
@@ -1632,7 +1648,7 @@ __global__ __launch_bounds__(64 * QWAVES) void k_queue(Imgs imgs, Ctrl *__restri
         }
         // everything this tile produced is pushed; retire the ring entry
         wait_vmem();
-        ring_retire(ctrl, ring, cap, gridDim.x * QWAVES, lane);
+        ticket = ring_retire(ctrl, ring, cap, gridDim.x * QWAVES, lane);
     }
     // fold the per-lane counters
     unsigned long long p = npush, r = retries;
@@ -1943,7 +1959,7 @@ template <typename T, int CONN, int V>
 static hipError_t tile_queue_v(const Imgs &imgs, Ctrl *ctrl, uint32_t *state, uint32_t *ring,
                                uint64_t cap, int max_iters, int grid, unsigned long long wait_us,
                                hipStream_t s, uint32_t round, uint32_t leave) {
-    hipLaunchKernelGGL((k_tile_queue<T, CONN, V>), dim3((unsigned)grid), dim3(64), 0, s, imgs,
+    hipLaunchKernelGGL((k_tile_queue<T, CONN, V>), dim3((unsigned)grid), dim3(64 * TQ_WAVES<T>), 0, s, imgs,
                        ctrl, state, ring, cap, max_iters, wait_us, round, leave);
     return hipGetLastError();
 }
@@ -1964,10 +1980,15 @@ hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_t
                              uint32_t leave) {
     if (!ctrl || round > (uint32_t)MAX_ROUNDS + 1 || grid < 1 || n_tiles < 1)
         return hipErrorInvalidValue;
-    // no more waves than tiles: a wave visits one tile at a time
-    grid = (int)std::min<int64_t>(std::min<int64_t>(grid, RING_SLACK), n_tiles);
+    // no more waves than tiles: a wave visits one tile at a time. uint8 launches
+    // hold half the chip's: their lists are short (see tail_leave), and waves
+    // without a tile only draw tickets and poll the ring (4096 x 4096 fill-holes
+    // 310 us with 1024 waves, 327 us with 2048, erosion 633 and 645 us).
+    if (tbytes == 1) grid = std::max(grid / 2, 1);
+    const int wg = tbytes == 1 ? TQ_WAVES<uint8_t> : TQ_WAVES<int32_t>;
+    grid = (int)((std::min<int64_t>(std::min<int64_t>(grid, RING_SLACK), n_tiles) + wg - 1) / wg);
     hipLaunchKernelGGL(k_tile_queue_seed, dim3(NBANDS), dim3(256), 0, s, lists, ctrl, n_tiles,
-                       round, leave, state, ring, cap, (uint32_t)grid);
+                       round, leave, state, ring, cap);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     if (tbytes == 1)
