@@ -85,7 +85,12 @@ template <typename T>
 hipError_t launch_not(T *a, const T *b, T *b_not, int64_t H, int64_t W, int64_t pitch,
                       hipStream_t s) {
     const auto al16 = [](const void *p) { return ((uintptr_t)p & 15) == 0; };
-    if ((pitch * (int64_t)sizeof(T)) % 16 == 0 && al16(a) && (!b || (al16(b) && al16(b_not)))) {
+    if (pitch == W) { // rows without gaps: one long row, whose pitch does not matter
+        W = H * W;
+        pitch = W;
+        H = 1;
+    }
+    if ((H == 1 || (pitch * (int64_t)sizeof(T)) % 16 == 0) && al16(a) && (!b || (al16(b) && al16(b_not)))) {
         const int64_t vecs = W * (int64_t)sizeof(T) / 16;
         if (vecs > 0) {
             const int64_t blocks = std::min<int64_t>((H * vecs + 255) / 256, 1 << 16);

@@ -34,6 +34,10 @@ struct ImgDesc {
     // pixel (row pitch W), so that a raise is one atomic maximum instead of a
     // compare-and-swap on the dword four pixels share; null: no such plane
     uint32_t *wide;
+    // Imgs.lowered: the marker is the mask lowered by h (saturating at the type's
+    // minimum), and *above is set if some pixel of the mask is above that minimum
+    uint32_t *above;
+    uint32_t h, pad;
 };
 
 // Bytes of a uint8 plane, from its base rounded down to 16, that tile loads
@@ -88,6 +92,9 @@ struct Imgs {
     int32_t staged;
     // 1 when the images have widened planes for the queue phase
     int32_t wide;
+    // 1 when the first round makes the working image from the mask alone
+    // (ImgDesc.h); J is then not read before it is written
+    int32_t lowered;
 };
 
 constexpr uint32_t Q_EMPTY = 0xFFFFFFFFu;
@@ -101,12 +108,20 @@ constexpr int64_t RING_SLACK = 8192;
 void clear_error();
 int set_error(int code, const char *msg);
 
+// Reconstruction of the mask lowered by h (keys saturate at 0) into J, whose
+// contents on entry do not matter; *above (device) gets 1 if some pixel of the
+// mask is above the type's minimum, else 0. Otherwise as mr_recon_dilate
+// (defined in mr_api.hip).
+int recon_lowered(void *J, const void *mask, int64_t H, int64_t W, int64_t pitch, int t, int conn,
+                  uint32_t h, uint32_t *above, void *ws, size_t ws_bytes, const mr_tune *tune,
+                  void *stream);
+
 // Host-side launchers (defined in mr_kernels.hip).
 hipError_t launch_clear_u32(uint32_t *p, int64_t n, uint32_t v, hipStream_t s);
 hipError_t launch_clear_ctrl(Ctrl *c, int64_t n_tiles, hipStream_t s);
 // Clears what a launch sequence starts from in one kernel: the control block,
 // flags[n_tiles], qflag[n_tiles] (0) and ring[ring_cap] (Q_EMPTY). Writes the
-// descriptor d to *desc as well, unless desc is null.
+// descriptor d to *desc as well, unless desc is null, and clears its *above.
 hipError_t launch_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_t *qflag,
                               uint32_t *ring, int64_t ring_cap, ImgDesc *desc, const ImgDesc &d,
                               hipStream_t s);

@@ -83,9 +83,12 @@ __device__ __forceinline__ ImgDesc desc_at(kptr<ImgDesc> d, int64_t k) {
     r.op = d[k].op;
     r.done = d[k].done;
     r.wide = d[k].wide;
+    r.above = d[k].above;
+    r.h = d[k].h;
+    r.pad = 0;
     return r;
 }
-static_assert(sizeof(ImgDesc) == 104, "desc_at copies every field of ImgDesc");
+static_assert(sizeof(ImgDesc) == 120, "desc_at copies every field of ImgDesc");
 
 // Descriptor of the image that owns `tile` (owner table, else binary search
 // on tile_base).
@@ -330,11 +333,32 @@ __device__ __forceinline__ void store_j(gptr<T> p, uint32_t off, T v) {
     else p[off] = v;
 }
 
+// Key k lowered by h, saturating at 0.
+__device__ __forceinline__ uint32_t lower(uint32_t k, uint32_t h) {
+    return __builtin_elementwise_sub_sat(k, h);
+}
+
+// How a visit starts; uniform, and constants in the kernels made for one kind.
+struct VisitKind {
+    bool fill, initial, lowered;
+};
+
+// A kernel's visit kind V: bit 0 initial, bit 1 fill-holes, bit 2 (with bit 0) a
+// marker lowered from the mask; V < 0: as the tile's image and round say (with
+// LOWERED for launches that may lower the mask: those of one uint8 image too
+// large to stage; the code for it costs mixed batches 10 % where it is not needed).
+template <int V, bool LOWERED>
+__device__ __forceinline__ VisitKind visit_kind(const Imgs &imgs, const ImgDesc &d, uint32_t round) {
+    if (V >= 0) return VisitKind{(bool)((V >> 1) & 1), (bool)(V & 1), (bool)((V >> 2) & 1)};
+    const bool initial = d.first_round == (int64_t)round;
+    return VisitKind{d.op == MR_OP_FILL, initial, LOWERED && initial && imgs.lowered};
+}
+
 // The register tile of one visit. `initial` builds the starting working image
 // (reconstruction: min(marker, mask); fill-holes: the complement on the image
-// border and the minimum inside) instead of reading it; `fill` reads the input
-// image and complements it into the mask. Both are uniform, and constants in
-// the kernels made for one kind of visit. Outside pixels become key 0 in
+// border and the minimum inside; `lowered`: the mask lowered by d.h) instead of
+// reading it; `fill` reads the input
+// image and complements it into the mask. Outside pixels become key 0 in
 // both planes, which keeps them at 0.
 // The halo is not frozen: a sweep may raise a halo pixel from its in-tile
 // neighbours. That is a true geodesic dilation step on real values, so every
@@ -357,8 +381,8 @@ __device__ __forceinline__ void store_j(gptr<T> p, uint32_t off, T v) {
 __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_t gx0, int lane,
                                            uint32_t (&J)[TS], uint32_t (&I)[TS],
                                            uint32_t (&IT)[TS], uint32_t &JL, uint32_t &JR,
-                                           const uint8_t *stage, bool &it_done, bool fill,
-                                           bool initial) {
+                                           const uint8_t *stage, bool &it_done, VisitKind kind) {
+    const bool fill = kind.fill, initial = kind.initial;
     const int64_t H = d.H, W = d.W;
     const int64_t gx = gx0 + lane;
     const bool xin = gx >= 0 && gx < W;
@@ -373,8 +397,9 @@ __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_
 #pragma unroll
         for (int r = 0; r < TS; ++r) {
             const uint32_t iv = stI[r * SROW + lane];
-            uint32_t jv = stJ[r * SROW + lane];
-            if (initial) jv = min(jv, iv);
+            uint32_t jv = kind.lowered ? 0u : stJ[r * SROW + lane];
+            if (kind.lowered) jv = lower(iv, d.h);
+            else if (initial) jv = min(jv, iv);
             J[r] = jv;
             I[r] = iv;
         }
@@ -386,7 +411,10 @@ __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_
         const uint8_t *rowJ = stJ + lane * SROW;
         JL = rowJ[0];
         JR = rowJ[TS - 1];
-        if (initial) {
+        if (kind.lowered) {
+            JL = lower(IT[0], d.h);
+            JR = lower(IT[TS - 1], d.h);
+        } else if (initial) {
             JL = min(JL, IT[0]);
             JR = min(JR, IT[TS - 1]);
         }
@@ -397,8 +425,10 @@ __device__ __forceinline__ void stage_read(const ImgDesc &d, int64_t gy0, int64_
             const int64_t gy = gy0 + r;
             const bool ok = xin && gy >= 0 && gy < H;
             const uint32_t iv = stI[r * SROW + lane];
-            uint32_t jv = stJ[r * SROW + lane];
-            if (initial)
+            uint32_t jv = kind.lowered ? 0u : stJ[r * SROW + lane];
+            if (kind.lowered)
+                jv = lower(iv, d.h);
+            else if (initial)
                 jv = fill ? ((xedge || gy == 0 || gy == H - 1) ? iv : 0u) : min(jv, iv);
             J[r] = ok ? jv : 0u;
             I[r] = ok ? iv : 0u;
@@ -411,13 +441,14 @@ template <typename T, bool COH = false>
 __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t t, int64_t gy0, int64_t gx0,
                                           int lane, uint32_t (&J)[TS], uint32_t (&I)[TS],
                                           uint32_t (&IT)[TS], uint32_t &JL, uint32_t &JR,
-                                          uint8_t *stage, bool &it_done, bool fill, bool initial) {
+                                          uint8_t *stage, bool &it_done, VisitKind kind) {
     using P = Pix<T>;
+    const bool fill = kind.fill, initial = kind.initial;
     if (sizeof(T) == 1 && stage_ok(d)) {
         const StageWords w = stage_fetch<true, COH ? CPOL_DEVICE : 0>(d, t, lane);
         stage_commit_words<true>(w, d, t, lane, stage, fill);
         wave_sync();
-        stage_read(d, gy0, gx0, lane, J, I, IT, JL, JR, stage, it_done, fill, initial);
+        stage_read(d, gy0, gx0, lane, J, I, IT, JL, JR, stage, it_done, kind);
         return;
     }
     const int64_t H = d.H, W = d.W;
@@ -435,8 +466,13 @@ __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t t, int64_t g
 #pragma unroll
         for (int r = 0; r < TS; ++r) {
             const uint32_t iv = P::key(Ip[oI]) ^ flip;
-            uint32_t jv = P::key(load_j<T, COH>(Jp, oJ));
-            if (initial) jv = min(jv, iv);
+            uint32_t jv;
+            if (kind.lowered) {
+                jv = lower(iv, d.h);
+            } else {
+                jv = P::key(load_j<T, COH>(Jp, oJ));
+                if (initial) jv = min(jv, iv);
+            }
             J[r] = jv;
             I[r] = iv;
             oI += (uint32_t)d.pI;
@@ -454,6 +490,8 @@ __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t t, int64_t g
         uint32_t jv;
         if (fill && initial) {
             jv = (xedge || yc == 0 || yc == (uint32_t)(H - 1)) ? iv : 0u;
+        } else if (kind.lowered) {
+            jv = lower(iv, d.h);
         } else {
             jv = P::key(load_j<T, COH>(Jp, yc * (uint32_t)d.pJ + xc));
             if (initial) jv = min(jv, iv);
@@ -868,12 +906,12 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
                                                  uint32_t *__restrict__ flags, Appender &app,
                                                  Ctrl *__restrict__ ctrl, uint32_t round,
                                                  int max_iters, uint32_t (*tb)[TS + 1],
-                                                 bool fill, bool initial,
-                                                 TailMarks *tm = nullptr,
+                                                 VisitKind kind, TailMarks *tm = nullptr,
                                                  const ImgDesc *dn = nullptr, int64_t tn = 0,
                                                  bool has_next = false) {
     StageWords pre{};
     using P = Pix<T>;
+    const bool initial = kind.initial;
     // nothing derived from the lane id is hoisted out of the caller's tile
     // loop: held across the sweeps, such values would be spilled, and their
     // reloads would wait behind the stores of the visit
@@ -887,10 +925,18 @@ __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, in
     bool it_done = false;
     if (PIPE) // the caller has written and synchronized the stage
         stage_read(d, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, (const uint8_t *)tb,
-                   it_done, fill, initial);
+                   it_done, kind);
     else
         load_tile<T, TAIL>(d, t, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, (uint8_t *)tb,
-                           it_done, fill, initial);
+                           it_done, kind);
+    if (kind.lowered) { // (outside pixels are key 0)
+        uint32_t any = 0;
+#pragma unroll
+        for (int r = 0; r < TS; ++r) any |= I[r];
+        if (__ballot(any != 0) != 0 && lane == 0 &&
+            __hip_atomic_load(d.above, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
+            atomicOr(d.above, 1u);
+    }
     if (!it_done) {
         // (before the mask transpose: fewer registers live)
         halo_cols(J, tb, lane, JL, JR);
@@ -1151,8 +1197,8 @@ __device__ __forceinline__ int64_t cursor_next(TileCursor &c, const RoundWork &w
 // band's dirty list (see round_work). Tiles are dealt to the band's blocks by
 // static interleave, so no block gets more than one tile above another. A
 // tile builds its image's initial working values in the image's first round.
-// V selects the visit: -1 dispatches per tile on the image's op and first
-// round (mixed batches, the server); otherwise (FILL << 1) | INITIAL for
+// V selects the visit (see visit_kind): -1 dispatches per tile on the image's op
+// and first round (mixed batches, the server); otherwise for
 // launches whose tiles all take the same visit, which keeps the other three
 // variants' code, and their registers, out of the kernel.
 template <typename T, int CONN, int V>
@@ -1176,8 +1222,7 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
         const ImgDesc d = load_desc(imgs, t);
         if (!d.done)
             visit_tile<T, CONN>(d, t, lane, flags, app, ctrl, round, max_iters, tb,
-                                V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL,
-                                V >= 0 ? V & 1 : d.first_round == (int64_t)round);
+                                visit_kind<V, sizeof(T) == 1>(imgs, d, round));
         if (app.cnt > APP_CAP - 9) app_flush(app, lane);
     }
     app_flush(app, lane);
@@ -1206,7 +1251,7 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                                                          uint32_t leave,
                                                          uint32_t *__restrict__ counts_clear) {
     if (counts_clear && blockIdx.x == 0 && threadIdx.x < NBANDS) counts_clear[threadIdx.x] = 0;
-    constexpr bool needJ = V != 3;
+    constexpr bool needJ = V != 3 && V != 5;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer and load stage
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
@@ -1228,12 +1273,11 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
     if (t >= 0) {
         StageWords pre = stage_fetch<needJ>(d, t, lane);
         while (true) {
-            const bool fill = V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL;
-            const bool initial = V >= 0 ? V & 1 : d.first_round == (int64_t)round;
+            const VisitKind kind = visit_kind<V, false>(imgs, d, round);
             // the fetched rows of tile t go to the stage; the previous visit's
             // last reads of the transpose buffer are behind this sync
             wave_sync();
-            stage_commit_words<needJ>(pre, d, t, lane, stage, fill);
+            stage_commit_words<needJ>(pre, d, t, lane, stage, kind.fill);
             wave_sync();
             ImgDesc dn = d;
             int64_t tn = next(dn);
@@ -1243,8 +1287,8 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                 dn = d;
             }
             pre = visit_tile<uint8_t, CONN, false, true, needJ>(d, t, lane, flags, app, ctrl,
-                                                                round, max_iters, tb, fill,
-                                                                initial, nullptr, &dn, tn, has);
+                                                                round, max_iters, tb, kind,
+                                                                nullptr, &dn, tn, has);
             if (app.cnt > APP_CAP - 9) app_flush(app, lane);
             if (!has) break;
             t = tn;
@@ -1360,8 +1404,9 @@ __global__ __launch_bounds__(64 * TQ_WAVES<T>, 2) void k_tile_queue(Imgs imgs, C
         TailMarks tm;
         if (!d.done) {
             ++visits;
+            const bool fill = V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL;
             visit_tile<T, CONN, true>(d, t, lane, nullptr, app, ctrl, 0, max_iters, tb,
-                                      V >= 0 ? (V >> 1) & 1 : d.op == MR_OP_FILL, false, &tm);
+                                      VisitKind{fill, false, false}, &tm);
         }
         // the visits these marks lead to must see this visit's stores
         wait_vmem();
@@ -1440,8 +1485,8 @@ __device__ __forceinline__ void seed_tile(const ImgDesc &d, int64_t t, int lane,
     const int64_t gy0 = (int64_t)ty * TI - 1, gx = (int64_t)tx * TI - 1 + lane;
     uint32_t J[TS], I[TS], IT[TS], JL, JR;
     bool it_done = false;
-    load_tile<T>(d, t, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, stage, it_done, fill,
-                 false);
+    load_tile<T>(d, t, gy0, (int64_t)tx * TI - 1, lane, J, I, IT, JL, JR, stage, it_done,
+                 VisitKind{fill, false, false});
     uint64_t myrow = 0; // lane r ends up holding row r's bits
     uint32_t nseed = 0;
     gptr<T> Jw = (gptr<T>)d.J;
@@ -1688,7 +1733,10 @@ __global__ void k_clear_ctrl(Ctrl *c, int64_t n_tiles) {
 // descriptor.
 __global__ void k_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_t *qflag,
                               uint32_t *ring, int64_t ring_cap, ImgDesc *desc, ImgDesc d) {
-    if (desc && blockIdx.x == 0 && threadIdx.x == 0) *desc = d;
+    if (desc && blockIdx.x == 0 && threadIdx.x == 0) {
+        *desc = d;
+        if (d.above) *d.above = 0u;
+    }
     if (blockIdx.x == 0) {
         unsigned long long *p = (unsigned long long *)c;
         const int n = (int)(sizeof(Ctrl) / sizeof(unsigned long long));
@@ -1913,6 +1961,7 @@ static hipError_t tile_round_t(const Imgs &imgs, int64_t n_tiles, uint32_t *flag
     case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
     case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
     case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    case 5: return tile_round_v<T, CONN, 5>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
     default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
     }
 }
@@ -1943,7 +1992,8 @@ hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_t
                              int max_iters, int grid, hipStream_t s, int op_all, uint32_t leave) {
     // every image starts in round 1 here, so with one op for all of them the
     // visit is known for the whole launch
-    const int variant = op_all < 0 ? -1 : ((op_all == MR_OP_FILL ? 2 : 0) | (round == 1 ? 1 : 0));
+    const int variant = op_all < 0 ? -1 : ((op_all == MR_OP_FILL ? 2 : 0) | (round == 1 ? 1 : 0) |
+                                           (round == 1 && imgs.lowered ? 4 : 0));
     // Round 1 visits every tile. Later int32 rounds may walk dense bands
     // (the lists of a sequence that starts at round 1 allow it): their
     // visits are bound by memory traffic, which the walk's order lowers.

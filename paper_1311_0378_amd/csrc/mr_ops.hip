@@ -61,9 +61,9 @@ template <> struct K<int32_t> {
     __device__ static int32_t val(uint32_t k) { return (int32_t)(k ^ 0x80000000u); }
 };
 
-// The streaming passes of the wrappers, one kind each:
-//  P_MARKER: m = f - h, saturating at the type's minimum (in key space: key -
-//            h floored at 0); *above |= 1 if some pixel is above the minimum;
+// The streaming passes of the wrappers, one kind each (the marker f - h is made by
+// the reconstruction's first round, which finds out whether some pixel is above
+// the type's minimum, *above):
 //  P_DOME:   f <- f - r (the h-dome; r <= f everywhere, so 0 <= f - r <= h);
 //  P_RMAX:   out = 255 where f > r (a dome of height 1), or everywhere when
 //            no pixel is above the minimum (*above == 0); else 0.
@@ -72,7 +72,7 @@ template <> struct K<int32_t> {
 // 16 / sizeof(T)-byte pieces), else one pixel. A row's last word may be
 // partial and goes pixel by pixel. Grid-stride over a grid of at most
 // MAX_STREAM_BLOCKS blocks.
-enum { P_MARKER = 0, P_DOME = 1, P_RMAX = 2 };
+enum { P_DOME = 1, P_RMAX = 2 };
 constexpr int64_t MAX_STREAM_BLOCKS = 4096;
 
 template <typename T> struct alignas(16) Word {
@@ -80,13 +80,10 @@ template <typename T> struct alignas(16) Word {
 };
 
 template <typename T, int KIND>
-__device__ __forceinline__ void pass_pixel(const T *f, const T *r, T *m, uint8_t *o, uint32_t h,
-                                           bool all_min, bool &any, int64_t i, int64_t oi) {
+__device__ __forceinline__ void pass_pixel(const T *f, const T *r, T *m, uint8_t *o, bool all_min,
+                                           int64_t i, int64_t oi) {
     const uint32_t kf = K<T>::key(f[i]);
-    if (KIND == P_MARKER) {
-        any |= kf != 0;
-        m[i] = K<T>::val(kf > h ? kf - h : 0u);
-    } else if (KIND == P_DOME) {
+    if (KIND == P_DOME) {
         m[i] = (T)(int32_t)(kf - K<T>::key(r[i])); // m aliases f here
     } else {
         o[oi] = (all_min || kf > K<T>::key(r[i])) ? 255 : 0;
@@ -105,16 +102,15 @@ template <typename T, int KIND, bool WORDS>
 __global__ __launch_bounds__(256) void k_stream_pass(const T *f, const T *r, T *m,
                                                      uint8_t *__restrict__ o, int64_t H,
                                                      int64_t W, int64_t pitch, int64_t out_pitch,
-                                                     uint32_t h, uint32_t *above) {
+                                                     const uint32_t *above) {
     constexpr int EPW = WORDS ? 16 / (int)sizeof(T) : 1;
     const int64_t wpr = (W + EPW - 1) / EPW; // items per row
     const bool all_min = KIND == P_RMAX && *above == 0;
-    bool any = false;
     for (int64_t it = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; it < H * wpr;
          it += (int64_t)gridDim.x * blockDim.x) {
         const int64_t y = it / wpr, x0 = (it - y * wpr) * EPW;
         const int64_t i0 = y * pitch + x0, o0 = y * out_pitch + x0;
-        if (WORDS && sizeof(T) == 1 && KIND != P_MARKER && x0 + EPW <= W) {
+        if (WORDS && sizeof(T) == 1 && x0 + EPW <= W) {
             // uint8 dome and maxima on whole dwords: r <= f in every byte, so
             // f - r as 32-bit words subtracts byte by byte without borrows
             const uint4 wf = *(const uint4 *)(f + i0), wr = *(const uint4 *)(r + i0);
@@ -127,48 +123,25 @@ __global__ __launch_bounds__(256) void k_stream_pass(const T *f, const T *r, T *
                                                      bytes_nonzero(d.z), bytes_nonzero(d.w)};
             }
         } else if (WORDS && x0 + EPW <= W) {
-            const Word<T> wf = *(const Word<T> *)(f + i0);
-            if (KIND == P_MARKER) {
+            const Word<T> wf = *(const Word<T> *)(f + i0), wr = *(const Word<T> *)(r + i0);
+            if (KIND == P_DOME) {
                 Word<T> wm;
 #pragma unroll
-                for (int e = 0; e < EPW; ++e) {
-                    const uint32_t kf = K<T>::key(wf.e[e]);
-                    any |= kf != 0;
-                    wm.e[e] = K<T>::val(kf > h ? kf - h : 0u);
-                }
+                for (int e = 0; e < EPW; ++e)
+                    wm.e[e] = (T)(int32_t)(K<T>::key(wf.e[e]) - K<T>::key(wr.e[e]));
                 *(Word<T> *)(m + i0) = wm;
-            } else {
-                const Word<T> wr = *(const Word<T> *)(r + i0);
-                if (KIND == P_DOME) {
-                    Word<T> wm;
+            } else { // (uint8 words went the other way: four pixels here)
+                uint32_t v = 0;
 #pragma unroll
-                    for (int e = 0; e < EPW; ++e)
-                        wm.e[e] = (T)(int32_t)(K<T>::key(wf.e[e]) - K<T>::key(wr.e[e]));
-                    *(Word<T> *)(m + i0) = wm;
-                } else {
-                    uint8_t ob[EPW];
-#pragma unroll
-                    for (int e = 0; e < EPW; ++e)
-                        ob[e] = (all_min || K<T>::key(wf.e[e]) > K<T>::key(wr.e[e])) ? 255 : 0;
-                    if (EPW == 16) {
-                        *(Word<uint8_t> *)(o + o0) = *(const Word<uint8_t> *)ob;
-                    } else {
-                        uint32_t v = 0;
-#pragma unroll
-                        for (int e = 0; e < EPW; ++e) v |= (uint32_t)ob[e] << (8 * e);
-                        *(uint32_t *)(o + o0) = v;
-                    }
-                }
+                for (int e = 0; e < EPW; ++e)
+                    v |= (all_min || K<T>::key(wf.e[e]) > K<T>::key(wr.e[e]) ? 255u : 0u) << (8 * (e & 3));
+                *(uint32_t *)(o + o0) = v;
             }
         } else {
             for (int e = 0; e < EPW && x0 + e < W; ++e)
-                pass_pixel<T, KIND>(f, r, m, o, h, all_min, any, i0 + e, o0 + e);
+                pass_pixel<T, KIND>(f, r, m, o, all_min, i0 + e, o0 + e);
         }
     }
-    // one atomic per wave at most, and none once some wave has set the flag
-    if (KIND == P_MARKER && __ballot(any) != 0 && (threadIdx.x & 63) == 0 &&
-        __hip_atomic_load(above, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-        atomicOr(above, 1u);
 }
 
 bool words_ok(const void *p, int64_t pitch_bytes) {
@@ -177,28 +150,30 @@ bool words_ok(const void *p, int64_t pitch_bytes) {
 
 template <typename T, int KIND>
 hipError_t stream_pass(const T *f, const T *r, T *m, uint8_t *o, int64_t H, int64_t W,
-                       int64_t pitch, int64_t out_pitch, uint32_t h, uint32_t *above,
-                       hipStream_t s) {
-    const int64_t pb = pitch * (int64_t)sizeof(T);
-    bool words = words_ok(f, pb) && (KIND == P_MARKER || words_ok(r, pb)) &&
+                       int64_t pitch, int64_t out_pitch, const uint32_t *above, hipStream_t s) {
+    if (pitch == W && (KIND != P_RMAX || out_pitch == W)) { // rows without gaps: one long row
+        W = pitch = out_pitch = H * W;
+        H = 1;
+    }
+    // (a single row's pitch does not matter)
+    const int64_t pb = H == 1 ? 0 : pitch * (int64_t)sizeof(T);
+    bool words = words_ok(f, pb) && words_ok(r, pb) &&
                  (KIND == P_RMAX || words_ok(m, pb));
     if (KIND == P_RMAX)
         words = words && ((uintptr_t)o % (16 / sizeof(T))) == 0 &&
-                out_pitch % (int64_t)(16 / sizeof(T)) == 0;
+                (H == 1 || out_pitch % (int64_t)(16 / sizeof(T)) == 0);
     const int64_t epw = words ? 16 / (int64_t)sizeof(T) : 1;
     const int64_t items = H * ((W + epw - 1) / epw);
     const unsigned g =
         (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, MAX_STREAM_BLOCKS));
     if (words)
         hipLaunchKernelGGL((k_stream_pass<T, KIND, true>), dim3(g), dim3(256), 0, s, f, r, m, o,
-                           H, W, pitch, out_pitch, h, above);
+                           H, W, pitch, out_pitch, above);
     else
         hipLaunchKernelGGL((k_stream_pass<T, KIND, false>), dim3(g), dim3(256), 0, s, f, r, m, o,
-                           H, W, pitch, out_pitch, h, above);
+                           H, W, pitch, out_pitch, above);
     return hipGetLastError();
 }
-
-__global__ void k_zero_u32(uint32_t *p) { *p = 0u; }
 
 struct HdomeLayout {
     size_t recon = 0, plane = 0, flag = 0, total = 0;
@@ -232,16 +207,6 @@ int hdome_common(const void *img, int64_t H, int64_t W, int64_t &pitch, int t, i
     return MR_OK;
 }
 
-template <typename T>
-hipError_t hdome_marker(const void *f, void *m, int64_t H, int64_t W, int64_t pitch, uint32_t h,
-                        uint32_t *flag, hipStream_t s) {
-    hipLaunchKernelGGL(k_zero_u32, dim3(1), dim3(1), 0, s, flag);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    return stream_pass<T, P_MARKER>((const T *)f, nullptr, (T *)m, nullptr, H, W, pitch, 0, h,
-                                    flag, s);
-}
-
 // ------------------------------------------------------------------ RGB2Gray
 
 // BT.601 luma weights in 14-bit fixed point (0.299, 0.587, 0.114; sum 2^14)
@@ -253,10 +218,17 @@ __device__ __forceinline__ uint32_t luma(uint32_t r, uint32_t g, uint32_t b) {
 
 // 16 pixels per lane from three 16-byte words (48 bytes = 16 RGB triples),
 // one 16-byte word out. Rows and both planes are 16-byte aligned; vec = the
-// whole 16-pixel groups per row.
+// whole 16-pixel groups per row. The `rest` pixels past the last row's groups
+// (of a plane without gaps, one long row) go one a lane.
 __global__ __launch_bounds__(256) void k_rgb2gray16(const uint8_t *__restrict__ rgb,
                                                     int64_t rgb_pitch, uint8_t *__restrict__ gray,
-                                                    int64_t gray_pitch, int64_t H, int64_t vec) {
+                                                    int64_t gray_pitch, int64_t H, int64_t vec,
+                                                    int rest) {
+    if (blockIdx.x == 0 && (int)threadIdx.x < rest) {
+        const int64_t x = vec * 16 + threadIdx.x;
+        const uint8_t *p = rgb + (H - 1) * rgb_pitch + 3 * x;
+        gray[(H - 1) * gray_pitch + x] = (uint8_t)luma(p[0], p[1], p[2]);
+    }
     const int64_t items = H * vec;
     for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < items;
          i += (int64_t)gridDim.x * 256) {
@@ -609,17 +581,14 @@ int mr_hdome(void *img_inout, int64_t H, int64_t W, int64_t pitch, mr_dtype t, i
     char *w = (char *)ws;
     void *marker = w + L.plane;
     uint32_t *flag = (uint32_t *)(w + L.flag);
-    hipError_t e = (int)t == MR_U8
-        ? hdome_marker<uint8_t>(img_inout, marker, H, W, pitch, hk, flag, s)
-        : hdome_marker<int32_t>(img_inout, marker, H, W, pitch, hk, flag, s);
-    if (e != hipSuccess) return ohip(e, "h-dome marker");
-    rc = mr_recon_dilate(marker, img_inout, H, W, pitch, t, conn, ws, L.recon, tune, stream);
+    rc = recon_lowered(marker, img_inout, H, W, pitch, (int)t, conn, hk, flag, ws, L.recon, tune,
+                       stream);
     if (rc != MR_OK) return rc;
-    e = (int)t == MR_U8
+    const hipError_t e = (int)t == MR_U8
         ? stream_pass<uint8_t, P_DOME>((const uint8_t *)img_inout, (const uint8_t *)marker,
-                                       (uint8_t *)img_inout, nullptr, H, W, pitch, 0, 0u, flag, s)
+                                       (uint8_t *)img_inout, nullptr, H, W, pitch, 0, flag, s)
         : stream_pass<int32_t, P_DOME>((const int32_t *)img_inout, (const int32_t *)marker,
-                                       (int32_t *)img_inout, nullptr, H, W, pitch, 0, 0u, flag, s);
+                                       (int32_t *)img_inout, nullptr, H, W, pitch, 0, flag, s);
     return e == hipSuccess ? MR_OK : ohip(e, "h-dome output");
 }
 
@@ -636,17 +605,13 @@ int mr_regional_maxima(const void *img, void *out_u8, int64_t H, int64_t W, int6
     char *w = (char *)ws;
     void *marker = w + L.plane;
     uint32_t *flag = (uint32_t *)(w + L.flag);
-    hipError_t e = (int)t == MR_U8
-        ? hdome_marker<uint8_t>(img, marker, H, W, pitch, 1u, flag, s)
-        : hdome_marker<int32_t>(img, marker, H, W, pitch, 1u, flag, s);
-    if (e != hipSuccess) return ohip(e, "regional maxima marker");
-    rc = mr_recon_dilate(marker, img, H, W, pitch, t, conn, ws, L.recon, tune, stream);
+    rc = recon_lowered(marker, img, H, W, pitch, (int)t, conn, 1u, flag, ws, L.recon, tune, stream);
     if (rc != MR_OK) return rc;
-    e = (int)t == MR_U8
+    const hipError_t e = (int)t == MR_U8
         ? stream_pass<uint8_t, P_RMAX>((const uint8_t *)img, (const uint8_t *)marker, nullptr,
-                                       (uint8_t *)out_u8, H, W, pitch, out_pitch, 0u, flag, s)
+                                       (uint8_t *)out_u8, H, W, pitch, out_pitch, flag, s)
         : stream_pass<int32_t, P_RMAX>((const int32_t *)img, (const int32_t *)marker, nullptr,
-                                       (uint8_t *)out_u8, H, W, pitch, out_pitch, 0u, flag, s);
+                                       (uint8_t *)out_u8, H, W, pitch, out_pitch, flag, s);
     return e == hipSuccess ? MR_OK : ohip(e, "regional maxima output");
 }
 
@@ -664,15 +629,20 @@ int mr_rgb2gray(const void *rgb, int64_t rgb_pitch, void *gray, int64_t gray_pit
     const uint8_t *src = (const uint8_t *)rgb;
     uint8_t *dst = (uint8_t *)gray;
     int64_t x0 = 0;
-    const bool al = ((uintptr_t)src % 16 == 0) && rgb_pitch % 16 == 0 &&
-                    ((uintptr_t)dst % 16 == 0) && gray_pitch % 16 == 0;
+    if (rgb_pitch == 3 * W && gray_pitch == W) { // rows without gaps: one long row
+        W = gray_pitch = H * W;
+        rgb_pitch = 3 * W;
+        H = 1;
+    }
+    const bool al = (uintptr_t)src % 16 == 0 && (uintptr_t)dst % 16 == 0 &&
+                    (H == 1 || (rgb_pitch % 16 == 0 && gray_pitch % 16 == 0));
     if (al && W >= 16) {
         const int64_t vec = W / 16;
         hipLaunchKernelGGL(k_rgb2gray16, dim3(grid_for(H * vec, 256)), dim3(256), 0, s, src,
-                           rgb_pitch, dst, gray_pitch, H, vec);
+                           rgb_pitch, dst, gray_pitch, H, vec, H == 1 ? (int)(W - vec * 16) : 0);
         hipError_t e = hipGetLastError();
         if (e != hipSuccess) return ohip(e, "rgb2gray");
-        x0 = vec * 16;
+        x0 = H == 1 ? W : vec * 16;
     }
     if (x0 < W) {
         hipLaunchKernelGGL(k_rgb2gray1, dim3(grid_for(H * (W - x0), 256)), dim3(256), 0, s, src,

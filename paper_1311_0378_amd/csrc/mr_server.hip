@@ -439,7 +439,7 @@ int mr_server_step(mr_server *s) {
     clear_error();
     if (!s) return sfail(MR_EINVAL, "null server");
     hipError_t e;
-    Imgs imgs{s->descs, s->max_jobs, s->owner, s->t == MR_U8 ? 1 : 0, 0};
+    Imgs imgs{s->descs, s->max_jobs, s->owner, s->t == MR_U8 ? 1 : 0, 0, 0};
     for (const auto &r : s->resident) // (planes the staged loads do not reach)
         if ((uint64_t)r.second.plane > STAGE_MAX_BYTES) imgs.staged = 0;
     // 0. put the jobs submitted since the last step on the next round's lists, and

@@ -329,3 +329,25 @@ def test_disk_row_forms(shape, pad):
     check(ops.disk13(0, d).cpu().numpy(), oracle.erode_disk13(img), "erode: ")
     check(ops.disk13(1, d).cpu().numpy(), oracle.dilate_disk13(img), "dilate: ")
     check(ops.open_disk13(d).cpu().numpy(), oracle.open_disk13(img), "open: ")
+
+
+# Rows without gaps are streamed as one long row (odd widths, lengths that end in
+# part of a word); h-dome and regional maxima make their marker in the first tile
+# round: tiles at the image's edges, lowered below the minimum, one pixel above it.
+@pytest.mark.parametrize("shape", [(1, 15), (3, 5), (61, 63), (64, 130), (77, 201)])
+@pytest.mark.parametrize("dt", [np.uint8, np.int32])
+def test_gapless_rows_and_lowered_marker(shape, dt):
+    rng = np.random.default_rng(shape[1])
+    low = 0 if dt == np.uint8 else np.iinfo(np.int32).min
+    f = (rng.integers(0, 60, shape) + low).astype(dt)
+    spike = np.full(shape, low, dt)
+    spike[-1, -1] = low + 1
+    for img in (f, spike, np.full(shape, low, dt)):
+        for pad in (0, 3):
+            d = to_dev(img, pad)
+            check(ops.regional_maxima(d, 8).cpu().numpy(), oracle.regional_maxima(img, 8))
+            for h in (1, 20):
+                d = to_dev(img, pad)
+                check(ops.hdome(d, h, 4).cpu().numpy(), oracle.hdome(img, h, 4), f"h={h}: ")
+    rgb = rng.integers(0, 256, (*shape, 3)).astype(np.uint8)
+    check(ops.rgb2gray(torch.from_numpy(rgb).to(DEV)).cpu().numpy(), oracle.rgb2gray(rgb))
