@@ -65,6 +65,11 @@ typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
 constexpr int CT = 64;              // tile side: a row is one 64-bit mask, lane = row
 constexpr int CT_RUNS = CT / 2;     // a row holds at most this many runs
 constexpr int CT_WAVES = 4;         // tiles (waves) per workgroup
+// Fewer tiles than this: a workgroup each, so that every CU gets one, and the
+// last pass takes CT_WAVES waves a tile. 2048 x 2048 (1024 tiles), label and area
+// threshold: 36.1 us so, 38.4 us with four tiles a workgroup; 4096 x 2048 the same
+// (46.1 us); 16384 x 16384 (65536 tiles) 742 us so, 695 us with four.
+constexpr uint32_t CT_FEW = 2048;
 
 // ------------------------------------------------------------- local phase
 
@@ -161,10 +166,14 @@ struct CclTile {
 // whose left neighbour is not common; with 8-connectivity a run's first pixel
 // takes the run above it or above-left of it, and every later pixel only the
 // run that begins above-right of it.
-// Bound by the image read: 16384 x 16384 uint8 with 1.6 % foreground takes 85 us
-// (3.2 TB/s of image). Per-pixel lanes on 32 x 64 tiles that loaded one byte a
+// A run's first union takes no atomic: the run is put below the run above it,
+// and the chains that this makes down the tile's rows are halved three times
+// before they are walked (512 x 3712 pixels, 20 % foreground: 7.0 us, 15.8 us
+// with every union by walk and atomic minimum).
+// Bound by the image read: 16384 x 16384 uint8 with 1.6 % foreground takes 78 us
+// (3.4 TB/s of image). Per-pixel lanes on 32 x 64 tiles that loaded one byte a
 // lane and stored every pixel's forest entry took 533 us.
-template <int CONN>
+template <int CONN, int CT_WAVES>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__restrict__ img,
                                                              uint32_t H, uint32_t W, int64_t pitch,
                                                              uint32_t tiles_x, uint32_t n_tiles,
@@ -232,32 +241,62 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
         *T.word(labels, lpitch, j) = T.nw == 2 ? half[j] : half[2 * j];
     }
     if (__ballot(m != 0) == 0) return;
-#pragma unroll
-    for (int k = 0; k < CT * CT_RUNS / 256; ++k) {
-        const uint32_t i = 256 * k + 4 * lane;
-        *(uint4 *)(P + i) = uint4{i, i + 1, i + 2, i + 3};
-    }
     const uint64_t up = lane > 0 ? row_of[lane - 1] : 0ull;
     const uint64_t s = m & ~(m << 1); // the runs' first pixels
-    ccl_wave_sync();
+    // Columns at which a run makes a union: with the run above at the column
+    // itself (uC), or above-left (uL) or above-right (uR) of it.
+    uint64_t uC, uL = 0, uR = 0;
     if (CONN == 4) {
-        const uint64_t c = m & up;
-        for (uint64_t u = c & ~(c << 1); u; u &= u - 1) {
-            const int x = __builtin_ctzll(u);
-            lunion(P, run_node(lane, m, x), run_node(lane - 1, up, x));
-        }
+        uC = m & up;
+        uC &= ~(uC << 1);
     } else {
-        // an above-left run is reached at column x - 1, an above-right one at
-        // x + 1; a run's first pixel takes the above-left run before the one above
-        const uint64_t uL = s & (up << 1), uC = s & up & ~(up << 1), uR = m & (up >> 1) & ~up;
-        for (uint64_t u = uL | uC; u; u &= u - 1) {
-            const int x = __builtin_ctzll(u);
-            lunion(P, run_node(lane, m, x),
-                   run_node(lane - 1, up, ((uC >> x) & 1) ? x : x - 1));
+        uL = s & (up << 1);
+        uC = s & up & ~(up << 1);
+        uR = m & (up >> 1) & ~up;
+    }
+    // the node of the run above that column x unites with (first: at x itself or
+    // to its left, else to its right)
+    auto above = [&](int x, bool right) -> uint32_t {
+        return run_node(lane - 1, up, right ? x + 1 : ((uL >> x) & 1) ? x - 1 : x);
+    };
+    // A run starts below the first run it unites with, which takes no atomic; the
+    // chains this makes down the rows are halved three times before anyone
+    // walks them; what a run touches besides is united then.
+    uint64_t left = uC | uL, right = uR;
+    for (uint64_t u = s; u; u &= u - 1) {
+        const int x = __builtin_ctzll(u);
+        const uint32_t node = (uint32_t)(lane * CT_RUNS + (x >> 1));
+        // this run's columns
+        const uint64_t gap = ~m & ~((2ull << x) - 1);
+        const uint64_t run = (gap ? (gap & -gap) - 1 : ~0ull) & ~((1ull << x) - 1);
+        const uint64_t l = left & run, r = right & run;
+        uint32_t parent = node;
+        if (l) {
+            parent = above(__builtin_ctzll(l), false);
+            left &= ~(l & -l);
+        } else if (r) {
+            parent = above(__builtin_ctzll(r), true);
+            right &= ~(r & -r);
         }
-        for (uint64_t u = uR; u; u &= u - 1) {
+        P[node] = parent;
+    }
+    ccl_wave_sync();
+#pragma unroll 1
+    for (int k = 0; k < 3; ++k) {
+        for (uint64_t u = s; u; u &= u - 1) {
+            const uint32_t node = (uint32_t)(lane * CT_RUNS + (__builtin_ctzll(u) >> 1));
+            P[node] = P[P[node]];
+        }
+        ccl_wave_sync();
+    }
+    if (__ballot((left | right) != 0)) {
+        for (uint64_t u = left; u; u &= u - 1) {
             const int x = __builtin_ctzll(u);
-            lunion(P, run_node(lane, m, x), run_node(lane - 1, up, x + 1));
+            lunion(P, run_node(lane, m, x), above(x, false));
+        }
+        for (uint64_t u = right; u; u &= u - 1) {
+            const int x = __builtin_ctzll(u);
+            lunion(P, run_node(lane, m, x), above(x, true));
         }
     }
     ccl_wave_sync();
@@ -333,7 +372,7 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_
                                                              uint32_t *labels, int64_t lpitch,
                                                              uint32_t *__restrict__ F) {
     const int lane = threadIdx.x & 63;
-    const uint32_t t = blockIdx.x * CT_WAVES + (threadIdx.x >> 6);
+    const uint32_t t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
     if (t >= n_tiles) return;
     const CclTile T(t, tiles_x, H, W);
     const uint32_t tx = T.x0 / CT;
@@ -391,21 +430,26 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_
 // written and took 242 us). The stores are streaming: the plane is four times
 // the last-level cache, and the call is 3 % faster than with cached ones.
 // Two or eight tiles a workgroup instead of four: 3 to 4 % slower calls.
+// With few tiles (CT_FEW) a tile is split over the workgroup's waves, ROWS rows
+// each: 512 x 3712 pixels 6.3 us instead of 8.3 us.
+template <int ROWS>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_t W,
                                                              uint32_t tiles_x, uint32_t n_tiles,
                                                              uint32_t *labels, int64_t lpitch,
                                                              const uint32_t *__restrict__ F) {
-    __shared__ uint32_t lists[CT_WAVES][CT * CT_RUNS];
-    __shared__ uint64_t rows[CT_WAVES][CT];
-    __shared__ uint32_t bases[CT_WAVES][CT]; // runs in the rows above
+    __shared__ uint32_t lists[CT_WAVES][ROWS * CT_RUNS];
+    __shared__ uint64_t rows[CT_WAVES][ROWS];
+    __shared__ uint32_t bases[CT_WAVES][ROWS]; // runs in the rows above
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t t = blockIdx.x * CT_WAVES + wv;
+    const uint32_t t = ROWS == CT ? blockIdx.x * CT_WAVES + wv : blockIdx.x;
+    const uint32_t r0 = ROWS == CT ? 0u : wv * ROWS; // this wave's rows of the tile
     if (t >= n_tiles) return;
     const CclTile T(t, tiles_x, H, W);
     uint32_t *list = lists[wv];
     uint64_t *row_of = rows[wv];
     uint32_t *base_of = bases[wv];
-    const uint64_t m = (uint32_t)lane < T.h ? T.mask(labels, lpitch, lane) : 0ull;
+    const bool in = lane < ROWS && r0 + lane < T.h;
+    const uint64_t m = in ? T.mask(labels, lpitch, r0 + lane) : 0ull;
     const bool any = __ballot(m != 0) != 0;
     if (any) {
         const uint64_t s = m & ~(m << 1);
@@ -418,10 +462,12 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
         }
         const uint32_t total = __shfl(end, 63);
         uint32_t at = end - n;
-        row_of[lane] = m;
-        base_of[lane] = at;
+        if (lane < ROWS) {
+            row_of[lane] = m;
+            base_of[lane] = at;
+        }
         for (uint64_t u = s; u; u &= u - 1)
-            list[at++] = T.first + lane * W + (uint32_t)__builtin_ctzll(u);
+            list[at++] = T.first + (r0 + lane) * W + (uint32_t)__builtin_ctzll(u);
         ccl_wave_sync();
         for (uint32_t i = lane; i < total; i += 64) {
             // (the forest is at rest here: plain loads)
@@ -433,16 +479,17 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
             list[i] = e;
         }
     }
-    // (the masks have been read: the wave's loads are done before its stores)
+    // (the masks have been read: the tile's loads are done before its stores)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     ccl_wave_sync();
+    if (ROWS < CT) __syncthreads();
     auto label = [&](uint64_t rm, uint64_t rs, uint32_t base, int x) -> uint32_t {
         if (!((rm >> x) & 1)) return 0u;
         return list[base + (uint32_t)__popcll(rs & ((2ull << x) - 1)) - 1u];
     };
     const int c = 4 * (lane & 15);
 #pragma unroll 4
-    for (int j = 0; j < CT / 4; ++j) {
+    for (int j = 0; j < ROWS / 4; ++j) {
         const uint32_t r = 4 * j + (lane >> 4);
         v4u v = {0, 0, 0, 0};
         if (any) {
@@ -454,8 +501,8 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
                         label(rm, rs, b, c + 3)};
             }
         }
-        if (r >= T.h) continue;
-        uint32_t *o = labels + (int64_t)(T.y0 + r) * lpitch + T.x0 + c;
+        if (r0 + r >= T.h) continue;
+        uint32_t *o = labels + (int64_t)(T.y0 + r0 + r) * lpitch + T.x0 + c;
         if (c + 4 <= (int)T.w) {
             __builtin_nontemporal_store(v, (v4u_dw *)o);
         } else {
@@ -632,8 +679,8 @@ __global__ __launch_bounds__(256) void k_area_filter(int32_t *__restrict__ label
 // The word path of the filter: a word's 4 counter reads are in flight
 // together, and it is written back only if one of its labels was cleared. With
 // `marks` (see the count) a wave takes `group` chunks (64 of a large plane, fewer
-// of a small one, so that it still spreads over the chip: 1003 x 1021 labels
-// took 13 us in groups of 64), lists the words that hold a label in LDS and gives each lane one of them, so that planes of mostly
+// of a smaller one, so that it still spreads over the chip), lists the words that
+// hold a label in LDS and gives each lane one of them, so that planes of mostly
 // background are not read again; a wave whose words are mostly marked, and
 // planes without marks, go chunk by chunk. 16384 x 16384 labels, 1.6 % of
 // them foreground: 22 us with marks, 222 us reading every word.
@@ -752,17 +799,20 @@ int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,
     uint32_t *F = (uint32_t *)ws, *L = (uint32_t *)labels;
     const uint32_t h = (uint32_t)H, w = (uint32_t)W;
     const uint32_t tx = (w + CT - 1) / CT, tiles = tx * ((h + CT - 1) / CT);
-    const dim3 grid((tiles + CT_WAVES - 1) / CT_WAVES), block(64 * CT_WAVES);
-    if (conn == 8) {
-        hipLaunchKernelGGL(k_ccl_local<8>, grid, block, 0, s, (const uint8_t *)img, h, w, pitch, tx,
-                           tiles, L, label_pitch, F);
-        hipLaunchKernelGGL(k_ccl_merge<8>, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
-    } else {
-        hipLaunchKernelGGL(k_ccl_local<4>, grid, block, 0, s, (const uint8_t *)img, h, w, pitch, tx,
-                           tiles, L, label_pitch, F);
-        hipLaunchKernelGGL(k_ccl_merge<4>, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
-    }
-    hipLaunchKernelGGL(k_ccl_write, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
+    const bool few = tiles < CT_FEW;
+    const dim3 grid(few ? tiles : (tiles + CT_WAVES - 1) / CT_WAVES), wide(64 * CT_WAVES);
+    const dim3 block = few ? dim3(64) : wide;
+    auto launch = [&](auto local, auto merge, auto write) {
+        hipLaunchKernelGGL(local, grid, block, 0, s, (const uint8_t *)img, h, w, pitch, tx, tiles,
+                           L, label_pitch, F);
+        hipLaunchKernelGGL(merge, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
+        hipLaunchKernelGGL(write, grid, wide, 0, s, h, w, tx, tiles, L, label_pitch, F);
+    };
+    const auto write = few ? k_ccl_write<CT / CT_WAVES> : k_ccl_write<CT>;
+    if (conn == 8)
+        launch(few ? k_ccl_local<8, 1> : k_ccl_local<8, CT_WAVES>, k_ccl_merge<8>, write);
+    else
+        launch(few ? k_ccl_local<4, 1> : k_ccl_local<4, CT_WAVES>, k_ccl_merge<4>, write);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? MR_OK : chip(e, "ccl");
 }
@@ -792,13 +842,15 @@ int mr_area_threshold(void *labels_inout, int64_t H, int64_t W, int64_t pitch, i
     const bool lin = pitch == W;
     if (NQ > 0 && (lin || (W % 4 == 0 && pitch % 4 == 0)) && (uintptr_t)labels_inout % 16 == 0) {
         int32_t *l = (int32_t *)labels_inout;
-        uint64_t *marks = ws_bytes >= need + area_marks_bytes(H * W)
-                              ? (uint64_t *)((char *)ws + need) : nullptr;
         const uint32_t wq = (uint32_t)(W / 4), chunks = (NQ + 63) / 64;
+        // (small planes are filtered faster word by word: 512 x 3712 labels 3.9
+        // against 4.8 us)
+        uint64_t *marks = chunks >= 16384 && ws_bytes >= need + area_marks_bytes(H * W)
+                              ? (uint64_t *)((char *)ws + need) : nullptr;
         const unsigned gc = std::min<unsigned>((chunks + 4 * AREA_UNROLL - 1) / (4 * AREA_UNROLL),
                                                AREA_BLOCKS);
         // chunks a wave of the filter takes: 4 waves a SIMD before it grows
-        const uint32_t group = std::max(4u, std::min(64u, chunks / 4096 / 4 * 4));
+        const uint32_t group = std::max((uint32_t)AREA_UNROLL, std::min(64u, chunks / 4096 / 4 * 4));
         const unsigned gf = std::min<unsigned>((chunks + 4 * group - 1) / (4 * group), AREA_BLOCKS);
         if (lin) {
             hipLaunchKernelGGL(k_area_count4<true>, dim3(gc), dim3(256), 0, s, l, N, NQ, wq, pitch,

@@ -263,6 +263,21 @@ def test_ccl_tile_edges(shape, pad, lpad, conn):
         assert bool((out[:, W:] == -9).all())
 
 
+# Both sides of the labels' tile count line (2046 and 2048 tiles of 64 x 64) and
+# of the area filter's line for marks (16250 and 16640 chunks of 64 words).
+@pytest.mark.parametrize("H", [64000, 65472, 65536])
+@pytest.mark.parametrize("p", [0.05, 0.55])
+def test_label_size_lines(H, p):
+    img = (np.random.default_rng(H).random((H, 65)) < p).astype(np.uint8)
+    ref = oracle.ccl(img, 8)
+    lab = ops.ccl(to_dev(img), 8)
+    check(lab.cpu().numpy(), ref)
+    n = np.bincount(ref.ravel())
+    ref[(n[ref] < 2) | (n[ref] > 40)] = 0
+    ops.area_threshold(lab, 2, 40)
+    check(lab.cpu().numpy(), ref)
+
+
 # The area threshold's word path on gapless planes of any length (words past
 # the last whole one, chunks past the last whole 64 words) and with a workspace
 # that has no room for the marks; sparse and dense planes.
