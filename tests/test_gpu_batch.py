@@ -61,6 +61,29 @@ def test_batch_matches_oracle(dt, conn, tune):
         assert np.array_equal(got, want), f"image {i} ({job[0]} {got.shape}): " + first_mismatch(got, want)
 
 
+# Mixed images in place in one large plane, at any byte alignment.
+@pytest.mark.parametrize("conn", [4, 8])
+def test_batch_unaligned_windows(conn):
+    jobs = make_batch(19, seed=60 + conn, lo=1, hi=300)
+    big = torch.full((2, 400, 19 * 301), 5, dtype=torch.uint8, device=DEV)
+    items = []
+    for i, (kind, a, m) in enumerate(jobs):
+        H, W = a.shape
+        win = (slice(i, i + H), slice(301 * i, 301 * i + W))
+        big[0][win] = torch.from_numpy(a).to(DEV)
+        if m is not None:
+            big[1][win] = torch.from_numpy(m).to(DEV)
+        items.append((big[0][win], big[1][win] if m is not None else None,
+                      mrecon.MR_OP_RECON if kind == "recon" else mrecon.MR_OP_FILL))
+    print(f"[gpu] batch of {len(items)} windows conn{conn}", flush=True)
+    mrecon.batch(items, conn)
+    for i, (job, (d, _, _)) in enumerate(zip(jobs, items)):
+        got, want = d.cpu().numpy(), oracle_of(job, conn)
+        assert np.array_equal(got, want), f"image {i}: " + first_mismatch(got, want)
+        d.fill_(5)
+    assert bool((big[0] == 5).all())
+
+
 def test_batch_equals_single_calls():
     jobs = make_batch(12, "u8", seed=7)
     items = to_items(jobs)

@@ -20,7 +20,8 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():  # collected on CPU-only hosts too
     pytest.skip("no GPU", allow_module_level=True)
 
-from gpu_util import first_mismatch, gpu_fill, gpu_recon  # noqa: E402
+from gpu_util import DEV, first_mismatch, gpu_fill, gpu_recon  # noqa: E402
+from paper_1311_0378_amd import mrecon  # noqa: E402
 
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden")
 
@@ -143,6 +144,46 @@ def test_pitched_rows():
     img = synth.binary_from_mask(mask)
     wantf, _ = oracle.fill_holes(img, 8)
     check(gpu_fill(img, 8, pad=13), wantf)
+
+
+# Planes of any byte alignment take the staged loads; widths with whole and partial
+# tiles, and rows whose last staged words reach past the plane.
+@pytest.mark.parametrize("shape", [(1, 1), (3, 62), (64, 65), (63, 190), (130, 187)],
+                         ids=lambda s: f"{s[0]}x{s[1]}")
+@pytest.mark.parametrize("off,pad", [(1, 0), (2, 1), (3, 5), (7, 64), (13, 3)])
+def test_unaligned_planes(shape, off, pad):
+    H, W = shape
+    rng = np.random.default_rng(H + W + off)
+    mask, marker = rng.integers(0, 7, (2, H, W)).astype(np.uint8)
+
+    def window(a):
+        flat = torch.full((off + H * (W + pad) + 9,), 99, dtype=torch.uint8, device=DEV)
+        t = flat[off:off + H * (W + pad)].view(H, W + pad)[:, :W]
+        t.copy_(torch.from_numpy(a))
+        return flat, t
+
+    print(f"[gpu] unaligned {shape} off={off} pad={pad}", flush=True)
+    for conn in (4, 8):
+        for a, b, run, want in (
+                (marker, mask, mrecon.recon_dilate, oracle.recon_dilate(marker, mask, conn)[0]),
+                (mask, None, mrecon.fill_holes, oracle.fill_holes(mask, conn)[0])):
+            flat, t = window(a)
+            run(t, window(b)[1], conn) if b is not None else run(t, conn)
+            check(t.cpu().numpy(), want)
+            rest = flat.clone()
+            rest[off:off + H * (W + pad)].view(H, W + pad)[:, :W] = 99
+            assert bool((rest == 99).all())
+
+
+# Both sides of the line from which uint8 images get tile rounds after the first
+# (5120 tiles of 62 x 62), and single tiles.
+@pytest.mark.parametrize("shape", [(62, 62), (3968, 4960), (3968, 4961)],
+                         ids=lambda s: f"{s[0]}x{s[1]}")
+def test_tile_queue_takes_over(shape):
+    marker, mask = synth.make_tile(*shape, 4000, 11, "u8", 0.0)
+    got, c = gpu_recon(marker, mask, 8, counters=True)
+    check(got, oracle.recon_dilate(marker, mask, 8)[0])
+    assert c["tiles"] >= -(-shape[0] // 62) * -(-shape[1] // 62)
 
 
 def test_i32_full_range_fill():

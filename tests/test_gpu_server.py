@@ -128,6 +128,36 @@ def test_server_windows_of_a_larger_image():
     assert not out.numpy()[~mask].any() and not outf.numpy()[~mask].any()
 
 
+# More device jobs than one admission launch takes, all in one step: windows of one
+# plane at any byte alignment, read where they are, with the results over the inputs.
+def test_server_device_jobs_in_place():
+    jobs = make_batch(35, seed=71, lo=1, hi=300)
+    big = torch.full((2, 400, 35 * 301), 5, dtype=torch.uint8, device=DEV)
+    srv = mrecon.Server(256 << 20, max_jobs=40)
+    wins, ids = [], {}
+    for i, (kind, a, m) in enumerate(jobs):
+        win = (slice(i, i + a.shape[0]), slice(301 * i, 301 * i + a.shape[1]))
+        big[0][win] = torch.from_numpy(a).to(DEV)
+        if m is not None:
+            big[1][win] = torch.from_numpy(m).to(DEV)
+        wins.append(win)
+    torch.cuda.synchronize()
+    for i, (kind, a, m) in enumerate(jobs):
+        d, k = big[0][wins[i]], big[1][wins[i]] if m is not None else None
+        ids[srv.submit(d, k, out=d)] = i
+    assert None not in ids and len(ids) == len(jobs)
+    print("[gpu] server device jobs in place", flush=True)
+    srv.drain()
+    got = {ids[j]: res for j, res in srv.poll()}
+    for i, job in enumerate(jobs):
+        want = oracle_of(job, 8)
+        res = got[i].cpu().numpy()
+        assert np.array_equal(res, want), f"job {i}: " + first_mismatch(res, want)
+        got[i].fill_(5)
+    srv.close()
+    assert bool((big[0] == 5).all())
+
+
 @pytest.mark.parametrize("conn", [4, 8])
 def test_server_device_jobs(conn):
     # jobs whose inputs and results are device memory (MR_JOB_DEVICE): the
