@@ -354,6 +354,13 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
         hipSuccess)
         return hip_fail(e, "clear");
 
+    // A launch with no more tiles than the tile queue takes over anyway leaves every
+    // round after the first to it: those rounds would find nothing to do (with timing
+    // on they are launched, for their records). The first round then marks the tiles
+    // for the queue itself.
+    const uint32_t leave = tail_leave(tbytes);
+    const bool queue_next = tn.sweep_rounds <= 0 && tn.tail_rounds > 0 &&
+                            L.n_tiles <= (int64_t)leave && g_timing.on == MR_TIMING_OFF;
     uint32_t round = 1;
     RoundSpan span(s); // span-mode timing of consecutive rounds
     span.begin(round);
@@ -363,7 +370,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
         // nearly every tile is visited again in the second tile round.
         LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
         e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                              tn.first_sweeps, grid, s, op_all, 0);
+                              tn.first_sweeps, grid, s, op_all, 0, queue_next ? qflag : nullptr);
     }
     if (e != hipSuccess) return hip_fail(e, "tile round");
     span.add();
@@ -404,7 +411,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
             {
                 LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                 e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                                      tn.max_sweeps, grid, s, op_all, 0);
+                                      tn.max_sweeps, grid, s, op_all, 0, nullptr);
             }
             if (e != hipSuccess) return hip_fail(e, "tile round");
             span.add();
@@ -419,17 +426,12 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
         // converge mode with the tile queue: a fixed number of rounds, then
         // the queue takes every tile still listed and runs to the fixed point
         // (it also writes ctrl->rounds)
-        const uint32_t leave = tail_leave(tbytes);
-        // a launch with no more tiles than that leaves every round after the
-        // first to the queue: those rounds would find nothing to do (with timing
-        // on they are launched, for their records)
-        const bool rounds = L.n_tiles > (int64_t)leave || g_timing.on != MR_TIMING_OFF;
-        for (round = 2; rounds && round <= (uint32_t)tn.tail_rounds; ++round) {
+        for (round = 2; !queue_next && round <= (uint32_t)tn.tail_rounds; ++round) {
             span.begin(round);
             {
                 LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                 e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl, round,
-                                      tn.max_sweeps, grid, s, op_all, leave);
+                                      tn.max_sweeps, grid, s, op_all, leave, nullptr);
             }
             if (e != hipSuccess) return hip_fail(e, "tile round");
             span.add();
@@ -439,7 +441,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
             LaunchTimer lt(s, MR_K_TILE_QUEUE, 0);
             e = launch_tile_queue(tbytes, conn, imgs, L.n_tiles, lists, (uint32_t)tn.tail_rounds + 1,
                                   ctrl, qflag, ring, L.ring_cap, tn.max_sweeps, grid,
-                                  QUEUE_WAIT_US, s, op_all, leave);
+                                  QUEUE_WAIT_US, s, op_all, leave, queue_next ? 2u : 0u);
         }
         if (e != hipSuccess) return hip_fail(e, "tile queue");
     } else {
@@ -463,7 +465,7 @@ int run_sequence(int tbytes, int conn, const Imgs &imgs, const Layout &L, void *
                 {
                     LaunchTimer lt(s, MR_K_TILE_ROUND, (int32_t)round);
                     e = launch_tile_round(tbytes, conn, imgs, L.n_tiles, flags, lists, ctrl,
-                                          round, tn.max_sweeps, grid, s, op_all, 0);
+                                          round, tn.max_sweeps, grid, s, op_all, 0, nullptr);
                 }
                 if (e != hipSuccess) return e;
                 span.add();
@@ -937,14 +939,28 @@ int mr_autotune(const mr_tile *tiles, int32_t n, mr_dtype t, int conn, void *ws,
     return rc;
 }
 
-int mr_read_counters(const void *ws, mr_counters *out, void *stream) {
-    g_err.clear();
-    if (!ws || !out) return fail(MR_EINVAL, "null pointer");
-    Ctrl h;
+// The control block of the last call that used ws (waits for it). Tiles of a round
+// that were left to the tile queue are moved to where handed-over tiles stand, behind
+// the last round.
+static int read_ctrl(const void *ws, Ctrl &h, void *stream) {
     hipError_t e = hipMemcpyAsync(&h, ws, sizeof h, hipMemcpyDeviceToHost, (hipStream_t)stream);
     if (e != hipSuccess) return hip_fail(e, "counter copy");
     if ((e = hipStreamSynchronize((hipStream_t)stream)) != hipSuccess)
         return hip_fail(e, "counter sync");
+    if (h.seed_round >= 2 && h.seed_round <= h.rounds && h.rounds <= (unsigned)MAX_ROUNDS)
+        for (int b = 0; b < NBANDS; ++b) {
+            h.round_tiles[h.rounds + 1][b] = h.round_tiles[h.seed_round][b];
+            h.round_tiles[h.seed_round][b] = 0;
+        }
+    return MR_OK;
+}
+
+int mr_read_counters(const void *ws, mr_counters *out, void *stream) {
+    g_err.clear();
+    if (!ws || !out) return fail(MR_EINVAL, "null pointer");
+    Ctrl h;
+    const int rc = read_ctrl(ws, h, stream);
+    if (rc != MR_OK) return rc;
     mr_counters c{};
     c.rounds = h.rounds;
     c.seeds = h.seeds_total.v;
@@ -983,9 +999,8 @@ int mr_read_round_tiles(const void *ws, uint32_t *out, int32_t cap, int32_t *n_r
     g_err.clear();
     if (!ws || !n_rounds || (cap > 0 && !out) || cap < 0) return fail(MR_EINVAL, "bad pointer or cap");
     Ctrl h;
-    hipError_t e = hipMemcpyAsync(&h, ws, sizeof h, hipMemcpyDeviceToHost, (hipStream_t)stream);
-    if (e != hipSuccess) return hip_fail(e, "copy");
-    if ((e = hipStreamSynchronize((hipStream_t)stream)) != hipSuccess) return hip_fail(e, "sync");
+    const int rc = read_ctrl(ws, h, stream);
+    if (rc != MR_OK) return rc;
     const int n = (int)std::min<unsigned long long>(h.rounds + 1, MAX_ROUNDS);
     *n_rounds = (int32_t)h.rounds;
     for (int i = 0; i < cap && i < n; ++i) out[i] = (uint32_t)round_total(h, i + 1);

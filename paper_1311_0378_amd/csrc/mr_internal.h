@@ -74,6 +74,8 @@ struct Ctrl {
     unsigned long long iters[NCNT];  // sweep iterations over all tile visits (spread)
     unsigned long long rounds;       // written by the host sequence
     unsigned long long watchdog;     // non-zero if a wave gave up waiting or a push was refused
+    uint32_t seed_round; // the round whose lists the tile queue started from (0: none ran)
+    uint32_t pad;
     // round_tiles[r][b]: length of band b's dirty list for round r (round 1:
     // the band's size, written when the block is cleared); round k + 1's lists
     // are what the seed pass starts from after k rounds.
@@ -131,11 +133,12 @@ hipError_t launch_clear_start(Ctrl *c, int64_t n_tiles, uint32_t *flags, uint32_
 // (flags[t] = the latest round t is listed for). Every image's first round
 // is 1; op_all is the op of all images (MR_OP_RECON / MR_OP_FILL), or -1 if
 // they differ. A round after the first that lists at most `leave` tiles visits
-// none of them: they are for a tile queue launched with the same `leave`.
+// none of them: they are for a tile queue launched with the same `leave`. With
+// `queued` (tile-queue states), the tiles it lists are marked as queued there.
 hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              uint32_t *flags, uint32_t *lists, Ctrl *ctrl, uint32_t round,
                              int max_iters, int grid, hipStream_t s, int op_all,
-                             uint32_t leave);
+                             uint32_t leave, uint32_t *queued);
 // The same round with explicit list-length counters (NBANDS each) for this
 // round and the next, and the counters of a round still to come, which it clears.
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
@@ -149,15 +152,16 @@ hipError_t launch_clear_u64(uint64_t *p, int64_t n, hipStream_t s);
 hipError_t launch_queue(int tbytes, int conn, const Imgs &imgs, Ctrl *ctrl, uint64_t *bitmap,
                         uint32_t *qflag, uint32_t *ring, uint64_t cap, int blocks,
                         unsigned long long wait_us, hipStream_t s);
-// Tile queue: seed it with every tile listed for `round`, or for the earlier
-// round that `leave` left to it (state[t] = 1, ring
-// entries, pending), then visit tiles from it on a persistent grid until none
-// is queued or running. state[] and ring[] start cleared (0, Q_EMPTY).
+// Tile queue: visits every tile listed for `round`, or for the earlier round that
+// `leave` left to it, and those that the visits lead to, on a persistent grid until
+// none is queued or running. With `from`, that round is known to be `from`, and the
+// round kernel that listed its tiles has marked them as queued. state[] and ring[]
+// start cleared (0, Q_EMPTY) otherwise.
 hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              const uint32_t *lists, uint32_t round, Ctrl *ctrl, uint32_t *state,
                              uint32_t *ring, uint64_t cap, int max_iters, int grid,
                              unsigned long long wait_us, hipStream_t s, int op_all,
-                             uint32_t leave);
+                             uint32_t leave, uint32_t from);
 // The queue phase's widened planes: copy every tile interior of J into
 // `wide` (to_wide), or back (from wide to J).
 hipError_t launch_widen(const Imgs &imgs, int64_t n_tiles, bool to_wide, hipStream_t s);

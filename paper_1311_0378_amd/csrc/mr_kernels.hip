@@ -643,6 +643,7 @@ struct Appender {
     uint32_t *list_out; // next round's dirty lists (band b's at its band start)
     uint32_t *counter;  // their lengths, NBANDS of them
     int64_t n_tiles;
+    uint32_t *queued;   // tile-queue states: set to 1 for the listed tiles; or null
 };
 
 // Append the batch: each lane takes one entry, and each band present gets
@@ -666,7 +667,10 @@ __device__ __forceinline__ void app_flush(Appender &a, int lane) {
     uint32_t base = 0;
     if (lane < NBANDS && mine) base = atomicAdd(a.counter + lane, (uint32_t)__popcll(mine));
     const uint32_t my_base = __shfl(base, be < 0 ? 0 : be);
-    if (valid) a.list_out[band_lo(a.n_tiles, be) + my_base + __popcll(under)] = e;
+    if (valid) {
+        a.list_out[band_lo(a.n_tiles, be) + my_base + __popcll(under)] = e;
+        if (a.queued) a.queued[e] = 1u;
+    }
     wave_sync();
     a.cnt = 0;
 }
@@ -788,16 +792,18 @@ __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64
 // Retire one processed entry and draw the next ticket, in one instruction (the
 // whole wave; the ticket is lane 1's). The wave that retires the last entry
 // writes a stop entry for each of the launch's `waves` waves (each holds at most
-// one ticket past the last entry, this one's new ticket among them).
+// one ticket past the last entry, this one's new ticket among them). `pending`
+// counts the entries beyond the launch's `seeds`.
 __device__ __forceinline__ unsigned long long ring_retire(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
-                                                          unsigned waves, int lane) {
+                                                          unsigned waves, uint32_t seeds,
+                                                          int lane) {
     unsigned long long got = 0, base = 0;
     if (lane < 2)
         got = __hip_atomic_fetch_add(lane == 0 ? &ctrl->pending.v : &ctrl->q_head.v,
                                      lane == 0 ? (unsigned long long)-1ll : 1ull, __ATOMIC_RELAXED,
                                      __HIP_MEMORY_SCOPE_AGENT);
     const unsigned long long ticket = __shfl(got, 1);
-    if (__ballot(lane == 0 && got == 1) == 0) return ticket;
+    if (__ballot(lane == 0 && got + seeds == 1) == 0) return ticket;
     if (lane == 0)
         base = __hip_atomic_fetch_add(&ctrl->q_tail.v, (unsigned long long)waves, __ATOMIC_RELAXED,
                                       __HIP_MEMORY_SCOPE_AGENT);
@@ -1210,13 +1216,15 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
                                                       int all_tiles, Ctrl *__restrict__ ctrl,
                                                       uint32_t round, int max_iters,
                                                       uint32_t leave,
-                                                      uint32_t *__restrict__ counts_clear) {
+                                                      uint32_t *__restrict__ counts_clear,
+                                                      uint32_t *__restrict__ queued) {
     if (counts_clear && blockIdx.x == 0 && threadIdx.x < NBANDS) counts_clear[threadIdx.x] = 0;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer (and load stage)
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
     const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round, leave);
-    Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles};
+    Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles,
+                 V < 0 || (V & 1) ? queued : nullptr};
     TileCursor cur = cursor_start(w);
     for (int64_t t; (t = cursor_next(cur, w, all_tiles, flags, round, lane)) >= 0;) {
         const ImgDesc d = load_desc(imgs, t);
@@ -1249,14 +1257,16 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
                                                          int all_tiles, Ctrl *__restrict__ ctrl,
                                                          uint32_t round, int max_iters,
                                                          uint32_t leave,
-                                                         uint32_t *__restrict__ counts_clear) {
+                                                         uint32_t *__restrict__ counts_clear,
+                                                      uint32_t *__restrict__ queued) {
     if (counts_clear && blockIdx.x == 0 && threadIdx.x < NBANDS) counts_clear[threadIdx.x] = 0;
     constexpr bool needJ = V != 3 && V != 5;
     __shared__ uint32_t tb[TS][TS + 1]; // transpose buffer and load stage
     __shared__ uint32_t abuf[APP_CAP];
     const int lane = threadIdx.x;
     const RoundWork w = round_work(n_tiles, lists, counts_in, all_tiles, round, leave);
-    Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles};
+    Appender app{abuf, 0, lists + ((round + 1) & 1) * n_tiles, counts_out, n_tiles,
+                 V < 0 || (V & 1) ? queued : nullptr};
     uint8_t *stage = (uint8_t *)tb;
     TileCursor cur = cursor_start(w);
     // the next tile to visit and its image (images that are done take no visit)
@@ -1300,13 +1310,12 @@ __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_ti
 
 // ------------------------------------------------------------- tile queue
 
-// Seeds the tile queue with band b's dirty list (block b): of `round`, or of an
-// earlier round whose tiles were left to the queue (more than none and at most
-// `leave` of them; the rounds after it had nothing to visit).
-__global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl, int64_t n_tiles,
-                                  uint32_t round, uint32_t leave, uint32_t *__restrict__ state,
-                                  uint32_t *__restrict__ ring, uint64_t cap) {
-    __shared__ unsigned long long base;
+// Before a tile queue that follows several rounds: finds the round whose lists it
+// starts from (`round`, or an earlier one whose tiles were left to the queue: no more
+// than `leave`; the rounds after it had nothing to visit), and marks band b's (block
+// b) listed tiles as queued.
+__global__ void k_tile_queue_mark(const uint32_t *__restrict__ lists, Ctrl *ctrl, int64_t n_tiles,
+                                  uint32_t round, uint32_t leave, uint32_t *__restrict__ state) {
     __shared__ uint32_t from;
     const int b = blockIdx.x;
     if (threadIdx.x == 0) {
@@ -1318,25 +1327,32 @@ __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl
             if (total <= leave) break;
         }
         from = r;
+        if (b == 0) ctrl->seed_round = r;
     }
     __syncthreads();
     const uint32_t n = ctrl->round_tiles[from][b];
-    if (n == 0) return;
     const uint32_t *list = lists + (from & 1) * n_tiles + band_lo(n_tiles, b);
-    if (threadIdx.x == 0) {
-        base = atomicAdd(&ctrl->q_tail.v, (unsigned long long)n);
-        atomicAdd(&ctrl->pending.v, (unsigned long long)n);
+    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) state[list[i]] = 1u;
+}
+
+// Entry i of the lists of a round laid end to end (uniform).
+__device__ __forceinline__ uint32_t listed_tile(const Ctrl *ctrl, const uint32_t *lists,
+                                                int64_t n_tiles, uint32_t round, uint32_t i) {
+    const auto c = kconst(ctrl->round_tiles[round]);
+    uint32_t lo = 0; // entries of the bands before
+    int64_t at = 0;
+#pragma unroll
+    for (int q = 0; q < NBANDS; ++q) {
+        const uint32_t n = c[q];
+        if (i >= lo && i < lo + n) at = band_lo(n_tiles, q) + (i - lo);
+        lo += n;
     }
-    __syncthreads();
-    for (uint32_t i = threadIdx.x; i < n; i += blockDim.x) {
-        const uint32_t t = list[i];
-        state[t] = 1u;
-        ring[(base + i) & (cap - 1)] = t;
-    }
+    return kconst(lists + (round & 1) * n_tiles)[at];
 }
 
 // The tile queue (the regular phase without rounds): each wave takes a tile
-// off the ring, visits it like a tile round does, and marks the neighbours
+// off the lists it starts from (tickets below their length `seeds`) or off the ring,
+// visits it like a tile round does, and marks the neighbours
 // straight into the ring, so a chain of dependent tiles costs one visit per
 // link instead of one round. A wave takes a ticket (the next ring position)
 // and waits for that entry, so no two waves contend for an entry. The wave
@@ -1347,7 +1363,8 @@ __global__ void k_tile_queue_seed(const uint32_t *__restrict__ lists, Ctrl *ctrl
 // tile, after 8 rounds, the queue takes 269 us (357 us with every neighbour
 // through the ring). The whole launch ends when every wave has its stop: written
 // by one lane, 2048 stops took 50 us. A wave that retires a tile draws its next
-// ticket in the same instruction.
+// ticket in the same instruction. Tickets read the lists themselves: a seed launch
+// that copied them to the ring cost small calls 3 us (293 x 421 uint8: 58.8 -> 56.2 us).
 
 // Waves per workgroup of the tile queue. int32 visits have no register to spare
 // for telling the waves of a workgroup apart (27 spills become 50, h-dome of a
@@ -1360,36 +1377,35 @@ __global__ __launch_bounds__(64 * TQ_WAVES<T>, 2) void k_tile_queue(Imgs imgs, C
                                                       uint32_t *__restrict__ ring, uint64_t cap,
                                                       int max_iters,
                                                       unsigned long long wait_us,
-                                                      uint32_t round, uint32_t leave) {
+                                                      uint32_t round, uint32_t from,
+                                                      const uint32_t *__restrict__ lists,
+                                                      int64_t n_tiles) {
     __shared__ uint32_t tbs[TQ_WAVES<T>][TS][TS + 1];
     const int lane = threadIdx.x & 63;
     uint32_t (*tb)[TS + 1] = tbs[TQ_WAVES<T> == 1 ? 0 : threadIdx.x >> 6];
-    // The counts for the work counters: rounds launched, and the tiles of a
-    // round left to the queue moved to where handed-over tiles stand.
-    if (blockIdx.x == 0 && threadIdx.x < NBANDS) {
-        if (lane == 0) ctrl->rounds = round - 1;
-        for (uint32_t r = 2; r < round; ++r) {
-            const uint32_t n = ctrl->round_tiles[r][lane];
-            uint32_t total = n;
-#pragma unroll
-            for (int k = 1; k < NBANDS; k <<= 1) total += __shfl_xor(total, k);
-            if (total <= leave) {
-                ctrl->round_tiles[r][lane] = 0;
-                ctrl->round_tiles[round][lane] = n;
-                break;
-            }
-        }
+    // the round whose lists this launch starts from; 0: as k_tile_queue_mark found
+    const uint32_t first_list = from ? from : *kconst(&ctrl->seed_round);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        ctrl->rounds = round - 1;
+        if (from) ctrl->seed_round = from;
     }
-    Appender app{nullptr, 0, nullptr, nullptr, 0}; // unused: marks go to the ring
+    uint32_t seeds = 0;
+#pragma unroll
+    for (int q = 0; q < NBANDS; ++q) seeds += kconst(ctrl->round_tiles[first_list])[q];
+    Appender app{nullptr, 0, nullptr, nullptr, 0, nullptr}; // unused: marks go to the ring
     unsigned long long visits = 0;
-    // nothing seeded: no wave will ever retire a tile and write the stops
-    if (__hip_atomic_load(&ctrl->pending.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-        return;
+    // nothing listed: no wave will ever retire a tile and write the stops
+    if (seeds == 0) return;
     uint32_t t = Q_EMPTY; // the tile this wave holds: its state is 2, it counts as pending
     unsigned long long ticket = ring_tickets(ctrl, TQ_WAVES<T>);
     while (true) {
         if (t == Q_EMPTY) {
-            if (lane == 0) t = ring_take(ctrl, ring, cap, ticket, wait_us);
+            const uint32_t i = (uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)ticket);
+            if (ticket < seeds) {
+                t = listed_tile(ctrl, lists, n_tiles, first_list, i);
+            } else if (lane == 0) {
+                t = ring_take(ctrl, ring, cap, ticket - seeds, wait_us);
+            }
             t = (uint32_t)__builtin_amdgcn_readfirstlane(t); // (uniform: scalar descriptor loads)
             if (t == Q_STOP) break;
             // queued -> visited, performed before any pixel is read: a mark that
@@ -1462,7 +1478,8 @@ __global__ __launch_bounds__(64 * TQ_WAVES<T>, 2) void k_tile_queue(Imgs imgs, C
         wait_vmem();
         ring_push(ctrl, ring, cap, push, lane);
         // one entry held before and, with a next tile, one held now
-        if (next == Q_EMPTY) ticket = ring_retire(ctrl, ring, cap, gridDim.x * TQ_WAVES<T>, lane);
+        if (next == Q_EMPTY) ticket = ring_retire(ctrl, ring, cap, gridDim.x * TQ_WAVES<T>, seeds,
+                                              lane);
         t = next;
     }
     if (lane == 0 && visits)
@@ -1693,7 +1710,7 @@ __global__ __launch_bounds__(64 * QWAVES) void k_queue(Imgs imgs, Ctrl *__restri
         }
         // everything this tile produced is pushed; retire the ring entry
         wait_vmem();
-        ticket = ring_retire(ctrl, ring, cap, gridDim.x * QWAVES, lane);
+        ticket = ring_retire(ctrl, ring, cap, gridDim.x * QWAVES, 0, lane);
     }
     // fold the per-lane counters
     unsigned long long p = npush, r = retries;
@@ -1936,17 +1953,17 @@ template <typename T, int CONN, int V>
 static hipError_t tile_round_v(const Imgs &imgs, int64_t n_tiles, uint32_t *flags,
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
-                               hipStream_t s, uint32_t leave, uint32_t *clear) {
+                               hipStream_t s, uint32_t leave, uint32_t *clear, uint32_t *queued) {
     const int64_t want = std::max<int64_t>(NBANDS, (n_tiles + NBANDS - 1) / NBANDS * NBANDS);
     const unsigned g = (unsigned)(std::min<int64_t>(grid, want) / NBANDS * NBANDS);
     // (uint8 planes beyond the stage's range are rare: one kernel for all visits)
     constexpr int VR = sizeof(T) == 1 ? -1 : V;
     if (sizeof(T) == 1 && imgs.staged)
         hipLaunchKernelGGL((k_tile_round_pf<CONN, V>), dim3(g), dim3(64), 0, s, imgs,
-                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear);
+                           n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear, queued);
     else
         hipLaunchKernelGGL((k_tile_round<T, CONN, VR>), dim3(g), dim3(64), 0, s, imgs, n_tiles,
-                           flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear);
+                           flags, lists, cin, cout, all, ctrl, round, max_iters, leave, clear, queued);
     return hipGetLastError();
 }
 
@@ -1955,14 +1972,14 @@ static hipError_t tile_round_t(const Imgs &imgs, int64_t n_tiles, uint32_t *flag
                                uint32_t *lists, const uint32_t *cin, uint32_t *cout, int all,
                                Ctrl *ctrl, uint32_t round, int max_iters, int grid,
                                hipStream_t s, int variant, uint32_t leave,
-                               uint32_t *clear) {
+                               uint32_t *clear, uint32_t *queued) {
     switch (variant) {
-    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
-    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
-    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
-    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
-    case 5: return tile_round_v<T, CONN, 5>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
-    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear);
+    case 0: return tile_round_v<T, CONN, 0>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
+    case 1: return tile_round_v<T, CONN, 1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
+    case 2: return tile_round_v<T, CONN, 2>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
+    case 3: return tile_round_v<T, CONN, 3>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
+    case 5: return tile_round_v<T, CONN, 5>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
+    default: return tile_round_v<T, CONN, -1>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, leave, clear, queued);
     }
 }
 
@@ -1970,13 +1987,13 @@ static hipError_t tile_round_any(int tbytes, int conn, const Imgs &imgs, int64_t
                                  uint32_t *flags, uint32_t *lists, const uint32_t *cin,
                                  uint32_t *cout, int all, Ctrl *ctrl, uint32_t round,
                                  int max_iters, int grid, hipStream_t s, int variant,
-                                 uint32_t leave, uint32_t *clear) {
+                                 uint32_t leave, uint32_t *clear, uint32_t *queued) {
     if (!ctrl) return hipErrorInvalidValue;
     if (tbytes == 1)
-        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear)
-                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear);
-    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear)
-                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear);
+        return conn == 8 ? tile_round_t<uint8_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear, queued)
+                         : tile_round_t<uint8_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear, queued);
+    return conn == 8 ? tile_round_t<int32_t, 8>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear, queued)
+                     : tile_round_t<int32_t, 4>(imgs, n_tiles, flags, lists, cin, cout, all, ctrl, round, max_iters, grid, s, variant, leave, clear, queued);
 }
 
 hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
@@ -1984,12 +2001,13 @@ hipError_t launch_tile_round_ex(int tbytes, int conn, const Imgs &imgs, int64_t 
                                 uint32_t *cout, uint32_t *clear, Ctrl *ctrl, uint32_t round,
                                 int max_iters, int grid, hipStream_t s) {
     return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, cin, cout, 0, ctrl, round,
-                          max_iters, grid, s, -1, 0, clear);
+                          max_iters, grid, s, -1, 0, clear, nullptr);
 }
 
 hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              uint32_t *flags, uint32_t *lists, Ctrl *ctrl, uint32_t round,
-                             int max_iters, int grid, hipStream_t s, int op_all, uint32_t leave) {
+                             int max_iters, int grid, hipStream_t s, int op_all, uint32_t leave,
+                             uint32_t *queued) {
     // every image starts in round 1 here, so with one op for all of them the
     // visit is known for the whole launch
     const int variant = op_all < 0 ? -1 : ((op_all == MR_OP_FILL ? 2 : 0) | (round == 1 ? 1 : 0) |
@@ -2002,32 +2020,34 @@ hipError_t launch_tile_round(int tbytes, int conn, const Imgs &imgs, int64_t n_t
     // stale more often), so uint8 rounds keep the lists.
     return tile_round_any(tbytes, conn, imgs, n_tiles, flags, lists, ctrl->round_tiles[round],
                           ctrl->round_tiles[round + 1], round == 1 ? 1 : (tbytes == 4 ? 2 : 0), ctrl, round,
-                          max_iters, grid, s, variant, leave, nullptr);
+                          max_iters, grid, s, variant, leave, nullptr, queued);
 }
 
 template <typename T, int CONN, int V>
 static hipError_t tile_queue_v(const Imgs &imgs, Ctrl *ctrl, uint32_t *state, uint32_t *ring,
                                uint64_t cap, int max_iters, int grid, unsigned long long wait_us,
-                               hipStream_t s, uint32_t round, uint32_t leave) {
+                               hipStream_t s, uint32_t round, uint32_t from,
+                               const uint32_t *lists, int64_t n_tiles) {
     hipLaunchKernelGGL((k_tile_queue<T, CONN, V>), dim3((unsigned)grid), dim3(64 * TQ_WAVES<T>), 0, s, imgs,
-                       ctrl, state, ring, cap, max_iters, wait_us, round, leave);
+                       ctrl, state, ring, cap, max_iters, wait_us, round, from, lists, n_tiles);
     return hipGetLastError();
 }
 template <typename T, int CONN>
 static hipError_t tile_queue_t(const Imgs &imgs, Ctrl *ctrl, uint32_t *state, uint32_t *ring,
                                uint64_t cap, int max_iters, int grid, unsigned long long wait_us,
-                               hipStream_t s, int op_all, uint32_t round, uint32_t leave) {
+                               hipStream_t s, int op_all, uint32_t round, uint32_t from,
+                               const uint32_t *lists, int64_t n_tiles) {
     if (op_all == MR_OP_RECON)
-        return tile_queue_v<T, CONN, 0>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
+        return tile_queue_v<T, CONN, 0>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, from, lists, n_tiles);
     if (op_all == MR_OP_FILL)
-        return tile_queue_v<T, CONN, 2>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
-    return tile_queue_v<T, CONN, -1>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, leave);
+        return tile_queue_v<T, CONN, 2>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, from, lists, n_tiles);
+    return tile_queue_v<T, CONN, -1>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, round, from, lists, n_tiles);
 }
 hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_tiles,
                              const uint32_t *lists, uint32_t round, Ctrl *ctrl, uint32_t *state,
                              uint32_t *ring, uint64_t cap, int max_iters, int grid,
                              unsigned long long wait_us, hipStream_t s, int op_all,
-                             uint32_t leave) {
+                             uint32_t leave, uint32_t from) {
     if (!ctrl || round > (uint32_t)MAX_ROUNDS + 1 || grid < 1 || n_tiles < 1)
         return hipErrorInvalidValue;
     // no more waves than tiles: a wave visits one tile at a time. uint8 launches
@@ -2037,15 +2057,17 @@ hipError_t launch_tile_queue(int tbytes, int conn, const Imgs &imgs, int64_t n_t
     if (tbytes == 1) grid = std::max(grid / 2, 1);
     const int wg = tbytes == 1 ? TQ_WAVES<uint8_t> : TQ_WAVES<int32_t>;
     grid = (int)((std::min<int64_t>(std::min<int64_t>(grid, RING_SLACK), n_tiles) + wg - 1) / wg);
-    hipLaunchKernelGGL(k_tile_queue_seed, dim3(NBANDS), dim3(256), 0, s, lists, ctrl, n_tiles,
-                       round, leave, state, ring, cap);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
+    if (!from) {
+        hipLaunchKernelGGL(k_tile_queue_mark, dim3(NBANDS), dim3(256), 0, s, lists, ctrl, n_tiles,
+                           round, leave, state);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
     if (tbytes == 1)
-        return conn == 8 ? tile_queue_t<uint8_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave)
-                         : tile_queue_t<uint8_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave);
-    return conn == 8 ? tile_queue_t<int32_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave)
-                     : tile_queue_t<int32_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, leave);
+        return conn == 8 ? tile_queue_t<uint8_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, from, lists, n_tiles)
+                         : tile_queue_t<uint8_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, from, lists, n_tiles);
+    return conn == 8 ? tile_queue_t<int32_t, 8>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, from, lists, n_tiles)
+                     : tile_queue_t<int32_t, 4>(imgs, ctrl, state, ring, cap, max_iters, grid, wait_us, s, op_all, round, from, lists, n_tiles);
 }
 
 template <typename T, int CONN>
