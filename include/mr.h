@@ -266,7 +266,9 @@ int mr_autotune(const mr_tile *tiles, int32_t n, mr_dtype t, int conn, void *ws,
  * (an upstream kernel produced them): the copies into and out of the arena
  * are device-to-device, and no PCIe transfer is involved. What a job only
  * reads (the mask, or the image to fill) may be read in place until the job is
- * done, and a filled image may be written to its result directly. */
+ * done, and a filled image may be written to its result directly. Another job's
+ * result may be written there all the same: each job sees its inputs as they were
+ * when it was submitted, or as results of jobs reported done by then left them. */
 enum { MR_JOB_DEVICE = 1 };
 typedef struct {
     const void *data; /* H x W: the marker (MR_OP_RECON) or the image (MR_OP_FILL) */

@@ -121,6 +121,7 @@ struct Job {
     int band;
     uint32_t first_round;
     ImgDesc d;
+    bool direct = false;      // the image that is only read is read where it is
     bool fill_direct = false; // the epilogue writes the result itself
 };
 
@@ -203,6 +204,19 @@ int check_job(const mr_server *s, const mr_job *j) {
     return MR_OK;
 }
 
+// The image a job only reads: the mask, or the image to fill.
+const void *read_image(const mr_job &j) { return j.op == MR_OP_RECON ? j.mask : j.data; }
+
+// Whether an H x W plane of job a (row pitch la, 0: its width) and one of job b share
+// bytes of memory.
+bool shares(const void *pa, int64_t la, const mr_job &a, const void *pb, int64_t lb,
+            const mr_job &b, int t) {
+    auto end = [t](const void *p, int64_t ld, const mr_job &j) {
+        return (uintptr_t)p + (uintptr_t)(((j.H - 1) * (ld ? ld : j.W) + j.W) * t);
+    };
+    return (uintptr_t)pa < end(pb, lb, b) && (uintptr_t)pb < end(pa, la, a);
+}
+
 int hip_err(hipError_t e, const char *what) {
     return sfail(MR_EHIP, "%s: %s", what, hipGetErrorString(e));
 }
@@ -216,6 +230,27 @@ int hip_err(hipError_t e, const char *what) {
 // resident job in the first band or two and leave the other dies' workgroups
 // idle, so a job's tiles go into the band with the fewest resident tiles
 // that has room, and anywhere only if no band has.
+// Copies the image that a resident job reads where it is into the job's planes: on the
+// upload stream if the job has not been admitted to a round yet, else between rounds.
+hipError_t own_input(mr_server *s, Job &x) {
+    char *p = s->arena + s->data_off + x.mem_off + (x.spec.op == MR_OP_RECON ? x.plane : 0);
+    const bool waiting =
+        std::find(s->admitted.begin(), s->admitted.end(), x.slot) != s->admitted.end();
+    const size_t row = (size_t)x.spec.W * s->t;
+    hipError_t e = hipMemcpy2DAsync(p, (size_t)x.pitch * s->t, x.d.I, (size_t)x.d.pI * s->t, row,
+                                    (size_t)x.spec.H, hipMemcpyDeviceToDevice,
+                                    waiting ? s->up : s->stream);
+    if (e != hipSuccess) return e;
+    x.direct = false;
+    x.d.I = p;
+    x.d.pI = x.pitch;
+    if (waiting)
+        s->copies = true;
+    else
+        e = launch_put_descs(s->descs + x.slot, &x.d, 1, s->stream);
+    return e;
+}
+
 int64_t band_start(int64_t n, int b) { return (int64_t)b * n / NBANDS; }
 
 int band_of_tile(int64_t n, int64_t t) {
@@ -383,9 +418,28 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
     // read where it is, and a filled image goes straight to its result; planes
     // beyond the tile loads' 32-bit offsets are copied into the arena like a host
     // job's.
-    const bool direct =
+    j.direct =
         device && (uint64_t)((job->H - 1) * ld + job->W) + 64 <= STAGE_MAX_BYTES &&
         (uintptr_t)(job->op == MR_OP_RECON ? job->mask : job->data) % s->t == 0;
+    // A result may be an input of another job in flight, which is to see what the
+    // buffer held when it was submitted: this job's input is copied now if a job
+    // before it will write there, and theirs if this one will.
+    for (auto &kv : s->resident) {
+        Job &x = kv.second;
+        if (shares(read_image(*job), job->ld, *job, x.spec.result, x.spec.ld_result, x.spec, s->t))
+            j.direct = false;
+        if (!x.direct ||
+            !shares(read_image(x.spec), x.spec.ld, x.spec, job->result, job->ld_result, *job, s->t))
+            continue;
+        const hipError_t ce = own_input(s, x);
+        if (ce != hipSuccess) {
+            s->mem.release(mo, need);
+            s->tiles.release(to, (size_t)j.n_tiles);
+            s->band_tiles[j.band] -= j.n_tiles;
+            return hip_err(ce, "input copy");
+        }
+    }
+    const bool direct = j.direct;
     const hipMemcpyKind in_kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
     hipError_t e = hipSuccess;
     auto copy_in = [&](char *dst, const void *src) {

@@ -158,6 +158,37 @@ def test_server_device_jobs_in_place():
     assert bool((big[0] == 5).all())
 
 
+# A result that is an input of another job in flight: both see what the buffer held when
+# they were submitted, whichever comes first and whether or not its rounds have begun.
+@pytest.mark.parametrize("steps", [0, 1])
+@pytest.mark.parametrize("reader_first", [False, True])
+def test_server_device_jobs_share_buffers(reader_first, steps):
+    from test_oracle_pins import serpentine
+    marker, mask = serpentine(500, 700, 8)  # a long chain: the reader ends last
+    x = torch.from_numpy(mask).to(DEV)
+    writer = (x, None, mrecon.MR_OP_FILL, x)
+    reader = (torch.from_numpy(marker).to(DEV), x, mrecon.MR_OP_RECON,
+              torch.zeros_like(x))
+    srv = mrecon.Server(64 << 20, max_jobs=4)
+    torch.cuda.synchronize()
+    print(f"[gpu] shared buffers reader_first={reader_first} steps={steps}", flush=True)
+    if reader_first:
+        srv.submit(*reader[:3], out=reader[3])
+        for _ in range(steps):
+            srv.step()
+        srv.submit(*writer[:3], out=writer[3])
+    else:
+        srv.submit(*writer[:3], out=writer[3])
+        srv.submit(*reader[:3], out=reader[3])
+    srv.drain()
+    srv.close()
+    want = oracle.recon_dilate(marker, mask, 8)[0]
+    assert np.array_equal(reader[3].cpu().numpy(), want), first_mismatch(reader[3].cpu().numpy(),
+                                                                         want)
+    want = oracle.fill_holes(mask, 8)[0]
+    assert np.array_equal(x.cpu().numpy(), want), first_mismatch(x.cpu().numpy(), want)
+
+
 @pytest.mark.parametrize("conn", [4, 8])
 def test_server_device_jobs(conn):
     # jobs whose inputs and results are device memory (MR_JOB_DEVICE): the
