@@ -1246,7 +1246,7 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
 // sweeps no longer need; the next visit writes them to the stage. With V < 0
 // (mixed batches, the server) a visit's kind is read from its image.
 // Planes of any base and pitch take this kernel: a batch of 40 mixed tiles of
-// odd sizes spends 582 us in its rounds (757 us when such planes were loaded
+// odd sizes spends 502 us in its rounds (757 us when such planes were loaded
 // byte by byte by k_tile_round), one 293 x 421 image 61 us instead of 120.
 template <int CONN, int V>
 __global__ __launch_bounds__(64, 2) void k_tile_round_pf(Imgs imgs, int64_t n_tiles,
