@@ -481,19 +481,38 @@ __device__ __forceinline__ void load_tile(const ImgDesc &d, int64_t t, int64_t g
         return;
     }
     const uint32_t xc = (uint32_t)(gx < 0 ? 0 : (gx > W - 1 ? W - 1 : gx));
+    // int32: all rows are loaded before any is used. Left to itself the compiler
+    // waits for each row before it loads the next, 64 memory latencies a visit to a
+    // border tile: 21 int32 jobs on the server 1255 -> 855 us, 1152 x 473 192 -> 173
+    // us. (uint8 tiles come here only from planes too large to stage.)
+    constexpr bool AHEAD = sizeof(T) == 4;
+    if (AHEAD) {
+        auto clamped = [&](int r) {
+            const int64_t gy = gy0 + r;
+            return (uint32_t)(gy < 0 ? 0 : (gy > H - 1 ? H - 1 : gy));
+        };
+#pragma unroll
+        for (int r = 0; r < TS; ++r) I[r] = (uint32_t)Ip[clamped(r) * (uint32_t)d.pI + xc];
+        if (!(fill && initial) && !kind.lowered) {
+#pragma unroll
+            for (int r = 0; r < TS; ++r)
+                J[r] = (uint32_t)load_j<T, COH>(Jp, clamped(r) * (uint32_t)d.pJ + xc);
+        }
+        asm volatile("" ::: "memory");
+    }
 #pragma unroll
     for (int r = 0; r < TS; ++r) {
         const int64_t gy = gy0 + r;
         const bool ok = xin && gy >= 0 && gy < H;
         const uint32_t yc = (uint32_t)(gy < 0 ? 0 : (gy > H - 1 ? H - 1 : gy));
-        uint32_t iv = P::key(Ip[yc * (uint32_t)d.pI + xc]) ^ flip;
+        uint32_t iv = P::key(AHEAD ? (T)I[r] : Ip[yc * (uint32_t)d.pI + xc]) ^ flip;
         uint32_t jv;
         if (fill && initial) {
             jv = (xedge || yc == 0 || yc == (uint32_t)(H - 1)) ? iv : 0u;
         } else if (kind.lowered) {
             jv = lower(iv, d.h);
         } else {
-            jv = P::key(load_j<T, COH>(Jp, yc * (uint32_t)d.pJ + xc));
+            jv = P::key(AHEAD ? (T)J[r] : load_j<T, COH>(Jp, yc * (uint32_t)d.pJ + xc));
             if (initial) jv = min(jv, iv);
         }
         jv = ok ? jv : 0u;
