@@ -20,7 +20,8 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():  # collected on CPU-only hosts too
     pytest.skip("no GPU", allow_module_level=True)
 
-from gpu_util import DEV, first_mismatch, gpu_fill, gpu_recon  # noqa: E402
+from gpu_util import first_mismatch, gpu_fill, gpu_recon  # noqa: E402
+from gpu_util import DEV  # noqa: E402
 from paper_1311_0378_amd import mrecon  # noqa: E402
 
 GOLDEN = os.path.join(os.path.dirname(__file__), "golden")
