@@ -331,15 +331,16 @@ void mr_server_destroy(mr_server *s);
 
 /* Copies the work counters held in a workspace to *out. Waits for `stream`.
  * Errors: MR_EINVAL (null pointer), MR_EHIP (a copy failed, or a wave of the
- * queue phase or the tile queue saw no new ring entry for 2 s and gave up:
- * the result of that call is then incomplete; *out is still written). */
+ * queue phase or the tile queue saw no progress -- no ring entry and no tile
+ * visit -- for 2 s and gave up: the result of that call is then incomplete;
+ * *out is still written). */
 int mr_read_counters(const void *ws, mr_counters *out, void *stream);
 
 /* Status of the last call that used a workspace (mr_recon_dilate,
  * mr_fill_holes, mr_recon_erode, mr_batch or a graph launch over it). Waits
  * for `stream`, then returns MR_OK if that call ran to its fixed point, or
- * MR_EHIP if a wave of its queue phase or tile queue gave up (no new ring
- * entry for 2 s) or a ring push was refused: the result is then incomplete.
+ * MR_EHIP if a wave of its queue phase or tile queue gave up (no progress
+ * for 2 s) or a ring push was refused: the result is then incomplete.
  * The status is kept until the next call on the same workspace clears it, so
  * check it before reusing the workspace. Costs one 8-byte copy.
  * Errors: MR_EINVAL (null ws), MR_EHIP (as above, or a failed copy). */

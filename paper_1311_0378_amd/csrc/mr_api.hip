@@ -39,9 +39,10 @@ uint64_t next_pow2(uint64_t v) {
     return p;
 }
 
-// The watchdog of the queue phase and the tile queue: microseconds without
-// any new ring entry after which a waiting wave gives up (on a working device
-// entries come every few microseconds until the queue drains).
+// The watchdog of the queue phase and the tile queue: microseconds in which no
+// entry was queued and no tile visited, after which a waiting wave gives up (on a
+// working device one or the other happens every few microseconds until the queue
+// drains).
 constexpr unsigned long long QUEUE_WAIT_US = 2000000ull;
 
 

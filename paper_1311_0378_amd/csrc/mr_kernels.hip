@@ -760,9 +760,9 @@ __device__ __forceinline__ void wait_vmem() { asm volatile("s_waitcnt vmcnt(0)" 
 
 // Ring consumers take a ticket (the next position) and wait for that entry,
 // so no two waves contend for one. An entry can legitimately take as long as
-// the whole run (a long chain), so the watchdog fires only when no entry at
-// all was pushed for wait_us microseconds (100 MHz constant clock): then the
-// wave gives up with Q_STOP. One lane per wave calls it.
+// the whole run (a long chain), so the watchdog fires only when nothing at all
+// moved (ring_progress) for wait_us microseconds (100 MHz constant clock): then
+// the wave gives up with Q_STOP. One lane per wave calls it.
 constexpr uint32_t Q_STOP = 0xFFFFFFFEu;
 
 // A wave's first ticket (later ones come with ring_retire); a workgroup draws those
@@ -779,19 +779,32 @@ __device__ __forceinline__ unsigned long long ring_tickets(Ctrl *ctrl, unsigned 
     return first + (threadIdx.x >> 6);
 }
 
+// Moves while a launch makes progress: entries pushed and the sweep iterations of
+// its visits. (A wave of the tile queue that hands itself tile after tile pushes
+// nothing, for as long as its chain lasts: seconds on a corridor that winds through
+// a whole slide level.)
+__device__ __forceinline__ unsigned long long ring_progress(const Ctrl *ctrl) {
+    unsigned long long p =
+        __hip_atomic_load(&ctrl->q_tail.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+#pragma unroll 1
+    for (int i = 0; i < NCNT; ++i)
+        p += __hip_atomic_load(&ctrl->iters[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    return p;
+}
+
 __device__ __forceinline__ uint32_t ring_take(Ctrl *ctrl, uint32_t *ring, uint64_t cap,
                                               unsigned long long h, unsigned long long wait_us) {
     uint32_t *slot = ring + (h & (cap - 1));
-    unsigned long long t0 = wall_clock64(), seen = h;
+    // (nothing seen yet: the first interval ends with a look, never with giving up)
+    unsigned long long t0 = wall_clock64(), seen = ~0ull;
     uint32_t t;
     for (unsigned long long spin = 0;; ++spin) {
         t = __hip_atomic_load(slot, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         if (t != Q_EMPTY) break;
         if ((spin & 63) == 63 && wall_clock64() - t0 > wait_us * 100ull) {
-            const unsigned long long tail =
-                __hip_atomic_load(&ctrl->q_tail.v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            if (tail != seen) { // progress: wait on
-                seen = tail;
+            const unsigned long long now = ring_progress(ctrl);
+            if (now != seen) { // progress: wait on
+                seen = now;
                 t0 = wall_clock64();
                 continue;
             }

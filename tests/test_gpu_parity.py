@@ -122,6 +122,24 @@ def test_serpentine_tile_queue(conn, tail):
         assert c["rounds"] == tail and c["tiles"] > 0
 
 
+# One chain of half a million tile visits through one wave, each handed on without a ring
+# entry: seconds, longer than the watchdog waits. The corridor is flat, so all of it is
+# raised and the result is the mask.
+@pytest.mark.parametrize("dtype,conn", [(torch.uint8, 8), (torch.int32, 4)])
+def test_chain_longer_than_the_watchdog(dtype, conn):
+    H = W = 8192
+    mask = torch.zeros((H, W), dtype=dtype, device=DEV)
+    mask[::2] = 200
+    mask[1::4, -1] = mask[3::4, 0] = 200
+    marker = torch.zeros_like(mask)
+    marker[-1, 0] = 200  # the corridor's far end
+    ws = mrecon.alloc_workspace(mrecon.workspace_bytes(mrecon.MR_OP_RECON, H, W, dtype, conn), DEV)
+    print(f"[gpu] one chain {H}x{W} {dtype} conn{conn}", flush=True)
+    mrecon.recon_dilate(marker, mask, conn, workspace=ws)
+    mrecon.status(ws)
+    assert torch.equal(marker, mask)
+
+
 @pytest.mark.parametrize("W", [1, 5, 17, 62, 63, 77, 130])
 @pytest.mark.parametrize("conn", [4, 8])
 def test_aligned_pitch_shapes(W, conn):
