@@ -257,18 +257,17 @@ int mr_autotune(const mr_tile *tiles, int32_t n, mr_dtype t, int conn, void *ws,
 /* A request: one image, answered in a buffer of the same kind. Rows of the
  * inputs are `ld` elements apart and rows of the result `ld_result` apart
  * (0 means W), so a job can be a window of a larger image. The buffers must
- * stay valid, and the inputs unchanged, until the job is reported done.
+ * stay valid until the job is reported done.
  * Host jobs (flags 0): data, mask and result are host memory; pinned
  * (page-locked) memory lets the copies run asynchronously, pageable memory
  * works but copies synchronously.
  * Device jobs (flags MR_JOB_DEVICE): data, mask and result are device
  * memory of the server's GPU, for callers whose tiles are already in HBM
  * (an upstream kernel produced them): the copies into and out of the arena
- * are device-to-device, and no PCIe transfer is involved. What a job only
- * reads (the mask, or the image to fill) may be read in place until the job is
- * done, and a filled image may be written to its result directly. Another job's
- * result may be written there all the same: each job sees its inputs as they were
- * when it was submitted, or as results of jobs reported done by then left them. */
+ * are device-to-device, and no PCIe transfer is involved. The inputs are
+ * copied when the job is submitted: work that the caller enqueues on `stream`
+ * after mr_server_submit may overwrite them. A filled image may be written to
+ * its result directly. */
 enum { MR_JOB_DEVICE = 1 };
 typedef struct {
     const void *data; /* H x W: the marker (MR_OP_RECON) or the image (MR_OP_FILL) */

@@ -175,6 +175,11 @@ hipError_t launch_put_descs(ImgDesc *dst, const ImgDesc *v, int n, hipStream_t s
 int queue_max_blocks(int tbytes, int conn);
 int persistent_grid();
 
+// Server support: copy H rows of `row` bytes from x to a and, unless y is null, from y
+// to b (input rows sp bytes apart, output rows dp bytes, 16-byte aligned). H * row is
+// below 2^34.
+hipError_t launch_server_copy(void *a, const void *x, void *b, const void *y, int64_t dp,
+                              int64_t sp, int64_t row, int64_t H, hipStream_t s);
 // Server support: admit n <= DESC_CHUNK images (descriptors, owner ids, every tile
 // on the dirty list of round `round`), and mark the images that still have tiles on
 // a round's lists (busy[owner] = stamp).

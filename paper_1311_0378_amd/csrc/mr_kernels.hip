@@ -1874,6 +1874,30 @@ __global__ void k_put_descs(ImgDesc *dst, DescChunk c) {
 
 // ------------------------------------------------------------------ server
 
+// Copy a job's inputs into its planes: 16 bytes a lane from any address, a row's last
+// bytes one by one; blockIdx.y says which plane. Both planes of a 2048 x 2048 uint8 job
+// (16 MiB moved) cost its launch and little more.
+__global__ __launch_bounds__(256) void k_server_copy(char *a, const char *x, char *b,
+                                                     const char *y, int64_t dp, int64_t sp,
+                                                     int64_t row, uint32_t H) {
+    char *dst = blockIdx.y ? b : a;
+    const char *src = blockIdx.y ? y : x;
+    const uint32_t vec = (uint32_t)((row + 15) / 16), items = H * vec;
+    for (uint32_t i = blockIdx.x * 256u + threadIdx.x; i < items; i += gridDim.x * 256u) {
+        const uint32_t r = i / vec;
+        const int64_t c = 16 * (int64_t)(i - r * vec);
+        const char *p = src + r * sp + c;
+        char *o = dst + r * dp + c;
+        if (c + 16 <= row) {
+            v4u v;
+            __builtin_memcpy(&v, p, 16);
+            *(v4u *)o = v;
+        } else {
+            for (int64_t k = 0; c + k < row; ++k) o[k] = p[k];
+        }
+    }
+}
+
 // Admit images: image blockIdx.y's descriptor, owner[t] for its tiles, and every one
 // of its tiles on the dirty list of `round` (where it builds its initial
 // values). One thread per tile; a wave reserves its places in a band's list with
@@ -1933,6 +1957,15 @@ int persistent_grid() {
             g = 2048;
     }
     return g;
+}
+
+hipError_t launch_server_copy(void *a, const void *x, void *b, const void *y, int64_t dp,
+                              int64_t sp, int64_t row, int64_t H, hipStream_t s) {
+    const int64_t items = H * ((row + 15) / 16);
+    const dim3 grid((unsigned)std::min<int64_t>((items + 255) / 256, 2048), y ? 2 : 1);
+    hipLaunchKernelGGL(k_server_copy, grid, dim3(256), 0, s, (char *)a, (const char *)x, (char *)b,
+                       (const char *)y, dp, sp, row, (uint32_t)H);
+    return hipGetLastError();
 }
 
 hipError_t launch_server_admit(ImgDesc *descs, const int32_t *slots, const ImgDesc *d, int n,

@@ -189,6 +189,40 @@ def test_server_device_jobs_share_buffers(reader_first, steps):
     assert np.array_equal(x.cpu().numpy(), want), first_mismatch(x.cpu().numpy(), want)
 
 
+def queue_upload(srv, side=8192):
+    """A job that keeps the server's input copies busy for a millisecond or more."""
+    z = torch.zeros((side, side), dtype=torch.uint8, pin_memory=True)
+    return z, srv.submit(z, z)
+
+
+# Device jobs' inputs overwritten before their rounds have begun, by work on the server's
+# stream or after a wait for the device: each job still sees what it was submitted with.
+@pytest.mark.parametrize("wait", [False, True])
+def test_server_device_inputs_overwritten_after_submit(wait):
+    jobs = make_batch(8, seed=5, lo=60, hi=700)
+    want = [oracle_of(j, 8) for j in jobs]
+    dev = [(torch.from_numpy(a).to(DEV), torch.from_numpy(m).to(DEV) if m is not None else None)
+           for _, a, m in jobs]
+    srv = mrecon.Server(512 << 20, max_jobs=16)
+    torch.cuda.synchronize()
+    print(f"[gpu] server inputs overwritten wait={wait}", flush=True)
+    keep, big = queue_upload(srv)
+    ids = {srv.submit(a, m): i for i, (a, m) in enumerate(dev)}
+    if wait:
+        torch.cuda.synchronize()
+    for a, m in dev:
+        a.fill_(255)
+        if m is not None:
+            m.fill_(255)
+    srv.drain()
+    got = dict(srv.poll())
+    srv.close()
+    assert not got.pop(big).any() and sorted(got) == sorted(ids)
+    for jid, i in ids.items():
+        res = got[jid].cpu().numpy()
+        assert np.array_equal(res, want[i]), f"job {i}: " + first_mismatch(res, want[i])
+
+
 @pytest.mark.parametrize("conn", [4, 8])
 def test_server_device_jobs(conn):
     # jobs whose inputs and results are device memory (MR_JOB_DEVICE): the
