@@ -267,7 +267,10 @@ int mr_autotune(const mr_tile *tiles, int32_t n, mr_dtype t, int conn, void *ws,
  * are device-to-device, and no PCIe transfer is involved. The inputs are
  * copied when the job is submitted: work that the caller enqueues on `stream`
  * after mr_server_submit may overwrite them. A filled image may be written to
- * its result directly. */
+ * its result directly.
+ * A job's inputs may lie where another job's result goes: they are read as they
+ * were when the job was submitted, or, if the server had begun to write that
+ * result by then, with the whole of it. */
 enum { MR_JOB_DEVICE = 1 };
 typedef struct {
     const void *data; /* H x W: the marker (MR_OP_RECON) or the image (MR_OP_FILL) */

@@ -22,7 +22,9 @@
 //  - the caller's stream waits for a host job's input copies as soon as it is
 //    submitted, and so its admission does;
 //  - a finished job's epilogue and result copy wait for the round that
-//    finished it;
+//    finished it, and for the input copies of jobs submitted before it was
+//    retired that read where the result goes;
+//  - input copies wait for the results under way that they read;
 //  - a finished job's arena space, tile ids and slot are handed out again
 //    only once the host has seen its result copy complete, so no later
 //    upload, admission (which rewrites tile owners and the descriptor) or
@@ -128,6 +130,33 @@ struct Job {
     bool fill_direct = false; // the epilogue writes the result itself
 };
 
+// Where a job's rows lie in memory: H rows of `row` bytes, `ld` bytes apart (ld >= row).
+struct Plane {
+    uintptr_t p;
+    int64_t ld, row, H;
+};
+
+// Whether two planes share a byte; planes of different row pitch that overlap as
+// whole ranges count as sharing.
+bool share(const Plane &a, const Plane &b) {
+    auto end = [](const Plane &x) { return x.p + (uintptr_t)((x.H - 1) * x.ld + x.row); };
+    if (a.p >= end(b) || b.p >= end(a)) return false;
+    if (a.ld != b.ld) return true;
+    // b's row j and a's row i share bytes iff -b.row < d - k ld < a.row, with k = i - j
+    // and d the distance of the first rows: for k = floor(d / ld) or the next
+    const int64_t d = (int64_t)(b.p - a.p), q = d / a.ld - (d % a.ld < 0 ? 1 : 0);
+    const int64_t r = d - q * a.ld; // 0 <= r < ld
+    auto rows = [&](int64_t k) { return k > -b.H && k < a.H; };
+    return (r < a.row && rows(q)) || (r + b.row > a.ld && rows(q + 1));
+}
+
+// The result of a job on the device or returning, for jobs that read it.
+struct Result {
+    int32_t slot;
+    bool returning; // its copy (or epilogue) has been enqueued
+    Plane plane;
+};
+
 struct Returning {
     uint64_t id;
     int32_t slot;
@@ -162,8 +191,9 @@ struct mr_server {
     std::map<int32_t, Job> resident;  // slot -> job still working
     std::deque<Returning> returning;  // finished, result copy in flight
     std::deque<uint64_t> done;        // result copy complete, not yet polled
+    std::vector<Result> results;      // of the resident and the returning jobs
     std::vector<int32_t> admitted;    // slots whose jobs the next step puts on the lists
-    hipEvent_t ev_in = nullptr;       // the input copies of the last host job
+    hipEvent_t ev_in = nullptr;       // a job's input copies
     std::vector<hipEvent_t> ev_out;   // per slot
     hipEvent_t ev_round[2] = {nullptr, nullptr};
     uint32_t *h_busy = nullptr; // pinned, [2][max_jobs]: busy after the last step of each parity
@@ -253,6 +283,12 @@ int collect(mr_server *s, bool wait) {
         s->tiles.release((size_t)r.tile_base, (size_t)r.n_tiles);
         s->band_tiles[r.band] -= r.n_tiles;
         s->free_slots.push_back(r.slot);
+        for (Result &x : s->results)
+            if (x.slot == r.slot) {
+                x = s->results.back();
+                s->results.pop_back();
+                break;
+            }
         s->returning.pop_front();
     }
     return MR_OK;
@@ -401,21 +437,36 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
     const size_t hp = (size_t)(job->ld ? job->ld : job->W) * s->t;
     const bool device = (job->flags & MR_JOB_DEVICE) != 0;
     const bool recon = job->op == MR_OP_RECON;
-    hipError_t e;
-    if (device && on_device(s, job->data, hp, row, job->H) &&
-        (!recon || on_device(s, job->mask, hp, row, job->H))) {
-        e = launch_server_copy(p0, job->data, p1, recon ? job->mask : nullptr, (int64_t)dp,
-                               (int64_t)hp, (int64_t)row, job->H, s->stream);
-    } else {
-        const hipMemcpyKind in_kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
-        e = hipMemcpy2DAsync(p0, dp, job->data, hp, row, (size_t)job->H, in_kind, s->up);
-        if (e == hipSuccess && recon)
-            e = hipMemcpy2DAsync(p1, dp, job->mask, hp, row, (size_t)job->H, in_kind, s->up);
-        // (waited for here, not at the next step: what the caller enqueues on the
-        // stream after this call may overwrite the inputs)
-        if (e == hipSuccess) e = hipEventRecord(s->ev_in, s->up);
-        if (e == hipSuccess) e = hipStreamWaitEvent(s->stream, s->ev_in, 0);
+    const bool here = device && on_device(s, job->data, hp, row, job->H) &&
+                      (!recon || on_device(s, job->mask, hp, row, job->H));
+    const hipStream_t in = here ? s->stream : s->up; // the input copies' stream
+    // Another job's result may be written to one of these inputs. If that is under way,
+    // the copies wait for it; else it waits for them.
+    hipError_t e = hipSuccess;
+    bool held = false;
+    for (const Result &x : s->results) {
+        if (!share(Plane{(uintptr_t)job->data, (int64_t)hp, (int64_t)row, job->H}, x.plane) &&
+            !(recon && share(Plane{(uintptr_t)job->mask, (int64_t)hp, (int64_t)row, job->H}, x.plane)))
+            continue;
+        if (!x.returning)
+            held = true;
+        else if (e == hipSuccess)
+            e = hipStreamWaitEvent(in, s->ev_out[x.slot], 0);
     }
+    if (e == hipSuccess && here) {
+        e = launch_server_copy(p0, job->data, p1, recon ? job->mask : nullptr, (int64_t)dp,
+                               (int64_t)hp, (int64_t)row, job->H, in);
+    } else if (e == hipSuccess) {
+        const hipMemcpyKind in_kind = device ? hipMemcpyDeviceToDevice : hipMemcpyHostToDevice;
+        e = hipMemcpy2DAsync(p0, dp, job->data, hp, row, (size_t)job->H, in_kind, in);
+        if (e == hipSuccess && recon)
+            e = hipMemcpy2DAsync(p1, dp, job->mask, hp, row, (size_t)job->H, in_kind, in);
+    }
+    if (e == hipSuccess && (held || !here)) e = hipEventRecord(s->ev_in, in);
+    if (e == hipSuccess && held) e = hipStreamWaitEvent(s->down, s->ev_in, 0);
+    // (waited for here, not at the next step: what the caller enqueues on the stream
+    // after this call may overwrite the inputs)
+    if (e == hipSuccess && !here) e = hipStreamWaitEvent(s->stream, s->ev_in, 0);
     ImgDesc &d = j.d;
     d = ImgDesc{};
     d.H = job->H;
@@ -449,6 +500,9 @@ int mr_server_submit(mr_server *s, const mr_job *job, uint64_t *id) {
         s->band_tiles[j.band] -= j.n_tiles;
         return hip_err(e, "admit");
     }
+    const int64_t ldr = (job->ld_result ? job->ld_result : job->W) * s->t;
+    s->results.push_back(
+        Result{j.slot, false, Plane{(uintptr_t)job->result, ldr, (int64_t)row, job->H}});
     s->admitted.push_back(j.slot);
     s->free_slots.pop_back();
     ++s->next_id;
@@ -547,6 +601,8 @@ int mr_server_step(mr_server *s) {
                                                out_kind, s->down)) != hipSuccess) ||
                 (e = hipEventRecord(s->ev_out[slot], s->down)) != hipSuccess)
                 return hip_err(e, "result copy");
+            for (Result &x : s->results)
+                if (x.slot == slot) x.returning = true;
             s->returning.push_back(
                 Returning{j.id, slot, j.mem_off, j.mem_len, j.tile_base, j.n_tiles, j.band});
             s->resident.erase(slot);

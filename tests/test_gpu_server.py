@@ -223,6 +223,56 @@ def test_server_device_inputs_overwritten_after_submit(wait):
         assert np.array_equal(res, want[i]), f"job {i}: " + first_mismatch(res, want[i])
 
 
+def ring(side):
+    """An image whose hole is all of its inside."""
+    a = np.full((side, side), 255, np.uint8)
+    a[1:-1, 1:-1] = 0
+    return a
+
+
+# A reader of the buffer that a job submitted before it fills: the writer's rounds are done,
+# its result is not written yet, and the reader's input copies wait behind an upload.
+@pytest.mark.parametrize("steps", [0, 1])
+def test_server_result_waits_for_its_readers(steps):
+    x = torch.from_numpy(ring(300)).to(DEV)
+    marker = torch.full_like(x, 77)
+    out = torch.zeros_like(x)
+    srv = mrecon.Server(512 << 20, max_jobs=4)
+    torch.cuda.synchronize()
+    print(f"[gpu] result waits for its readers steps={steps}", flush=True)
+    srv.submit(x, None, mrecon.MR_OP_FILL, out=x)
+    for _ in range(steps):
+        srv.step()
+    torch.cuda.synchronize()
+    keep, _ = queue_upload(srv)
+    srv.submit(marker, x, mrecon.MR_OP_RECON, out=out)
+    srv.drain()
+    srv.close()
+    want = np.minimum(ring(300), 77)
+    assert np.array_equal(out.cpu().numpy(), want), first_mismatch(out.cpu().numpy(), want)
+    assert bool((x == 255).all())
+
+
+# A reader of a buffer that a finished job's result is on its way to, behind a larger
+# result: it sees the whole result.
+def test_server_reader_waits_for_a_result_under_way():
+    full = torch.full((8192, 8192), 255, dtype=torch.uint8, pin_memory=True)
+    x = torch.zeros((300, 300), dtype=torch.uint8, pin_memory=True)
+    srv = mrecon.Server(512 << 20, max_jobs=4)
+    print("[gpu] reader waits for a result under way", flush=True)
+    srv.submit(full)
+    srv.submit(torch.from_numpy(ring(300)).pin_memory(), out=x)
+    srv.step()
+    torch.cuda.synchronize()
+    srv.step()  # both results are enqueued, the larger one first
+    j = srv.submit(x)
+    srv.drain()
+    res = dict(srv.poll())[j].numpy()
+    srv.close()
+    assert (x.numpy() == 255).all()
+    assert (res == 255).all(), first_mismatch(res, np.full_like(res, 255))
+
+
 @pytest.mark.parametrize("conn", [4, 8])
 def test_server_device_jobs(conn):
     # jobs whose inputs and results are device memory (MR_JOB_DEVICE): the
