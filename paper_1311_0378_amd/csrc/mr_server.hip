@@ -519,18 +519,19 @@ int mr_server_step(mr_server *s) {
     for (const auto &r : s->resident) // (planes the staged loads do not reach)
         if ((uint64_t)r.second.plane > STAGE_MAX_BYTES) imgs.staged = 0;
     // 0. put the jobs submitted since the last step on the next round's lists
-    for (size_t i = 0; i < s->admitted.size(); i += DESC_CHUNK) {
-        const int n = (int)std::min<size_t>(DESC_CHUNK, s->admitted.size() - i);
+    while (!s->admitted.empty()) {
+        const int n = (int)std::min<size_t>(DESC_CHUNK, s->admitted.size());
         ImgDesc d[DESC_CHUNK];
-        for (int k = 0; k < n; ++k) d[k] = s->resident[s->admitted[i + k]].d;
+        for (int k = 0; k < n; ++k) d[k] = s->resident[s->admitted[k]].d;
         const uint32_t r = s->round;
-        if ((e = launch_server_admit(s->descs, &s->admitted[i], d, n, s->owner, s->flags,
+        if ((e = launch_server_admit(s->descs, s->admitted.data(), d, n, s->owner, s->flags,
                                      s->lists + (size_t)(r & 1) * s->n_tiles,
                                      s->counts + (r % RING) * NBANDS, s->n_tiles, r, s->stream)) !=
             hipSuccess)
             return hip_err(e, "admit");
+        // (one by one: after a failed launch the next step must not list these again)
+        s->admitted.erase(s->admitted.begin(), s->admitted.begin() + n);
     }
-    s->admitted.clear();
     // 1. launch the step's rounds over every resident job (including those
     //    admitted since the last step); the host does not wait for them here
     uint32_t launched = 0;
