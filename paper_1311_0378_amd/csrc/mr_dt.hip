@@ -15,7 +15,7 @@
 // gives every pixel of its 96 x 96 interior its distance where that is at most
 // DW_MAX, and that value is final, because a background pixel outside the
 // window is further away than that. Pixels further from the background start
-// unreached (infinity), and the tiles that hold one are listed.
+// unreached (infinity), and the tiles where they meet settled ones are listed.
 // Those are left to rounds over 64 x 64 register tiles (a 62 x 62
 // interior and a one-pixel halo) held by one wave each: lane = column,
 // register = row. A visit loads the tile,
@@ -289,7 +289,7 @@ __global__ __launch_bounds__(64 * DW_WAVES) void k_dt_first(
         return __ballot((ok[0] && a != 0) || (ok[1] && b != 0)) != 0;
     };
     const bool some = inside_any();
-    bool far = false;
+    bool far = false, last = false; // last: E ends eroded DW_MAX times
     if (some) {
         uint32_t S[DW_SLICES][2][4];
 #pragma unroll
@@ -305,11 +305,12 @@ __global__ __launch_bounds__(64 * DW_WAVES) void k_dt_first(
 #pragma unroll
         for (int k = 1; k <= DW_MAX; ++k) {
             erode_once<CONN>(E);
+            last = k == DW_MAX; // what is left is further than DW_MAX
             if (!inside_any()) {
                 far = false;
                 break;
             }
-            if (k == DW_MAX) break; // what is left is further than DW_MAX
+            if (last) break;
 #pragma unroll
             for (int j = 0; j < DW_SLICES; ++j)
                 if ((k + 1) % (1 << j) == 0)
@@ -372,25 +373,50 @@ __global__ __launch_bounds__(64 * DW_WAVES) void k_dt_first(
             }
         }
     }
-    if (!far) return;
-    // list for round 2 the register tiles (DI x DI interiors) that hold one of
-    // this interior's unsettled pixels: at most 3 x 3 of them
-    const int64_t ty0 = y0 / DI, tx0 = x0 / DI;
+    if (!last) return;
+    // List for round 2 the register tiles (DI x DI interiors) that hold an unsettled
+    // pixel next to a settled one: only there can a visit change anything yet, and
+    // the wave goes on from there (an image of one large object without background
+    // has none: 8192 x 8192 297 us with all its tiles listed). Looked for in the
+    // interior and the pixels around it: a pixel of the interior counts as settled
+    // only if it is, and one around it as unsettled if it is, so of each such pair
+    // the window whose interior holds the settled pixel finds the other. At most
+    // 3 x 3 tiles.
+    uint32_t next[2][4];
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) next[r][i] = E[r][i];
+    erode_once<CONN>(next);
+    const int f_lo = std::max(c_lo, DW_MARGIN - 1), f_hi = std::min(c_hi, DW_MARGIN + DW_IN + 1);
+    const int g_lo = std::max(r_lo, DW_MARGIN - 1), g_hi = std::min(r_hi, DW_MARGIN + DW_IN + 1);
+    uint32_t any = 0;
+#pragma unroll
+    for (int r = 0; r < 2; ++r)
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const bool in = 2 * lane + r >= g_lo && 2 * lane + r < g_hi;
+            E[r][i] = in ? E[r][i] & ~next[r][i] & cols(f_lo, f_hi, i) : 0u;
+            any |= E[r][i];
+        }
+    if (__ballot(any != 0) == 0) return;
+    const int64_t ty0 = (y0 > 0 ? y0 - 1 : 0) / DI, tx0 = (x0 > 0 ? x0 - 1 : 0) / DI;
     bool want = false;
 #pragma unroll 1
     for (int q = 0; q < 9; ++q) {
-        const int64_t ty = ty0 + q / 3, tx = tx0 + q % 3;
-        const int a = (int)(tx * DI - wx0), b = a + DI; // its columns in the window
-        const int64_t ra = ty * DI - y0, rb = ra + DI;  // its interior rows
+        // the tile's columns and rows in the window
+        const int a = (int)((tx0 + q % 3) * DI - wx0), b = a + DI;
+        const int ra = (int)((ty0 + q / 3) * DI - wy0), rb = ra + DI;
         uint32_t hit[2] = {0, 0};
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const uint32_t m = cm[i] & cols(a, b, i);
+            const uint32_t m = cols(a, b, i);
             hit[0] |= E[0][i] & m;
             hit[1] |= E[1][i] & m;
         }
-        const bool here = (ok[0] && ir >= ra && ir < rb && hit[0] != 0) ||
-                          (ok[1] && ir + 1 >= ra && ir + 1 < rb && hit[1] != 0);
+        const int y = 2 * lane;
+        const bool here =
+            (y >= ra && y < rb && hit[0] != 0) || (y + 1 >= ra && y + 1 < rb && hit[1] != 0);
         const bool listed = __ballot(here) != 0;
         if (lane == q) want = listed;
     }

@@ -298,6 +298,24 @@ def test_area_threshold_words(H, W, p):
             check(ws[: 4 * (H * W + 1)].view(torch.int32).cpu().numpy(), n.astype(np.int32))
 
 
+# Tiles are first visited where the first pass's last settled distance, 16, meets further
+# pixels: one background pixel at every place around the corner of four windows, so that
+# the ring of that distance crosses window and tile borders in every phase.
+@pytest.mark.parametrize("conn", [4, 8])
+def test_dt_front_across_windows(conn):
+    H, W = 211, 223
+    y, x = torch.arange(H, device=DEV)[:, None], torch.arange(W, device=DEV)[None]
+    img = torch.full((H, W), 9, dtype=torch.uint8, device=DEV)
+    print(f"[gpu] dt front conn{conn}", flush=True)
+    for cy in range(76, 116):
+        for cx in range(78, 115, 1 + cy % 3):
+            img[cy, cx] = 0
+            dy, dx = (y - cy).abs(), (x - cx).abs()
+            want = (torch.maximum(dy, dx) if conn == 8 else dy + dx).to(torch.int32)
+            assert torch.equal(ops.distance_transform(img, conn), want), (cy, cx)
+            img[cy, cx] = 9
+
+
 # The distance transform's first pass settles distances up to 16 in windows of
 # 96 x 96 pixels (16 more on each side): distances around that bound, deep
 # objects that later rounds finish, background only in a margin or only far
