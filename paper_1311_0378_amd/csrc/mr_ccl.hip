@@ -587,8 +587,15 @@ __global__ __launch_bounds__(256) void k_area_count(const int32_t *__restrict__ 
 // any length; else W and the pitch are multiples of 4. A wave's chunk is 64
 // words; runs are found across it, and a run that spans two chunks is added
 // in two parts.
-constexpr int AREA_UNROLL = 2;
+constexpr int AREA_UNROLL = 2;   // chunks of the count loaded together
+constexpr int FILTER_UNROLL = 4; // words of the filter
+constexpr uint32_t AREA_GROUP = 32; // most chunks a wave of the filter takes
 constexpr unsigned AREA_BLOCKS = 1u << 22;
+// The one-pixel kernels walk the plane with this many blocks at most: waves that run
+// together then lie far apart, and fewer of them add to one label's counter at once
+// (16384 x 16377 labels, rows 16384 apart, squares of 300 pixels: 1661 us, 2299 us with
+// a block for every 256 pixels).
+constexpr int64_t AREA_PIXEL_BLOCKS = 1 << 16;
 
 template <bool LIN>
 __device__ __forceinline__ int64_t area_word(uint32_t i, uint32_t Wq, int64_t pitch) {
@@ -601,17 +608,25 @@ __device__ __forceinline__ int64_t area_word(uint32_t i, uint32_t Wq, int64_t pi
 // lane, else at the first head of the next lane that has one, else at the
 // chunk's end. AREA_UNROLL chunks are loaded at a time. With `marks`, each
 // chunk leaves a mask of its words that hold a countable label, so that the
-// filter reads only those. Bound by the label read: 197 us on 16384 x 16384
-// labels (5.4 TB/s). One pass of two chunks a wave: four chunks, or a fixed
-// grid of 4096 blocks walking the plane, made the call 1 and 13 % slower.
+// filter reads only those. Bound by the label read: 217 us on 16384 x 16384
+// labels, 1.6 % of them foreground (4.9 TB/s). One pass of two chunks a wave: four
+// chunks, or a fixed grid of 4096 blocks walking the plane, made the call 1 and 13 %
+// slower. On dense labels the atomics bound it: blocks take a large plane in eight bands, so
+// that those which run together add to fewer of the same counters (squares of 300
+// pixels 509 -> 269 us), and a chunk of short runs goes through LDS, so that an atomic
+// instruction's lanes hold neighbouring pixels, whose labels often share a cache line
+// (one-pixel stripes at 11584 x 11584 901 -> 552 us; the two cost 1.6 % foreground 5 us).
 template <bool LIN>
 __global__ __launch_bounds__(256) void k_area_count4(const int32_t *__restrict__ labels,
                                                      uint32_t N, uint32_t NQ, uint32_t Wq,
                                                      int64_t pitch, int32_t *__restrict__ area,
-                                                     uint64_t *__restrict__ marks) {
+                                                     uint64_t *__restrict__ marks,
+                                                     uint32_t bands) {
+    __shared__ int4 runs[4][2][64];
     const int lane = threadIdx.x & 63;
     const uint32_t chunks = (NQ + 63) / 64;
-    const uint32_t wave = blockIdx.x * 4u + (threadIdx.x >> 6), waves = gridDim.x * 4u;
+    const uint32_t blk = blockIdx.x % bands * (gridDim.x / bands) + blockIdx.x / bands;
+    const uint32_t wave = blk * 4u + (threadIdx.x >> 6), waves = gridDim.x * 4u;
     for (uint32_t c0 = wave * AREA_UNROLL; c0 < chunks; c0 += waves * AREA_UNROLL) {
         int4 qs[AREA_UNROLL];
 #pragma unroll
@@ -644,13 +659,30 @@ __global__ __launch_bounds__(256) void k_area_count4(const int32_t *__restrict__
             const int fn = __shfl(first, ln);
             const int next = later ? 4 * ln + fn : 4 * (64 - __builtin_clzll(valid));
             const int32_t lv[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                if (!((hm >> j) & 1u)) continue;
+            auto run = [&](int j) -> int32_t { // pixels of the run that label j starts
                 const uint32_t rest = hm >> (j + 1);
                 const int end = rest ? 4 * lane + j + 1 + __builtin_ctz(rest) : next;
-                if (counts(lv[j])) atomicAdd(area + lv[j], end - (4 * lane + j));
+                return end - (4 * lane + j);
+            };
+            if (__popcll(__ballot((hm & (hm - 1)) != 0)) > 16) {
+                int4 *L = runs[threadIdx.x >> 6][0], *C = runs[threadIdx.x >> 6][1];
+                int32_t len[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) len[j] = (hm >> j) & 1u && counts(lv[j]) ? run(j) : 0;
+                L[lane] = q;
+                C[lane] = int4{len[0], len[1], len[2], len[3]};
+                ccl_wave_sync();
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int32_t c = ((const int32_t *)C)[64 * j + lane];
+                    if (c) atomicAdd(area + ((const int32_t *)L)[64 * j + lane], c);
+                }
+                ccl_wave_sync();
+                continue;
             }
+#pragma unroll
+            for (int j = 0; j < 4; ++j)
+                if ((hm >> j) & 1u && counts(lv[j])) atomicAdd(area + lv[j], run(j));
         }
     }
     // LIN: the labels past the last whole word
@@ -678,19 +710,21 @@ __global__ __launch_bounds__(256) void k_area_filter(int32_t *__restrict__ label
 
 // The word path of the filter: a word's 4 counter reads are in flight
 // together, and it is written back only if one of its labels was cleared. With
-// `marks` (see the count) a wave takes `group` chunks (64 of a large plane, fewer
+// `marks` (see the count) a wave takes `group` chunks (32 of a large plane, fewer
 // of a smaller one, so that it still spreads over the chip), lists the words that
-// hold a label in LDS and gives each lane one of them, so that planes of mostly
-// background are not read again; a wave whose words are mostly marked, and
-// planes without marks, go chunk by chunk. 16384 x 16384 labels, 1.6 % of
-// them foreground: 22 us with marks, 222 us reading every word.
+// hold a label in LDS and deals them to its lanes, so that planes of mostly
+// background are not read again; a wave with too many marked words (half of a large
+// group's, three quarters of a small one's) and planes without marks go chunk by chunk. 16384 x 16384 labels: 1.6 % of
+// them foreground 25 us with marks, 222 us reading every word; squares of 300
+// pixels 412 us (535 us with 64 chunks a wave and one word a lane at a time; with four
+// words a lane, 64 chunks take 21 and 446 us, 16 chunks 38 and 394 us).
 template <bool LIN>
 __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labels, uint32_t N,
                                                       uint32_t NQ, uint32_t Wq, int64_t pitch,
                                                       const int32_t *__restrict__ area, int64_t lo,
                                                       int64_t hi, uint32_t group,
                                                       const uint64_t *__restrict__ marks) {
-    constexpr uint32_t LIST = 2048; // listed words of a wave's 4096
+    constexpr uint32_t LIST = AREA_GROUP * 32; // listed words of a wave's AREA_GROUP * 64
     __shared__ uint16_t lists[4][LIST];
     const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
     uint16_t *list = lists[wv];
@@ -707,10 +741,8 @@ __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labe
         if (o.x != l.x || o.y != l.y || o.z != l.z || o.w != l.w) *p = o;
     };
     for (uint32_t c0 = wave * group; c0 < chunks; c0 += waves * group) {
-        uint64_t w = (uint32_t)lane < group && c0 + lane < chunks ? ~0ull : 0ull;
-        uint32_t total = LIST + 1;
         if (marks) {
-            if (w) w = marks[c0 + lane];
+            const uint64_t w = (uint32_t)lane < group && c0 + lane < chunks ? marks[c0 + lane] : 0ull;
             const uint32_t n = (uint32_t)__popcll(w);
             uint32_t end = n;
 #pragma unroll
@@ -718,32 +750,40 @@ __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labe
                 const uint32_t o = __shfl_up(end, k);
                 if (lane >= k) end += o;
             }
-            total = __shfl(end, 63);
-            if (total <= LIST) {
+            const uint32_t total = __shfl(end, 63);
+            if (total <= LIST && 4 * total <= 3 * 64 * group) {
                 uint32_t e = end - n;
                 for (uint64_t u = w; u; u &= u - 1)
                     list[e++] = (uint16_t)(lane * 64 + __builtin_ctzll(u));
                 ccl_wave_sync();
-                for (uint32_t i = lane; i < total; i += 64) {
-                    int4 *p = at(c0 * 64u + list[i]);
-                    filter(p, *p);
+                for (uint32_t i = lane; i < total; i += 64 * FILTER_UNROLL) {
+                    int4 *p[FILTER_UNROLL], q[FILTER_UNROLL];
+#pragma unroll
+                    for (int j = 0; j < FILTER_UNROLL; ++j) {
+                        p[j] = at(c0 * 64u + list[std::min(i + 64 * j, total - 1)]);
+                        q[j] = int4{0, 0, 0, 0};
+                        if (i + 64 * j < total) q[j] = *p[j];
+                    }
+#pragma unroll
+                    for (int j = 0; j < FILTER_UNROLL; ++j)
+                        if (i + 64 * j < total) filter(p[j], q[j]);
                 }
                 ccl_wave_sync();
                 continue;
             }
         }
-        for (uint32_t k = 0; k < group; k += AREA_UNROLL) {
-            int4 q[AREA_UNROLL];
+        for (uint32_t k = 0; k < group; k += FILTER_UNROLL) {
+            int4 q[FILTER_UNROLL];
 #pragma unroll
-            for (int j = 0; j < AREA_UNROLL; ++j) {
+            for (int j = 0; j < FILTER_UNROLL; ++j) {
                 const uint32_t i = (c0 + k + j) * 64u + lane;
                 q[j] = int4{0, 0, 0, 0};
-                if (i < NQ) q[j] = *at(i);
+                if (k + j < group && i < NQ) q[j] = *at(i);
             }
 #pragma unroll
-            for (int j = 0; j < AREA_UNROLL; ++j) {
+            for (int j = 0; j < FILTER_UNROLL; ++j) {
                 const uint32_t i = (c0 + k + j) * 64u + lane;
-                if (i < NQ) filter(at(i), q[j]);
+                if (k + j < group && i < NQ) filter(at(i), q[j]);
             }
         }
     }
@@ -754,8 +794,8 @@ __global__ __launch_bounds__(256) void k_area_filter4(int32_t *__restrict__ labe
     }
 }
 
-unsigned grid_for(int64_t items) {
-    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, 1 << 22));
+unsigned grid_for(int64_t items, int64_t most) {
+    return (unsigned)std::max<int64_t>(1, std::min<int64_t>((items + 255) / 256, most));
 }
 
 // The word path's marks, one bit per 16-byte word of labels, behind the areas.
@@ -837,7 +877,7 @@ int mr_area_threshold(void *labels_inout, int64_t H, int64_t W, int64_t pitch, i
         return cfail(MR_ENOMEM, "workspace too small: %zu bytes given, %zu needed", ws_bytes, need);
     hipStream_t s = (hipStream_t)stream;
     int32_t *area = (int32_t *)ws;
-    hipLaunchKernelGGL(k_area_clear, dim3(grid_for(H * W / 4 + 1)), dim3(256), 0, s, area, H * W + 1);
+    hipLaunchKernelGGL(k_area_clear, dim3(grid_for(H * W / 4 + 1, 1 << 22)), dim3(256), 0, s, area, H * W + 1);
     const uint32_t N = (uint32_t)(H * W), NQ = N / 4;
     const bool lin = pitch == W;
     if (NQ > 0 && (lin || (W % 4 == 0 && pitch % 4 == 0)) && (uintptr_t)labels_inout % 16 == 0) {
@@ -847,26 +887,29 @@ int mr_area_threshold(void *labels_inout, int64_t H, int64_t W, int64_t pitch, i
         // against 4.8 us)
         uint64_t *marks = chunks >= 16384 && ws_bytes >= need + area_marks_bytes(H * W)
                               ? (uint64_t *)((char *)ws + need) : nullptr;
-        const unsigned gc = std::min<unsigned>((chunks + 4 * AREA_UNROLL - 1) / (4 * AREA_UNROLL),
-                                               AREA_BLOCKS);
-        // chunks a wave of the filter takes: 4 waves a SIMD before it grows
-        const uint32_t group = std::max((uint32_t)AREA_UNROLL, std::min(64u, chunks / 4096 / 4 * 4));
+        // (2048 x 2048 labels, whose words still lie in the dies' L2s: 19 us in order, 25 us
+        // in bands; squares of 300 pixels at 6000 x 6000 195 us in order, 172 us in bands)
+        const uint32_t bands = chunks >= 131072 ? 8 : 1;
+        const unsigned gc = (std::min<unsigned>((chunks + 4 * AREA_UNROLL - 1) / (4 * AREA_UNROLL),
+                                                AREA_BLOCKS) + bands - 1) / bands * bands;
+        // chunks a wave of the filter takes: 8 waves a SIMD before it grows
+        const uint32_t group = std::max(1u, std::min(AREA_GROUP, chunks / 8192u));
         const unsigned gf = std::min<unsigned>((chunks + 4 * group - 1) / (4 * group), AREA_BLOCKS);
         if (lin) {
             hipLaunchKernelGGL(k_area_count4<true>, dim3(gc), dim3(256), 0, s, l, N, NQ, wq, pitch,
-                               area, marks);
+                               area, marks, bands);
             hipLaunchKernelGGL(k_area_filter4<true>, dim3(gf), dim3(256), 0, s, l, N, NQ, wq, pitch,
                                (const int32_t *)area, min_area, max_area, group, marks);
         } else {
             hipLaunchKernelGGL(k_area_count4<false>, dim3(gc), dim3(256), 0, s, l, N, NQ, wq, pitch,
-                               area, marks);
+                               area, marks, bands);
             hipLaunchKernelGGL(k_area_filter4<false>, dim3(gf), dim3(256), 0, s, l, N, NQ, wq,
                                pitch, (const int32_t *)area, min_area, max_area, group, marks);
         }
     } else {
-        hipLaunchKernelGGL(k_area_count, dim3(grid_for(H * W)), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_area_count, dim3(grid_for(H * W, AREA_PIXEL_BLOCKS)), dim3(256), 0, s,
                            (const int32_t *)labels_inout, H, W, pitch, area);
-        hipLaunchKernelGGL(k_area_filter, dim3(grid_for(H * W)), dim3(256), 0, s,
+        hipLaunchKernelGGL(k_area_filter, dim3(grid_for(H * W, AREA_PIXEL_BLOCKS)), dim3(256), 0, s,
                            (int32_t *)labels_inout, H, W, pitch, (const int32_t *)area,
                            min_area, max_area);
     }

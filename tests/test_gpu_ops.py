@@ -384,3 +384,33 @@ def test_gapless_rows_and_lowered_marker(shape, dt):
                 check(ops.hdome(d, h, 4).cpu().numpy(), oracle.hdome(img, h, 4), f"h={h}: ")
     rgb = rng.integers(0, 256, (*shape, 3)).astype(np.uint8)
     check(ops.rgb2gray(torch.from_numpy(rgb).to(DEV)).cpu().numpy(), oracle.rgb2gray(rgb))
+
+
+# Area threshold planes whose filter waves take 2, 4 and 32 chunks of 64 words, with parts
+# of every kind: background, single labels, short runs, long runs, labels out of range.
+@pytest.mark.parametrize("H,W,pad", [(2100, 2003, 0), (2100, 2004, 8), (3001, 3001, 0),
+                                     (8200, 8193, 0)])
+def test_area_threshold_mixed_planes(H, W, pad):
+    n = H * W
+    g = torch.Generator(device=DEV).manual_seed(n)
+    lab = torch.zeros((H, W + pad), dtype=torch.int32, device=DEV)[:, :W]
+    q = H // 5
+    one = torch.rand((q, W), generator=g, device=DEV) < 0.01
+    lab[:q][one] = torch.randint(1, n + 1, (int(one.sum()),), generator=g, device=DEV,
+                                 dtype=torch.int32)
+    x = torch.arange(W, device=DEV, dtype=torch.int32)
+    lab[q : 2 * q] = torch.where(x % 2 == 0, x + 1, 0)
+    lab[2 * q : 3 * q] = (x // 7 + 5) * ((x // 7) % 3 != 0)
+    lab[3 * q : 4 * q] = n - x // 300
+    lab[4 * q :: 3] = torch.where(x % 5 < 2, n + 1 + x, -x)
+    print(f"[gpu] area threshold {H}x{W}+{pad}", flush=True)
+    ok = (lab > 0) & (lab <= n)
+    areas = torch.bincount(lab[ok].long(), minlength=n + 1)
+    k = areas[lab.clamp(0, n).long()]
+    for lo, hi in ((2, 5 * q), (q * 2, 10**9)):
+        want = torch.where(ok & ((k < lo) | (k > hi)), 0, lab)
+        d = lab.clone() if pad == 0 else torch.empty_like(lab.as_strided((H, W + pad), (W + pad, 1)))[:, :W]
+        d.copy_(lab)
+        _, ws = ops.area_threshold(d, lo, hi)
+        assert torch.equal(d, want), (lo, hi)
+        assert torch.equal(ws[: 4 * (n + 1)].view(torch.int32), areas.to(torch.int32)), (lo, hi)
