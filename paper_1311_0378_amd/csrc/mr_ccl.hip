@@ -64,12 +64,16 @@ typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
 
 constexpr int CT = 64;              // tile side: a row is one 64-bit mask, lane = row
 constexpr int CT_RUNS = CT / 2;     // a row holds at most this many runs
+constexpr int CT_NODES = CT_RUNS + 1; // a row's nodes, one unused: rows lie a bank apart
 constexpr int CT_WAVES = 4;         // tiles (waves) per workgroup
 // Fewer tiles than this: a workgroup each, so that every CU gets one, and the
 // last pass takes CT_WAVES waves a tile. 2048 x 2048 (1024 tiles), label and area
 // threshold: 36.1 us so, 38.4 us with four tiles a workgroup; 4096 x 2048 the same
 // (46.1 us); 16384 x 16384 (65536 tiles) 742 us so, 695 us with four.
 constexpr uint32_t CT_FEW = 2048;
+constexpr int WALKS = 4;            // walks to a root that a lane of the last pass makes at once
+constexpr int CT_DENSE = 4;         // runs of a row above which a tile's workgroup shares it
+constexpr uint32_t RANK = 1u << 31; // there: a place in the run list, not a label (below 2^31)
 
 // ------------------------------------------------------------- local phase
 
@@ -85,10 +89,15 @@ __device__ __forceinline__ uint32_t lds_load(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
 }
 
-__device__ __forceinline__ uint32_t lfind(const uint32_t *P, uint32_t x) {
+// The root of x's tree in the tile's LDS forest. Each second node passed is put below
+// its parent's parent (plain stores, see gfind).
+__device__ __forceinline__ uint32_t lfind(uint32_t *P, uint32_t x) {
     uint32_t p = lds_load(P + x);
     while (p != x) {
-        x = p;
+        const uint32_t g = lds_load(P + p);
+        if (g == p) return p;
+        __hip_atomic_store(P + x, g, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP);
+        x = g;
         p = lds_load(P + x);
     }
     return x;
@@ -128,7 +137,7 @@ __device__ __forceinline__ int run_start(uint64_t m, int x) {
 // column (two runs of a row start at least two columns apart). Nodes are
 // ordered like the runs' first pixels.
 __device__ __forceinline__ uint32_t run_node(int row, uint64_t m, int x) {
-    return (uint32_t)(row * CT_RUNS + (run_start(m, x) >> 1));
+    return (uint32_t)(row * CT_NODES + (run_start(m, x) >> 1));
 }
 
 // The tile of this wave: its place and size in the image (32-bit: H * W is
@@ -157,40 +166,149 @@ struct CclTile {
     }
 };
 
-// One wave per tile. Four lanes read a row (16 pixels each; a load
-// instruction covers 16 rows), so the wave's whole tile is in flight with
-// four loads a lane, and each lane packs its pixels' foreground into 16 bits.
-// A tile without foreground stores its empty masks and is done. Otherwise lane
-// = row: a run makes one union per run above it that it touches, made at the
+// The unions of one tile from its row masks, by TW waves (thread th of them), and its
+// forest entries. A thread has a row (TW = 1), or those runs of a row that begin in
+// 16 of its columns. A run makes one union per run above it that it touches, made at the
 // first pixel that reaches that run: with 4-connectivity a common column
 // whose left neighbour is not common; with 8-connectivity a run's first pixel
 // takes the run above it or above-left of it, and every later pixel only the
 // run that begins above-right of it.
 // A run's first union takes no atomic: the run is put below the run above it,
-// and the chains that this makes down the tile's rows are halved three times
-// before they are walked (512 x 3712 pixels, 20 % foreground: 7.0 us, 15.8 us
-// with every union by walk and atomic minimum).
-// Bound by the image read: 16384 x 16384 uint8 with 1.6 % foreground takes 78 us
+// and the chains that this makes down the tile's rows are halved three times (by four
+// waves until they are flat) before they are walked (512 x 3712 pixels, 20 %
+// foreground: 7.0 us, 15.8 us with every union by walk and atomic minimum).
+template <int CONN, int TW>
+__device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, uint32_t *P,
+                                         const uint64_t *row_of, uint32_t *__restrict__ F) {
+    auto sync = [] {
+        if (TW == 1) ccl_wave_sync();
+        else __syncthreads();
+    };
+    auto any = [](bool x) -> bool { return TW == 1 ? __ballot(x) != 0 : __syncthreads_or(x); };
+    const int row = TW == 1 ? th : th >> 2;
+    const uint64_t mine = TW == 1 ? ~0ull : 0xFFFFull << (16 * (th & 3));
+    const uint64_t m = row_of[row];
+    const uint64_t up = row > 0 ? row_of[row - 1] : 0ull;
+    const uint64_t first = m & ~(m << 1); // the runs' first pixels
+    const uint64_t s = first & mine;
+    // Columns at which a run makes a union: with the run above at the column
+    // itself (uC), or above-left (uL) or above-right (uR) of it.
+    uint64_t uC, uL = 0, uR = 0;
+    if (CONN == 4) {
+        uC = m & up;
+        uC &= ~(uC << 1);
+    } else {
+        uL = first & (up << 1);
+        uC = first & up & ~(up << 1);
+        uR = m & (up >> 1) & ~up;
+    }
+    // the node of the run above that column x unites with (first: at x itself or
+    // to its left, else to its right)
+    auto above = [&](int x, bool right) -> uint32_t {
+        return run_node(row - 1, up, right ? x + 1 : ((uL >> x) & 1) ? x - 1 : x);
+    };
+    // A run starts below the first run it unites with, which takes no atomic; the
+    // chains this makes down the rows are halved three times before anyone
+    // walks them; what a run touches besides is united then.
+    const uint64_t at = uC | uL;
+    uint64_t left = 0, right = 0; // what is left to unite
+    for (uint64_t u = s; u; u &= u - 1) {
+        const int x = __builtin_ctzll(u);
+        const uint32_t node = (uint32_t)(row * CT_NODES + (x >> 1));
+        // this run's columns
+        const uint64_t gap = ~m & ~((2ull << x) - 1);
+        const uint64_t run = (gap ? (gap & -gap) - 1 : ~0ull) & ~((1ull << x) - 1);
+        uint64_t l = at & run, r = uR & run;
+        uint32_t parent = node;
+        if (l) {
+            parent = above(__builtin_ctzll(l), false);
+            l &= l - 1;
+        } else if (r) {
+            parent = above(__builtin_ctzll(r), true);
+            r &= r - 1;
+        }
+        left |= l;
+        right |= r;
+        P[node] = parent;
+    }
+    sync();
+#pragma unroll 1
+    for (int k = 0; k < (TW == 1 ? 3 : 6); ++k) {
+        bool moved = false;
+        for (uint64_t u = s; u; u &= u - 1) {
+            const uint32_t node = (uint32_t)(row * CT_NODES + (__builtin_ctzll(u) >> 1));
+            const uint32_t p = P[node], g = P[p];
+            P[node] = g;
+            moved |= g != p;
+        }
+        if (TW > 1 && !any(moved)) break;
+        sync();
+    }
+    if (TW > 1 || __ballot((left | right) != 0)) {
+        for (uint64_t u = left; u; u &= u - 1) {
+            const int x = __builtin_ctzll(u);
+            lunion(P, run_node(row, m, x), above(x, false));
+        }
+        for (uint64_t u = right; u; u &= u - 1) {
+            const int x = __builtin_ctzll(u);
+            lunion(P, run_node(row, m, x), above(x, true));
+        }
+    }
+    sync();
+    // the forest entry of a node's root: root's linear index + 1
+    auto entry = [&](uint32_t node) -> uint32_t {
+        const uint32_t r = lfind(P, node);
+        const uint32_t rr = r / CT_NODES, k = 2 * (r - rr * CT_NODES);
+        const uint64_t rm = row_of[rr];
+        // the run starts at column k, or else at k + 1
+        const uint32_t x = k + (((rm & ~(rm << 1)) >> k & 1) ? 0 : 1);
+        return T.first + rr * W + x + 1u;
+    };
+    for (uint64_t u = s; u; u &= u - 1) {
+        const int x = __builtin_ctzll(u);
+        F[T.first + row * W + x] = entry(row * CT_NODES + (x >> 1));
+    }
+    if (m >> 63 && (TW == 1 || (th & 3) == 3)) F[T.first + row * W + 63] = entry(run_node(row, m, 63));
+    // first and last row, lane = column
+    const int lane = threadIdx.x & 63;
+    const uint64_t m0 = row_of[0], m1 = row_of[T.h - 1];
+    if ((TW == 1 || th < 64) && (m0 >> lane) & 1) F[T.first + lane] = entry(run_node(0, m0, lane));
+    if ((TW == 1 || th >= 192) && (m1 >> lane) & 1)
+        F[T.first + (T.h - 1) * W + lane] = entry(run_node((int)T.h - 1, m1, lane));
+}
+
+// TW waves per tile. Four threads read a row (16 pixels each; a wave's load
+// instruction covers 16 rows), so the whole tile is in flight with at most
+// four loads a thread, and each thread packs its pixels' foreground into 16 bits.
+// A tile without foreground stores its empty masks and is done, the others make their
+// unions. Bound by the image read: 16384 x 16384 uint8 with 1.6 % foreground takes 78 us
 // (3.4 TB/s of image). Per-pixel lanes on 32 x 64 tiles that loaded one byte a
 // lane and stored every pixel's forest entry took 533 us.
-template <int CONN, int CT_WAVES>
+// Dense tiles are bound by the walks in LDS: node rows one bank apart, and nodes passed on
+// a walk put below their parent's parent, take 4096 x 4096 one-pixel stripes from 234 to
+// 77 us, half foreground at random (conn 8) from 72 to 53 us. With few tiles, whose time is one
+// tile's, four waves share a tile with rows of many runs: 300 x 411 pixels, half of them
+// foreground at random, 33 -> 19 us.
+template <int CONN, int TW>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__restrict__ img,
                                                              uint32_t H, uint32_t W, int64_t pitch,
                                                              uint32_t tiles_x, uint32_t n_tiles,
                                                              uint32_t *__restrict__ labels,
                                                              int64_t lpitch,
                                                              uint32_t *__restrict__ F) {
-    __shared__ uint32_t Ps[CT_WAVES][CT * CT_RUNS];
-    __shared__ uint64_t rows[CT_WAVES][CT];
-    const int wv = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const uint32_t t = blockIdx.x * CT_WAVES + wv;
+    constexpr int TILES = CT_WAVES / TW; // tiles a workgroup
+    constexpr int NJ = 4 / TW;           // 16-pixel chunks a thread loads
+    __shared__ uint32_t Ps[TILES][CT * CT_NODES];
+    __shared__ uint64_t rows[TILES][CT];
+    const int wv = threadIdx.x / (64 * TW), th = threadIdx.x % (64 * TW); // tile, thread of it
+    const uint32_t t = blockIdx.x * TILES + wv;
     if (t >= n_tiles) return;
     const CclTile T(t, tiles_x, H, W);
     uint32_t *P = Ps[wv];
     uint64_t *row_of = rows[wv];
     {
-        const int c0 = 16 * (lane & 3);
-        uint32_t bits[4];
+        const int c0 = 16 * (th & 3);
+        uint32_t bits[NJ];
         if (W >= 16) {
             // a chunk that leaves the image on the right loads the image's last
             // 16 columns, and its bits are shifted back
@@ -199,11 +317,11 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
             // Aligned words that hold the 16 pixels: a fifth word where the
             // pixels are not word-aligned (it holds the last of them, so no
             // word is read that holds none).
-            uint4 d[4];
-            uint32_t d4[4], sh[4];
+            uint4 d[NJ];
+            uint32_t d4[NJ], sh[NJ];
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t r = std::min<uint32_t>(16 * j + (lane >> 2), T.h - 1);
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t r = std::min<uint32_t>(16 * j + (th >> 2), T.h - 1);
                 const uintptr_t a = (uintptr_t)(img + (int64_t)(T.y0 + r) * pitch + (int64_t)T.x0 + cs);
                 const uint32_t *q = (const uint32_t *)(a & ~(uintptr_t)3);
                 sh[j] = (uint32_t)(a & 3);
@@ -211,7 +329,7 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
                 d4[j] = q[sh[j] ? 4 : 3];
             }
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
+            for (int j = 0; j < NJ; ++j)
                 bits[j] = (nonzero_bits(__builtin_amdgcn_alignbyte(d[j].y, d[j].x, sh[j])) |
                            nonzero_bits(__builtin_amdgcn_alignbyte(d[j].z, d[j].y, sh[j])) << 4 |
                            nonzero_bits(__builtin_amdgcn_alignbyte(d[j].w, d[j].z, sh[j])) << 8 |
@@ -219,8 +337,8 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
                           back;
         } else {
 #pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                const uint32_t r = std::min<uint32_t>(16 * j + (lane >> 2), T.h - 1);
+            for (int j = 0; j < NJ; ++j) {
+                const uint32_t r = std::min<uint32_t>(16 * j + (th >> 2), T.h - 1);
                 const uint8_t *p = img + (int64_t)(T.y0 + r) * pitch + T.x0;
                 bits[j] = 0;
                 for (int k = 0; k < 16 && c0 + k < (int)T.w; ++k)
@@ -228,97 +346,26 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__re
             }
         }
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const uint32_t r = 16 * j + (lane >> 2);
-            ((uint16_t *)row_of)[4 * r + (lane & 3)] = (uint16_t)(r < T.h ? bits[j] : 0u);
+        for (int j = 0; j < NJ; ++j) {
+            const uint32_t r = 16 * j + (th >> 2);
+            ((uint16_t *)row_of)[4 * r + (th & 3)] = (uint16_t)(r < T.h ? bits[j] : 0u);
         }
     }
-    ccl_wave_sync();
-    const uint64_t m = row_of[lane]; // lane = row from here on
+    if (TW == 1) ccl_wave_sync();
+    else __syncthreads();
     // the masks, in word order, coalesced
-    for (uint32_t j = lane; j < T.h * T.nw; j += 64) {
+    for (uint32_t j = th; j < T.h * T.nw; j += 64 * TW) {
         const uint32_t *half = (const uint32_t *)row_of;
         *T.word(labels, lpitch, j) = T.nw == 2 ? half[j] : half[2 * j];
     }
+    const uint64_t m = row_of[threadIdx.x & 63];
     if (__ballot(m != 0) == 0) return;
-    const uint64_t up = lane > 0 ? row_of[lane - 1] : 0ull;
-    const uint64_t s = m & ~(m << 1); // the runs' first pixels
-    // Columns at which a run makes a union: with the run above at the column
-    // itself (uC), or above-left (uL) or above-right (uR) of it.
-    uint64_t uC, uL = 0, uR = 0;
-    if (CONN == 4) {
-        uC = m & up;
-        uC &= ~(uC << 1);
+    // all four waves of a workgroup take a tile with rows of many runs, else one does
+    if (TW == 1 || __ballot(__popcll(m & ~(m << 1)) > CT_DENSE) == 0) {
+        if (th < 64) ccl_tile<CONN, 1>(T, W, th, P, row_of, F);
     } else {
-        uL = s & (up << 1);
-        uC = s & up & ~(up << 1);
-        uR = m & (up >> 1) & ~up;
+        ccl_tile<CONN, TW>(T, W, th, P, row_of, F);
     }
-    // the node of the run above that column x unites with (first: at x itself or
-    // to its left, else to its right)
-    auto above = [&](int x, bool right) -> uint32_t {
-        return run_node(lane - 1, up, right ? x + 1 : ((uL >> x) & 1) ? x - 1 : x);
-    };
-    // A run starts below the first run it unites with, which takes no atomic; the
-    // chains this makes down the rows are halved three times before anyone
-    // walks them; what a run touches besides is united then.
-    uint64_t left = uC | uL, right = uR;
-    for (uint64_t u = s; u; u &= u - 1) {
-        const int x = __builtin_ctzll(u);
-        const uint32_t node = (uint32_t)(lane * CT_RUNS + (x >> 1));
-        // this run's columns
-        const uint64_t gap = ~m & ~((2ull << x) - 1);
-        const uint64_t run = (gap ? (gap & -gap) - 1 : ~0ull) & ~((1ull << x) - 1);
-        const uint64_t l = left & run, r = right & run;
-        uint32_t parent = node;
-        if (l) {
-            parent = above(__builtin_ctzll(l), false);
-            left &= ~(l & -l);
-        } else if (r) {
-            parent = above(__builtin_ctzll(r), true);
-            right &= ~(r & -r);
-        }
-        P[node] = parent;
-    }
-    ccl_wave_sync();
-#pragma unroll 1
-    for (int k = 0; k < 3; ++k) {
-        for (uint64_t u = s; u; u &= u - 1) {
-            const uint32_t node = (uint32_t)(lane * CT_RUNS + (__builtin_ctzll(u) >> 1));
-            P[node] = P[P[node]];
-        }
-        ccl_wave_sync();
-    }
-    if (__ballot((left | right) != 0)) {
-        for (uint64_t u = left; u; u &= u - 1) {
-            const int x = __builtin_ctzll(u);
-            lunion(P, run_node(lane, m, x), above(x, false));
-        }
-        for (uint64_t u = right; u; u &= u - 1) {
-            const int x = __builtin_ctzll(u);
-            lunion(P, run_node(lane, m, x), above(x, true));
-        }
-    }
-    ccl_wave_sync();
-    // the forest entry of a node's root: root's linear index + 1
-    auto entry = [&](uint32_t node) -> uint32_t {
-        const uint32_t r = lfind(P, node);
-        const uint32_t rr = r / CT_RUNS, k = 2 * (r % CT_RUNS);
-        const uint64_t rm = row_of[rr];
-        // the run starts at column k, or else at k + 1
-        const uint32_t x = k + (((rm & ~(rm << 1)) >> k & 1) ? 0 : 1);
-        return T.first + rr * W + x + 1u;
-    };
-    for (uint64_t u = s; u; u &= u - 1) {
-        const int x = __builtin_ctzll(u);
-        F[T.first + lane * W + x] = entry(lane * CT_RUNS + (x >> 1));
-    }
-    if (m >> 63) F[T.first + lane * W + 63] = entry(run_node(lane, m, 63));
-    // first and last row, lane = column
-    const uint64_t m0 = row_of[0], m1 = row_of[T.h - 1];
-    if ((m0 >> lane) & 1) F[T.first + lane] = entry(run_node(0, m0, lane));
-    if ((m1 >> lane) & 1)
-        F[T.first + (T.h - 1) * W + lane] = entry(run_node((int)T.h - 1, m1, lane));
 }
 
 // ------------------------------------------------------------- border phase
@@ -327,11 +374,17 @@ __device__ __forceinline__ uint32_t gload(const uint32_t *p) {
     return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
-// Root index of x's tree in the global forest (entries: parent index + 1).
-__device__ __forceinline__ uint32_t gfind(const uint32_t *F, uint32_t x) {
+// Root index of x's tree in the global forest (entries: parent index + 1). Each second
+// pixel passed is put below its parent's parent. A plain store does: x is not a root and
+// never becomes one again, what is stored is an ancestor of x, and a merge whose minimum
+// on x's entry it overwrites goes on to merge with the parent that the minimum returned.
+__device__ __forceinline__ uint32_t gfind(uint32_t *F, uint32_t x) {
     uint32_t p = gload(F + x) - 1u;
     while (p != x) {
-        x = p;
+        const uint32_t g = gload(F + p) - 1u;
+        if (g == p) return p;
+        __hip_atomic_store(F + x, g + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        x = g;
         p = gload(F + x) - 1u;
     }
     return x;
@@ -365,14 +418,19 @@ __device__ __forceinline__ void gunion(uint32_t *F, uint32_t a, uint32_t b) {
 // the tiles above; where its runs straddle a tile border, the left-border
 // rule of those tiles joins them). Bound by the latency of the mask reads and
 // the few walks: 34 us on that image (204 us when border pixels were found
-// by reading the forest).
-template <int CONN>
+// by reading the forest). Dense images are bound by the walks: shortened on the way
+// (gfind), half foreground at random at 8192 x 8192 takes 116 us instead of 275.
+// With few tiles a workgroup of two waves takes a tile, one for each border (300 x 411
+// pixels, half of them foreground 18 -> 12 us).
+template <int CONN, bool SPLIT>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_t W,
                                                              uint32_t tiles_x, uint32_t n_tiles,
                                                              uint32_t *labels, int64_t lpitch,
                                                              uint32_t *__restrict__ F) {
     const int lane = threadIdx.x & 63;
-    const uint32_t t = blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
+    // SPLIT: a workgroup of two waves a tile, one for each border
+    const uint32_t wv = threadIdx.x >> 6;
+    const uint32_t t = SPLIT ? blockIdx.x : blockIdx.x * CT_WAVES + wv;
     if (t >= n_tiles) return;
     const CclTile T(t, tiles_x, H, W);
     const uint32_t tx = T.x0 / CT;
@@ -392,17 +450,19 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_
         if (CONN == 8 && tx + 1 < tiles_x)
             upR = CclTile(t - tiles_x + 1, tiles_x, H, W).mask(labels, lpitch, CT - 1) & 1;
     }
-    const uint64_t cb = __ballot((m & 1) != 0), lb = __ballot((l >> 63) != 0);
-    const uint64_t straight = cb & lb;
-    const uint32_t p = T.first + lane * W;
-    if (((straight & ~(straight << 1)) >> lane) & 1) gunion(F, p, p - 1);
-    if (CONN == 8 && lane > 0) {
-        const uint64_t d1 = cb & (lb << 1) & ~lb & ~(cb << 1); // (y, c) and (y - 1, l)
-        const uint64_t d2 = lb & (cb << 1) & ~cb & ~(lb << 1); // (y, l) and (y - 1, c)
-        if ((d1 >> lane) & 1) gunion(F, p, p - W - 1);
-        if ((d2 >> lane) & 1) gunion(F, p - 1, p - W);
+    if (!SPLIT || wv == 0) {
+        const uint64_t cb = __ballot((m & 1) != 0), lb = __ballot((l >> 63) != 0);
+        const uint64_t straight = cb & lb;
+        const uint32_t p = T.first + lane * W;
+        if (((straight & ~(straight << 1)) >> lane) & 1) gunion(F, p, p - 1);
+        if (CONN == 8 && lane > 0) {
+            const uint64_t d1 = cb & (lb << 1) & ~lb & ~(cb << 1); // (y, c) and (y - 1, l)
+            const uint64_t d2 = lb & (cb << 1) & ~cb & ~(lb << 1); // (y, l) and (y - 1, c)
+            if ((d1 >> lane) & 1) gunion(F, p, p - W - 1);
+            if ((d2 >> lane) & 1) gunion(F, p - 1, p - W);
+        }
     }
-    if (T.y0 == 0) return;
+    if (T.y0 == 0 || (SPLIT && wv == 0)) return;
     const uint64_t m0 = (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)m) |
                         (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane((uint32_t)(m >> 32)) << 32;
     const uint32_t q = T.first + lane;
@@ -431,7 +491,9 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_merge(uint32_t H, uint32_
 // the last-level cache, and the call is 3 % faster than with cached ones.
 // Two or eight tiles a workgroup instead of four: 3 to 4 % slower calls.
 // With few tiles (CT_FEW) a tile is split over the workgroup's waves, ROWS rows
-// each: 512 x 3712 pixels 6.3 us instead of 8.3 us.
+// each: 512 x 3712 pixels 6.3 us instead of 8.3 us. Dense tiles are bound by the walks:
+// four at a time, and of a whole tile's component once, take half foreground at random
+// at 8192 x 8192 from 249 to 111 us and one-pixel stripes from 558 to 166 us.
 template <int ROWS>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_t W,
                                                              uint32_t tiles_x, uint32_t n_tiles,
@@ -452,6 +514,7 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
     const uint64_t m = in ? T.mask(labels, lpitch, r0 + lane) : 0ull;
     const bool any = __ballot(m != 0) != 0;
     if (any) {
+        const uint32_t first = T.first + r0 * W; // this wave's first pixel
         const uint64_t s = m & ~(m << 1);
         const uint32_t n = (uint32_t)__popcll(s);
         uint32_t end = n; // inclusive scan over the rows
@@ -469,14 +532,63 @@ __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_write(uint32_t H, uint32_
         for (uint64_t u = s; u; u &= u - 1)
             list[at++] = T.first + (r0 + lane) * W + (uint32_t)__builtin_ctzll(u);
         ccl_wave_sync();
-        for (uint32_t i = lane; i < total; i += 64) {
-            // (the forest is at rest here: plain loads)
-            uint32_t e = list[i] + 1u, p = F[e - 1u];
-            while (p != e) {
-                e = p;
-                p = F[e - 1u];
+        // The forest is at rest here: plain loads
+        if (total <= 64) {
+            if ((uint32_t)lane < total) {
+                uint32_t e = list[lane] + 1u, p = F[e - 1u];
+                while (p != e) {
+                    e = p;
+                    p = F[e - 1u];
+                }
+                list[lane] = e;
             }
-            list[i] = e;
+        } else {
+            // WALKS at a time. A run whose parent lies in this wave's rows takes the
+            // label of the parent's run, so that a component of the tile is walked to
+            // its root once and not by each of its runs (split tiles: their rows are few).
+            for (uint32_t i = lane; i < total; i += 64 * WALKS) {
+                uint32_t e[WALKS], p[WALKS];
+#pragma unroll
+                for (int k = 0; k < WALKS; ++k) e[k] = list[std::min(i + 64 * k, total - 1)] + 1u;
+#pragma unroll
+                for (int k = 0; k < WALKS; ++k) p[k] = F[e[k] - 1u];
+                bool on = false;
+                uint32_t in_tile = 0; // bit k: list[..] is to be the rank in e[k]
+#pragma unroll
+                for (int k = 0; k < WALKS; ++k) {
+                    const uint32_t d = p[k] - 1u - first, y = d / W, x = d - y * W;
+                    if (ROWS == CT && p[k] != e[k] && p[k] > first && y < ROWS && x < T.w) {
+                        const uint64_t rm = row_of[y];
+                        e[k] = base_of[y] + (uint32_t)__popcll((rm & ~(rm << 1)) & ((2ull << x) - 1)) - 1u;
+                        p[k] = e[k];
+                        in_tile |= 1u << k;
+                    }
+                    on |= p[k] != e[k];
+                }
+                while (on) {
+                    on = false;
+                    uint32_t q[WALKS];
+#pragma unroll
+                    for (int k = 0; k < WALKS; ++k) q[k] = (in_tile >> k) & 1u ? p[k] : F[p[k] - 1u];
+#pragma unroll
+                    for (int k = 0; k < WALKS; ++k) {
+                        e[k] = p[k];
+                        p[k] = q[k];
+                        on |= p[k] != e[k];
+                    }
+                }
+#pragma unroll
+                for (int k = 0; k < WALKS; ++k)
+                    if (i + 64 * k < total) list[i + 64 * k] = (in_tile >> k) & 1u ? e[k] | RANK : e[k];
+            }
+            ccl_wave_sync();
+            for (uint32_t i = lane; ROWS == CT && i < total; i += 64) {
+                uint32_t e = lds_load(list + i);
+                if (!(e & RANK)) continue;
+                do e = lds_load(list + (e & ~RANK)); // (parents come first: this ends)
+                while (e & RANK);
+                list[i] = e;
+            }
         }
     }
     // (the masks have been read: the tile's loads are done before its stores)
@@ -841,18 +953,20 @@ int mr_ccl(const void *img, void *labels, int64_t H, int64_t W, int64_t pitch,
     const uint32_t tx = (w + CT - 1) / CT, tiles = tx * ((h + CT - 1) / CT);
     const bool few = tiles < CT_FEW;
     const dim3 grid(few ? tiles : (tiles + CT_WAVES - 1) / CT_WAVES), wide(64 * CT_WAVES);
-    const dim3 block = few ? dim3(64) : wide;
     auto launch = [&](auto local, auto merge, auto write) {
-        hipLaunchKernelGGL(local, grid, block, 0, s, (const uint8_t *)img, h, w, pitch, tx, tiles,
+        hipLaunchKernelGGL(local, grid, wide, 0, s, (const uint8_t *)img, h, w, pitch, tx, tiles,
                            L, label_pitch, F);
-        hipLaunchKernelGGL(merge, grid, block, 0, s, h, w, tx, tiles, L, label_pitch, F);
+        hipLaunchKernelGGL(merge, grid, few ? dim3(128) : wide, 0, s, h, w, tx, tiles, L, label_pitch,
+                           F);
         hipLaunchKernelGGL(write, grid, wide, 0, s, h, w, tx, tiles, L, label_pitch, F);
     };
     const auto write = few ? k_ccl_write<CT / CT_WAVES> : k_ccl_write<CT>;
     if (conn == 8)
-        launch(few ? k_ccl_local<8, 1> : k_ccl_local<8, CT_WAVES>, k_ccl_merge<8>, write);
+        launch(few ? k_ccl_local<8, CT_WAVES> : k_ccl_local<8, 1>,
+               few ? k_ccl_merge<8, true> : k_ccl_merge<8, false>, write);
     else
-        launch(few ? k_ccl_local<4, 1> : k_ccl_local<4, CT_WAVES>, k_ccl_merge<4>, write);
+        launch(few ? k_ccl_local<4, CT_WAVES> : k_ccl_local<4, 1>,
+               few ? k_ccl_merge<4, true> : k_ccl_merge<4, false>, write);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? MR_OK : chip(e, "ccl");
 }

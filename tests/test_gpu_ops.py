@@ -263,6 +263,26 @@ def test_ccl_tile_edges(shape, pad, lpad, conn):
         assert bool((out[:, W:] == -9).all())
 
 
+# Tiles of many runs, of an image with few tiles and of one with many: 4 and 5 runs a row
+# (beside single dots: 64 and 65 runs a tile), stripes joined at the far end, whose trees
+# cross every tile of a column, checkers, and dense noise.
+@pytest.mark.parametrize("shape", [(130, 200), (4096, 2112)])
+@pytest.mark.parametrize("conn", [4, 8])
+def test_ccl_dense_tiles(shape, conn):
+    H, W = shape
+    rng = np.random.default_rng(H)
+    y, x = np.arange(H)[:, None], np.arange(W)[None]
+    comb = np.broadcast_to(x % 2 == 0, shape).copy()
+    comb[-1] = True
+    comb[:, 101] = False
+    four = (x % 16 == 3) & (y % 4 == 1)  # 16 rows of 4 runs: 64 a tile
+    more = four | ((x % 64 == 20) & (y % 64 == 9))  # 65 runs, one row of 5
+    for img in (comb, four, more, (x + y) % 2 == 0, rng.random(shape) < 0.6):
+        img = img.astype(np.uint8)
+        print(f"[gpu] ccl dense {shape} conn{conn}", flush=True)
+        check(ops.ccl(to_dev(img), conn).cpu().numpy(), oracle.ccl(img, conn))
+
+
 # Both sides of the labels' tile count line (2046 and 2048 tiles of 64 x 64) and
 # of the area filter's line for marks (16250 and 16640 chunks of 64 words).
 @pytest.mark.parametrize("H", [64000, 65472, 65536])
