@@ -26,7 +26,10 @@
  *  - Images are row-major, element (y, x) at index y * pitch + x; pitch is in
  *    elements, pitch >= W, and 0 means W; H * pitch must be below 2^32.
  *    Pixel types: MR_U8 (uint8) and MR_I32 (int32, full signed range).
- *    Image pointers are aligned to the pixel size. For MR_U8 the working
+ *    Image pointers are aligned to the pixel size. MR_U8 images are read in
+ *    aligned 16-byte words from the one that holds the first pixel to the 32-bit
+ *    word that holds the last, gaps between rows included; what lies there
+ *    beside the pixels does not matter. For MR_U8 the working
  *    image is updated with 32-bit compare-and-swap on the aligned words that
  *    hold its pixels, so the allocation must cover those whole words and no
  *    other agent may write bytes that share a word with the image while a
@@ -68,7 +71,9 @@ enum {
 
 enum { MR_OP_RECON = 0, MR_OP_FILL = 1 };
 
-/* Tuning knobs. A NULL mr_tune* means "use the defaults" (mr_default_tune).
+/* Tuning knobs. A NULL mr_tune* leaves the schedule to the library: the defaults
+ * (mr_default_tune), except that int32 launches that reconstruct take two sweep
+ * iterations in the first round unless MR_TUNE_FIRST_SWEEPS is set.
  * No knob changes the result, only the time it takes. */
 typedef struct {
     int32_t sweep_rounds;      /* tile rounds before the queue phase (1..1000);
@@ -125,8 +130,8 @@ typedef struct {
  * MR_TUNE_SWEEP_ROUNDS, MR_TUNE_MAX_SWEEPS, MR_TUNE_PERSISTENT_BLOCKS,
  * MR_TUNE_CONVERGE_ROUNDS, MR_TUNE_TAIL_ROUNDS or MR_TUNE_FIRST_SWEEPS
  * replaces that field's default when it is a whole number in the field's
- * valid range (it is ignored otherwise). Calls given a NULL mr_tune* use
- * these defaults too. */
+ * valid range (it is ignored otherwise). Calls given a NULL mr_tune* start
+ * from these defaults too. */
 void mr_default_tune(mr_tune *out);
 
 /* Workspace bytes needed by one mr_recon_dilate (op = MR_OP_RECON) or

@@ -12,7 +12,7 @@
  * Conventions (as in mr.h): every image pointer is a DEVICE pointer owned by
  * the caller; rows are `pitch` elements apart (0 means W); H, W >= 1; uint8
  * images are read in aligned 32-bit words, each holding at least one of the
- * image's pixels; the
+ * image's pixels (by h-dome and regional maxima as mr.h's calls read them); the
  * library allocates no device memory, scratch space is the caller's
  * workspace (256-byte aligned, contents on entry irrelevant) whose size the
  * *_workspace_bytes call gives; `stream` is a hipStream_t as void* (NULL =

@@ -26,8 +26,7 @@
 // A merge links the larger of two roots below the smaller
 // with an atomic minimum on the larger's parent; if another merge got there
 // first, the atomic returns the new parent and the merge goes on from it.
-// Parents only ever decrease and stay below their children, so every walk
-// ends at a root.
+// Parents stay below their children, so every walk ends at a root.
 //
 // Area threshold: the map step reads each pixel's label; the reduction counts
 // pixels per label with device atomic adds into one counter per possible
@@ -58,9 +57,6 @@ int chip(hipError_t e, const char *what) {
 }
 
 size_t up256(size_t n) { return (n + 255) / 256 * 256; }
-
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
 
 constexpr int CT = 64;              // tile side: a row is one 64-bit mask, lane = row
 constexpr int CT_RUNS = CT / 2;     // a row holds at most this many runs
@@ -119,12 +115,6 @@ __device__ __forceinline__ void lunion(uint32_t *P, uint32_t a, uint32_t b) {
         if (old == b) return; // b was still a root: linked
         b = old;              // b was linked meanwhile: go on from its parent
     }
-}
-
-// Bit k set for every nonzero byte k of x.
-__device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
-    const uint32_t top = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
-    return ((top >> 7) * 0x10204080u) >> 28;
 }
 
 // The run of a row (mask m) that holds column x: its first column.

@@ -115,14 +115,6 @@ constexpr int DW_ROW = DW_IN / 4 + 1; // dwords per row of the byte tile: odd, n
 constexpr uint32_t DW_FAR = 0xFFu; // byte of a pixel further than DW_MAX
 static_assert(DW_MAX < 1 << DW_SLICES && DW == 2 * 64, "a lane holds two rows");
 
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
-
-// Bit k set for every nonzero byte k of x.
-__device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
-    const uint32_t top = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
-    return ((top >> 7) * 0x10204080u) >> 28;
-}
 // Lane i gets lane i-1's (i+1's) value; all ones come in at the wave's ends.
 __device__ __forceinline__ uint32_t ones_from_left(uint32_t v) {
     return (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, 0x138 /* wave_shr:1 */, 0xF, 0xF,

@@ -10,6 +10,15 @@
 
 namespace mr {
 
+typedef uint32_t v4u __attribute__((ext_vector_type(4)));
+typedef v4u v4u_dw __attribute__((aligned(4))); // on any dword
+
+// Bit k set for every nonzero byte k of x.
+__device__ __forceinline__ uint32_t nonzero_bits(uint32_t x) {
+    const uint32_t top = (((x & 0x7F7F7F7Fu) + 0x7F7F7F7Fu) | x) & 0x80808080u;
+    return ((top >> 7) * 0x10204080u) >> 28;
+}
+
 // Register tile: 64 lanes x 64 rows of 32-bit keys, whose outer ring is a
 // frozen halo, so each tile owns a 62 x 62 interior. Tile (ty, tx) covers
 // image rows ty*62-1 .. ty*62+62 and columns tx*62-1 .. tx*62+62.

@@ -203,8 +203,6 @@ constexpr int STAGE_BYTES = TS * SROW;
 static_assert(STAGE_PAD + 2 * STAGE_BYTES <= TS * (TS + 1) * 4,
               "the stage must fit in the transpose buffer");
 
-typedef uint32_t v4u __attribute__((ext_vector_type(4)));
-
 // Byte offset of pixel (gy, gx) from the plane's aligned start (mod 2^32: a
 // tile at the image's left edge starts before its row, in row 0 before the
 // plane, where the offset wraps out of the resource's range).
@@ -936,9 +934,9 @@ __device__ __forceinline__ uint32_t mark_neighbours(const ImgDesc &d, int lane, 
 }
 
 // PIPE (the pipelined round kernel; implies a stage the caller has written
-// and synchronized): on the round path, after the marking atomics are issued
-// and before the stores, the visit issues the stage loads of the next tile
-// (*dn, tn) when has_next, and returns them; otherwise it returns zeros.
+// and synchronized): after the stores and once the marking atomics are issued
+// the visit issues the stage loads of the next tile (*dn, tn) when has_next, and
+// returns them; otherwise it returns zeros.
 template <typename T, int CONN, bool TAIL = false, bool PIPE = false, bool NEEDJ = true>
 __device__ __forceinline__ StageWords visit_tile(const ImgDesc &d, int64_t t, int lane,
                                                  uint32_t *__restrict__ flags, Appender &app,
@@ -1271,9 +1269,9 @@ __global__ __launch_bounds__(64, 2) void k_tile_round(Imgs imgs, int64_t n_tiles
 // The same round for launches whose images are all uint8 (of a size the stage
 // reaches), software-pipelined
 // over the block's tiles: the stage loads of the next tile are issued during
-// the current visit, after its marking atomics and before its stores, so
+// the current visit, behind its stores and marking atomics, so
 // that their memory latency (and that of the next list entry and
-// descriptor) overlaps the current tile's stores and the wait for its marks
+// descriptor) overlaps the wait for the marks and the append to the list
 // instead of starting the next visit. The loads land in registers that the
 // sweeps no longer need; the next visit writes them to the stage. With V < 0
 // (mixed batches, the server) a visit's kind is read from its image.

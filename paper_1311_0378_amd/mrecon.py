@@ -462,7 +462,8 @@ class Server:
         memory of the job's shape, unit-stride rows) receives the result; by
         default a pinned buffer is allocated. CUDA tensors make a device job
         (MR_JOB_DEVICE): the result goes to ``out``, a device tensor (by
-        default a new one). Returns the job id, or None if there is no room
+        default a new one), and later work on the server's stream may
+        overwrite the inputs. Returns the job id, or None if there is no room
         right now."""
         if op is None:
             op = MR_OP_RECON if mask is not None else MR_OP_FILL
