@@ -715,9 +715,9 @@ __device__ __forceinline__ int64_t area_word(uint32_t i, uint32_t Wq, int64_t pi
 // chunks, or a fixed grid of 4096 blocks walking the plane, made the call 1 and 13 %
 // slower. On dense labels the atomics bound it: blocks take a large plane in eight bands, so
 // that those which run together add to fewer of the same counters (squares of 300
-// pixels 509 -> 269 us), and a chunk of short runs goes through LDS, so that an atomic
-// instruction's lanes hold neighbouring pixels, whose labels often share a cache line
-// (one-pixel stripes at 11584 x 11584 901 -> 552 us; the two cost 1.6 % foreground 5 us).
+// pixels 509 -> 256 us, 1.6 % foreground 204 -> 218 us), and a chunk of short runs goes
+// through LDS, so that an atomic instruction's lanes hold neighbouring pixels, whose
+// labels often share a cache line (one-pixel stripes at 11584 x 11584 901 -> 552 us).
 template <bool LIN>
 __global__ __launch_bounds__(256) void k_area_count4(const int32_t *__restrict__ labels,
                                                      uint32_t N, uint32_t NQ, uint32_t Wq,
