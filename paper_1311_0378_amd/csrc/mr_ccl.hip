@@ -165,8 +165,9 @@ struct CclTile {
 // run that begins above-right of it.
 // A run's first union takes no atomic: the run is put below the run above it,
 // and the chains that this makes down the tile's rows are halved three times (by four
-// waves until they are flat) before they are walked (512 x 3712 pixels, 20 %
-// foreground: 7.0 us, 15.8 us with every union by walk and atomic minimum).
+// waves once: 300 x 411 pixels, half foreground at random, 15 us, 19 us when halved until
+// they were flat) before they are walked (512 x 3712 pixels, 20 % foreground: 7.0 us,
+// 15.8 us with every union by walk and atomic minimum).
 template <int CONN, int TW>
 __device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, uint32_t *P,
                                          const uint64_t *row_of, uint32_t *__restrict__ F) {
@@ -174,7 +175,6 @@ __device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, u
         if (TW == 1) ccl_wave_sync();
         else __syncthreads();
     };
-    auto any = [](bool x) -> bool { return TW == 1 ? __ballot(x) != 0 : __syncthreads_or(x); };
     const int row = TW == 1 ? th : th >> 2;
     const uint64_t mine = TW == 1 ? ~0ull : 0xFFFFull << (16 * (th & 3));
     const uint64_t m = row_of[row];
@@ -198,7 +198,7 @@ __device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, u
         return run_node(row - 1, up, right ? x + 1 : ((uL >> x) & 1) ? x - 1 : x);
     };
     // A run starts below the first run it unites with, which takes no atomic; the
-    // chains this makes down the rows are halved three times before anyone
+    // chains this makes down the rows are halved before anyone
     // walks them; what a run touches besides is united then.
     const uint64_t at = uC | uL;
     uint64_t left = 0, right = 0; // what is left to unite
@@ -223,15 +223,11 @@ __device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, u
     }
     sync();
 #pragma unroll 1
-    for (int k = 0; k < (TW == 1 ? 3 : 6); ++k) {
-        bool moved = false;
+    for (int k = 0; k < (TW == 1 ? 3 : 1); ++k) {
         for (uint64_t u = s; u; u &= u - 1) {
             const uint32_t node = (uint32_t)(row * CT_NODES + (__builtin_ctzll(u) >> 1));
-            const uint32_t p = P[node], g = P[p];
-            P[node] = g;
-            moved |= g != p;
+            P[node] = P[P[node]];
         }
-        if (TW > 1 && !any(moved)) break;
         sync();
     }
     if (TW > 1 || __ballot((left | right) != 0)) {
@@ -278,7 +274,7 @@ __device__ __forceinline__ void ccl_tile(const CclTile &T, uint32_t W, int th, u
 // a walk put below their parent's parent, take 4096 x 4096 one-pixel stripes from 234 to
 // 77 us, half foreground at random (conn 8) from 72 to 53 us. With few tiles, whose time is one
 // tile's, four waves share a tile with rows of many runs: 300 x 411 pixels, half of them
-// foreground at random, 33 -> 19 us.
+// foreground at random, 33 -> 15 us.
 template <int CONN, int TW>
 __global__ __launch_bounds__(64 * CT_WAVES) void k_ccl_local(const uint8_t *__restrict__ img,
                                                              uint32_t H, uint32_t W, int64_t pitch,
